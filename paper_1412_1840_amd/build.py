@@ -17,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqmi.so")
-SOURCES = ["qmi_kernels.hip", "qmi_search.hip", "qmi_bands.hip", "qmi_prep.hip", "qmi_api.hip"]
+SOURCES = ["qmi_kernels.hip", "qmi_modes.hip", "qmi_search.hip", "qmi_bands.hip", "qmi_prep.hip", "qmi_api.hip"]
 PROBE = os.path.join(HERE, "valu_rates")
 ARCH = "gfx950"
 
@@ -34,6 +34,9 @@ def flags():
     # f0 + k * df are rounded twice exactly as the definition states (explicit fma() calls in the
     # kernels are unaffected).
     return ["-O3", "-std=c++17", "-fPIC", "--offload-arch=" + ARCH, "-ffp-contract=off",
+            # No SLP vectorisation: pairing scalar float code costs conversions and moves here (packed
+            # FP32 is off), and it splits the half-precision fused conversions of the mode sums.
+            "-fno-slp-vectorize",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-I", os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function"]
 

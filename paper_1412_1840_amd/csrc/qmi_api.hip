@@ -57,7 +57,8 @@ struct qmi_ctx {
         kT, kY, kE, kCP, kOrder, kRowStart, kK, kR, kRP, kRD, kKS, kCoarse, kCoarse2, kFine, kFine2,
         kIps, kPeakK, kNpk, kWin, kArgmax, kRes, kFreqs, kProbe, kTS, kYS, kBandT, kBandCnt,
         kBandId, kS, kTrials, kTrialK, kPOff, kPStIn, kPCnt, kPSt, kPDet, kPTo, kPYo, kPEo,
-        kPPer, kPart, kNumBufs
+        kPPer, kPart, kModeC, kModeTs, kModeRows, kModeFrag, kModePart, kModeB, kModeCoef, kTieCnt, kTieSlot,
+        kTieScore, kNumBufs
     };
     Buf bufs[kNumBufs];
     static_assert(kNumBufs <= 64, "one bit per buffer in in_use");
@@ -73,6 +74,9 @@ struct qmi_ctx {
     std::vector<uint64_t> graph_key;
     // Autotuner: pair-kernel variant per length bucket (-1: not tuned yet).
     int tuned[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
+    // Harmonic groups of the mode sums at the last call's (smallest) sigma_t.
+    double mode_sigma_t = 0.0;
+    int mode_groups = 0;
     // Spurious-period masks applied by the selection kernels (qmi_set_masks).
     qmi::MaskDev masks{};
     // Serving.
@@ -190,6 +194,12 @@ T* dptr(qmi_ctx* ctx, int id) {
     return reinterpret_cast<T*>(ctx->ws_base ? ctx->ws_ptr[id] : ctx->bufs[id].p);
 }
 
+int scratch_full(qmi_ctx* ctx) {
+    set_err(ctx, "the call needs more than the %zu bytes of scratch memory available to "
+            "qmi_periodogram_noalloc", ctx->ws_size);
+    return QMI_ENOMEM;
+}
+
 // A buffer of the current call: the context's own (grown on demand, see ensure), or in scratch
 // mode the next 256-byte aligned piece of the scratch array.  Scratch mode never allocates.
 int acquire(qmi_ctx* ctx, int id, size_t bytes) {
@@ -197,9 +207,7 @@ int acquire(qmi_ctx* ctx, int id, size_t bytes) {
     if (bytes == 0) bytes = 256;
     const size_t at = (ctx->ws_used + 255) / 256 * 256;
     if (at > ctx->ws_size || bytes > ctx->ws_size - at) {
-        set_err(ctx, "the call needs more than the %zu bytes of scratch memory available to "
-                "qmi_periodogram_noalloc", ctx->ws_size);
-        return QMI_ENOMEM;
+        return scratch_full(ctx);
     }
     ctx->ws_ptr[id] = ctx->ws_base + at;
     ctx->ws_used = at + bytes;
@@ -393,9 +401,31 @@ void record(qmi_ctx* ctx) {
     (void)hipEventRecord(ctx->ev[ctx->ev_used++], ctx->stream);
 }
 
+// Harmonics that the mode sums keep at a periodic-kernel width, as nodes_kernel counts them: the
+// coefficients 2 e^-k I_m(k), k = 1 / sigma_t^2, by the trapezoid rule.
+int mode_count(double sigma_t) {
+    const int cap = (int)(7.0 / sigma_t) + 8, L = 3 * cap + 32;
+    const double kap = 1.0 / (sigma_t * sigma_t), turn = 2.0 * M_PI / L;
+    std::vector<double> co(L), ev(L);
+    for (int j = 0; j < L; ++j) {
+        co[j] = std::cos(turn * j);
+        ev[j] = std::exp(kap * (co[j] - 1.0));
+    }
+    double tail = 0.0;
+    for (int m = cap; m > 1; --m) {
+        double s = 0.0;
+        for (int j = 0; j < L; ++j) s += ev[j] * co[(int64_t)m * j % L];
+        tail += 2.0 * s / L;
+        if (tail > kModeTail) return m;
+    }
+    return 1;
+}
+
+// Runs one group.  pairs_only: every curve by the pair sums (curves that the mode sums left to
+// them); *left receives the curves of the group that the mode sums left.
 template <typename R>
 int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group& g,
-              std::vector<int32_t>& pair_event_idx) {
+              std::vector<int32_t>& pair_event_idx, bool pairs_only, std::vector<int32_t>* left) {
     begin_use(ctx);
     const int32_t nc = g.c1 - g.c0;
     const int64_t ns = g.s1 - g.s0;
@@ -407,6 +437,23 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     std::vector<int32_t> order(nc);
     std::vector<int64_t> row_start(nc);
     int64_t koff = 0, poff = 0, ksoff = 0, rows = 0, pieces = 0;
+    std::vector<ModeCurve> mc(nc);
+    std::memset(mc.data(), 0, nc * sizeof(ModeCurve));
+    int64_t mblocks = 0;
+    int64_t all_k = 0, all_p = 0, all_ks = 0;  // the pair sums' tables if they took every curve
+    int32_t n_modes = 0;  // curves whose sums are taken over modes
+    int max_mode_n = 2;
+    const bool rule_t = kp->sigma_t == QMI_SIGMA_T_SKEWNESS;
+    const double min_sigma_t = !rule_t ? kp->sigma_t
+                               : kp->skew_lambda > 0.0 ? kp->skew_lambda : QMI_SKEW_LAMBDA;
+    const bool mixed = kp->precision == QMI_PREC_MIXED && !pairs_only;
+    if (mixed && ctx->mode_sigma_t != min_sigma_t) {
+        ctx->mode_sigma_t = min_sigma_t;
+        ctx->mode_groups = min_sigma_t * kModeCapMax > 8.0
+                               ? (mode_count(min_sigma_t) + kModeGroup - 1) / kModeGroup : 0;
+    }
+    const int mode_groups = mixed ? ctx->mode_groups : 0;
+    const int mode_cap = mode_groups * kModeGroup + 8;
     constexpr int kPassR = kWaves * rows_per_wave<R>();
     int max_n = 2, max_pieces = 0;
     for (int32_t i = 0; i < nc; ++i) {
@@ -421,7 +468,24 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         p.sigma_t = kp->sigma_t;
         p.sigma_y_rule = kp->sigma_y;
         p.sigma_y = NAN;
+        row_start[i] = rows;
+        order[i] = i;
         if (p.status == QMI_OK) {
+            const int64_t np = round_up(p.n, kPass);
+            all_k += p.n * np;
+            all_p += np;
+            all_ks += (int64_t)((p.n + kPassR - 1) / kPassR) * kWaves * p.n;
+        }
+        const int room = mode_groups > 0 ? mode_room(p.n, mode_groups) : 0;
+        if (p.status == QMI_OK && room >= (p.n + 31) / 32 + 2) {
+            ModeCurve& m = mc[i];
+            m.cap = room;
+            m.boff = mblocks;
+            mblocks += m.cap;
+            ++n_modes;
+            max_mode_n = std::max(max_mode_n, p.n);
+            max_n = std::max(max_n, p.n);
+        } else if (p.status == QMI_OK) {
             p.npad = (int32_t)round_up(p.n, kPass);
             p.koff = koff;
             p.poff = poff;
@@ -433,19 +497,18 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             p.pqoff = pieces;
             pieces += (int64_t)nbp * (nbp + 1) / 2;
             max_pieces = std::max(max_pieces, nbp * (nbp + 1) / 2);
-            row_start[i] = rows;
             rows += p.n;
             max_n = std::max(max_n, p.n);
-        } else {
-            row_start[i] = rows;
         }
-        order[i] = i;
     }
-    // Largest work first: the dispatcher hands out work items in order.
+    // The curves summed over modes first, then the others; among each, largest work first (the
+    // dispatcher hands out work items in order).
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t c) {
+        if ((mc[a].cap > 0) != (mc[c].cap > 0)) return mc[a].cap > 0;
         const int64_t na = cp[a].status ? 0 : cp[a].n, nb = cp[c].status ? 0 : cp[c].n;
         return na > nb;
     });
+    const int32_t n_pairs = nc - n_modes;
 
     const qmi_bands* bp = cs.bands;
     const bool search = !cs.periodogram && !bp;
@@ -458,6 +521,16 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     const int score_kind = cs.periodogram ? cs.score : bp ? bp->score : cs.search->score;
 
     int rc;
+    if (ctx->ws_base && n_modes) {
+        // Scratch memory holds the pair sums' tables of every curve (any of them may be left to
+        // the pair sums, and the mode tables are smaller), or the call is refused.
+        size_t at = 0;
+        for (size_t bytes : {nc * sizeof(CurveParams), nc * sizeof(int32_t), nc * sizeof(int64_t),
+                             (size_t)all_k * sizeof(R), (size_t)all_p * 8, (size_t)ns * 8,
+                             (size_t)all_ks * sizeof(R)})
+            at = (at + 255) / 256 * 256 + std::max<size_t>(bytes, 1);
+        if (at > ctx->ws_size) return scratch_full(ctx);
+    }
 #define ENSURE(id, bytes) \
     if ((rc = acquire(ctx, id, (bytes))) != QMI_OK) return rc
     if (!cs.dev_inputs) {
@@ -468,10 +541,26 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     ENSURE(qmi_ctx::kCP, nc * sizeof(CurveParams));
     ENSURE(qmi_ctx::kOrder, nc * sizeof(int32_t));
     ENSURE(qmi_ctx::kRowStart, nc * sizeof(int64_t));
-    ENSURE(qmi_ctx::kK, std::max<int64_t>(koff, 1) * sizeof(R));
-    ENSURE(qmi_ctx::kRP, std::max<int64_t>(poff, 1) * 8);
-    ENSURE(qmi_ctx::kRD, std::max<int64_t>(ns, 1) * 8);
-    ENSURE(qmi_ctx::kKS, std::max<int64_t>(ksoff, 1) * sizeof(R));
+    if (n_pairs) {
+        ENSURE(qmi_ctx::kK, std::max<int64_t>(koff, 1) * sizeof(R));
+        ENSURE(qmi_ctx::kRP, std::max<int64_t>(poff, 1) * 8);
+        ENSURE(qmi_ctx::kRD, std::max<int64_t>(ns, 1) * 8);
+        ENSURE(qmi_ctx::kKS, std::max<int64_t>(ksoff, 1) * sizeof(R));
+    }
+    if (n_modes) {
+        ENSURE(qmi_ctx::kModeC, nc * sizeof(ModeCurve));
+        ENSURE(qmi_ctx::kModeTs, mblocks * 256);
+        ENSURE(qmi_ctx::kModeRows, mblocks * 4);
+        ENSURE(qmi_ctx::kModeFrag, mblocks * 4096);
+        ENSURE(qmi_ctx::kModePart, mblocks * 256);
+        ENSURE(qmi_ctx::kModeB, mblocks * 256);
+        if (refine) {
+            ENSURE(qmi_ctx::kTieCnt, nc * 4);
+            ENSURE(qmi_ctx::kTieSlot, nc * (int64_t)kTieMax * 4);
+            ENSURE(qmi_ctx::kTieScore, nc * (int64_t)kTieMax * 8);
+        }
+        ENSURE(qmi_ctx::kModeCoef, nc * (int64_t)mode_stride(mode_cap) * 8);
+    }
     if (!(cs.periodogram && cs.dev_outputs)) ENSURE(qmi_ctx::kCoarse, nc * F1 * 8);
     if (!cs.periodogram) ENSURE(qmi_ctx::kCoarse2, nc * F1 * 8);
     if (refine) {
@@ -506,16 +595,19 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     constexpr int64_t kSplitBelow = 2048;
     constexpr int64_t kSplitMaxBytes = int64_t(256) << 20;
     const int64_t tiles1 = (F1 + 63) / 64, tiles2 = (F2 + 63) / 64;
-    const int64_t part_bytes = pieces * std::max(F1, F2) * 24;
-    bool split1 = max_pieces > 1 && nc * tiles1 < kSplitBelow;
-    bool split2 = refine && max_pieces > 1 && nc * tiles2 < kSplitBelow;
-    if ((split1 || split2) &&
+    const int64_t mode_parts = (int64_t)n_modes * mode_groups;
+    const int64_t part_bytes = std::max(pieces, mode_parts) * std::max(F1, F2) * 24;
+    bool split1 = max_pieces > 1 && n_pairs * tiles1 < kSplitBelow;
+    bool split2 = refine && max_pieces > 1 && n_pairs * tiles2 < kSplitBelow;
+    bool msplit1 = mode_groups > 1 && n_modes * tiles1 < kSplitBelow;
+    bool msplit2 = refine && mode_groups > 1 && n_modes * tiles2 < kSplitBelow;
+    if ((split1 || split2 || msplit1 || msplit2) &&
         (part_bytes > kSplitMaxBytes || (size_t)part_bytes > ctx->budget / 8 ||
          acquire(ctx, qmi_ctx::kPart, part_bytes) != QMI_OK)) {
-        split1 = split2 = false;
+        split1 = split2 = msplit1 = msplit2 = false;
         ctx->err.clear();
     }
-    double* dpart = (split1 || split2) ? dptr<double>(ctx, qmi_ctx::kPart) : nullptr;
+    double* dpart = (split1 || split2 || msplit1 || msplit2) ? dptr<double>(ctx, qmi_ctx::kPart) : nullptr;
 
     hipStream_t st = ctx->stream;
     const double* t = cs.dev_inputs ? b->t + g.s0 : dptr<double>(ctx, qmi_ctx::kT);
@@ -534,7 +626,26 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     const hipMemcpyKind h2d = hipMemcpyHostToDevice;
     HIP_OK(ctx, hipMemcpyAsync(dcp, cp.data(), nc * sizeof(CurveParams), h2d, st));
     HIP_OK(ctx, hipMemcpyAsync(dorder, order.data(), nc * sizeof(int32_t), h2d, st));
-    HIP_OK(ctx, hipMemcpyAsync(drow, row_start.data(), nc * sizeof(int64_t), h2d, st));
+    if (n_pairs)
+        HIP_OK(ctx, hipMemcpyAsync(drow, row_start.data(), nc * sizeof(int64_t), h2d, st));
+    ModeDev md{};
+    TieDev tie{};
+    if (n_modes) {
+        md.curves = dptr<ModeCurve>(ctx, qmi_ctx::kModeC);
+        md.ts = dptr<double>(ctx, qmi_ctx::kModeTs);
+        md.rows = dptr<int32_t>(ctx, qmi_ctx::kModeRows);
+        md.frag = dptr<char>(ctx, qmi_ctx::kModeFrag);
+        md.part = dptr<double>(ctx, qmi_ctx::kModePart);
+        md.b = dptr<double>(ctx, qmi_ctx::kModeB);
+        md.coef = dptr<double>(ctx, qmi_ctx::kModeCoef);
+        if (refine)
+            tie = TieDev{dptr<int32_t>(ctx, qmi_ctx::kTieCnt),
+                         dptr<int32_t>(ctx, qmi_ctx::kTieSlot),
+                         dptr<double>(ctx, qmi_ctx::kTieScore), md.curves};
+        md.mode_cap = mode_cap;
+        md.max_groups = mode_groups;
+        HIP_OK(ctx, hipMemcpyAsync(md.curves, mc.data(), nc * sizeof(ModeCurve), h2d, st));
+    }
     const double* dfreqs = nullptr;
     if (cs.periodogram) {
         if (cs.dev_inputs) {
@@ -545,10 +656,10 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         }
     }
 
-    R* K = dptr<R>(ctx, qmi_ctx::kK);
-    double* rp = dptr<double>(ctx, qmi_ctx::kRP);
-    double* rd = dptr<double>(ctx, qmi_ctx::kRD);
-    R* ks = dptr<R>(ctx, qmi_ctx::kKS);
+    R* K = n_pairs ? dptr<R>(ctx, qmi_ctx::kK) : nullptr;
+    double* rp = n_pairs ? dptr<double>(ctx, qmi_ctx::kRP) : nullptr;
+    double* rd = n_pairs ? dptr<double>(ctx, qmi_ctx::kRD) : nullptr;
+    R* ks = n_pairs ? dptr<R>(ctx, qmi_ctx::kKS) : nullptr;
 
     FreqPlan fp{};
     PairOut po{};
@@ -633,7 +744,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     // per SIMD, 64-column chunks), the fastest on every length mix measured.
     std::vector<int32_t> lens;
     for (int32_t i = 0; i < nc; ++i)
-        if (cp[i].status == QMI_OK) lens.push_back(cp[i].n);
+        if (cp[i].status == QMI_OK && (n_pairs == 0 || mc[i].cap == 0)) lens.push_back(cp[i].n);
     int bucket = 0;
     if (!lens.empty()) {
         std::nth_element(lens.begin(), lens.begin() + lens.size() / 2, lens.end());
@@ -648,7 +759,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     else if (!fp64 && ctx->tuned[bucket] >= 0) variant = ctx->tuned[bucket];
     double group_items = 0.0;
     for (int32_t i = 0; i < nc; ++i)
-        if (cp[i].status == QMI_OK) group_items += 0.5 * cp[i].n * (cp[i].n - 1.0) * (double)F1;
+        if (cp[i].status == QMI_OK && mc[i].cap == 0) group_items += 0.5 * cp[i].n * (cp[i].n - 1.0) * (double)F1;
     const bool tune_now = !fp64 && !fold32 && ctx->tile == 0 && ctx->tuned[bucket] < 0 &&
                           nvar > 1 && !ctx->ws_base && group_items > 2e9;
     ctx->stats.pair_variant = variant;
@@ -665,13 +776,21 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         };
         rec();  // device section start
         HIP_OK(ctx, launch_prologue(st, dcp, nc, max_n, t, y, e, skew_lambda, skew_mu));
-        HIP_OK(ctx, launch_gram<R>(st, dcp, nc, rows, drow, y, K, rp, rd));
-        HIP_OK(ctx, launch_gram_finalize<R>(st, dcp, nc, rd, rp));
-        HIP_OK(ctx, launch_ksum<R>(st, dcp, nc, max_n, K, ks));
+        if (n_modes) HIP_OK(ctx, launch_nodes(st, dcp, nc, max_mode_n, t, y, md));
+        if (n_pairs) {
+            HIP_OK(ctx, launch_gram<R>(st, dcp, nc, rows, drow, y, K, rp, rd));
+            HIP_OK(ctx, launch_gram_finalize<R>(st, dcp, nc, rd, rp));
+            HIP_OK(ctx, launch_ksum<R>(st, dcp, nc, max_n, K, ks));
+        }
         if (bp) HIP_OK(ctx, launch_bands(st, dcp, nc, max_n, t, y, bd));
         if (events) pair_event_idx.push_back(ctx->ev_used);
         rec();
         {
+            PairOut pm1 = po;
+            pm1.part = msplit1 ? dpart : nullptr;
+            if (n_modes)
+                HIP_OK(ctx, launch_modes(st, dcp, dorder, n_modes, fp, md, pm1,
+                                         msplit1 ? mode_groups : 0));
             PairOut pc1 = po;
             pc1.part = split1 ? dpart : nullptr;
             // Per-curve lists whose last tile would hold only one or two slots (the bands
@@ -687,12 +806,13 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
                     rem_slot0 = full * kLanes;
                 }
             }
-            HIP_OK(ctx, launch_pairs<R>(st, dcp, dorder, nc, fpm, t, K, rd, rp, ks, pc1, variant,
-                                        split1 ? max_pieces : 0));
+            const int32_t* porder = dorder + n_modes;
+            HIP_OK(ctx, launch_pairs<R>(st, dcp, porder, n_pairs, fpm, t, K, rd, rp, ks, pc1,
+                                        variant, split1 ? max_pieces : 0));
             if constexpr (sizeof(R) == 4) {
                 if (rem_slot0 >= 0)
-                    HIP_OK(ctx, launch_pairs_rows(st, dcp, dorder, nc, fp, rem_slot0, t, K, rd,
-                                                  pc1));
+                    HIP_OK(ctx, launch_pairs_rows(st, dcp, porder, n_pairs, fp, rem_slot0, t, K,
+                                                  rd, pc1));
             }
         }
         rec();
@@ -707,14 +827,23 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
                 PairOut fo{fine, fine2, nullptr, score_kind, 0, split2 ? dpart : nullptr};
                 if (events) pair_event_idx.push_back(ctx->ev_used);
                 rec();
-                HIP_OK(ctx,
-                       launch_pairs<R>(st, dcp, dorder, nc, ff, t, K, rd, rp, ks, fo, variant,
-                                       split2 ? max_pieces : 0));
+                PairOut fm = fo;
+                fm.part = msplit2 ? dpart : nullptr;
+                if (n_modes)
+                    HIP_OK(ctx, launch_modes(st, dcp, dorder, n_modes, ff, md, fm,
+                                             msplit2 ? mode_groups : 0));
+                HIP_OK(ctx, launch_pairs<R>(st, dcp, dorder + n_modes, n_pairs, ff, t, K, rd, rp,
+                                            ks, fo, variant, split2 ? max_pieces : 0));
                 rec();
             }
             HIP_OK(ctx, launch_best(st, dcp, nc, coarse, coarse2, s->n_coarse, fine, fine2,
                                     refine ? top_k : 0, refine ? n_fine : 0, score_kind, fp.f0,
-                                    fp.df, ctx->masks, pk, dres));
+                                    fp.df, ctx->masks, pk, tie, dres));
+            if (tie.count) {
+                HIP_OK(ctx, launch_mode_ties(st, dcp, nc, ff, md, score_kind, tie));
+                HIP_OK(ctx, launch_best_of_ties(st, nc, fine, fine2, top_k, n_fine, score_kind,
+                                                pk, tie, dres));
+            }
         }
         rec();  // device section end
         return QMI_OK;
@@ -737,7 +866,10 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             u(dres), (uint64_t)(bp != nullptr), dbits(bd.f_lo), dbits(bd.df),
             (uint64_t)bd.n_grid, (uint64_t)bd.n_bands, (uint64_t)bd.n_keep, (uint64_t)bd.n_trials,
             (uint64_t)bd.stride, u(bd.ts), u(bd.ys), u(bd.band_t), u(bd.band_cnt), u(bd.band_id),
-            u(bd.S), u(bd.trials), u(bd.trial_k)};
+            u(bd.S), u(bd.trials), u(bd.trial_k), (uint64_t)n_modes, (uint64_t)max_mode_n,
+            (uint64_t)mode_groups, (uint64_t)max_pieces, (uint64_t)split1, (uint64_t)split2,
+            (uint64_t)msplit1, (uint64_t)msplit2, u(dpart), u(md.curves), u(md.ts), u(md.rows),
+            u(md.frag), u(md.part), u(md.b), u(md.coef), u(tie.count), u(tie.slot), u(tie.score)};
         if (ctx->graph_exec && key == ctx->graph_key) {
             record(ctx);
             HIP_OK(ctx, hipGraphLaunch(ctx->graph_exec, st));
@@ -805,6 +937,8 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         HIP_OK(ctx, hipMemcpyAsync(cpo.data(), dcp, nc * sizeof(CurveParams),
                                    hipMemcpyDeviceToHost, st));
         HIP_OK(ctx, hipStreamSynchronize(st));
+        for (int32_t i = 0; i < nc; ++i)
+            if (cpo[i].status == QMI_OK && cpo[i].sparse) left->push_back(g.c0 + i);
         for (int32_t i = 0; i < nc; ++i) {
             if (cs.ip_y_out) cs.ip_y_out[g.c0 + i] = cpo[i].status ? NAN : cpo[i].ipy;
             if (cs.status_out) cs.status_out[g.c0 + i] = cpo[i].status;
@@ -855,6 +989,10 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         }
         for (int32_t i = 0; i < nc; ++i) {
             qmi_result& rr = cs.out[g.c0 + i];
+            if (rr.status == QMI_OK && rr.reserved) {  // left to the pair sums
+                left->push_back(g.c0 + i);
+                continue;
+            }
             if (cp[i].status != QMI_OK) {
                 // The kernels skipped this curve; make its record explicit.
                 rr.status = cp[i].status;
@@ -878,7 +1016,8 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     if (cs.periodogram) {
         for (int32_t i = 0; i < nc; ++i) {
             const int64_t n = b->offsets[g.c0 + i + 1] - b->offsets[g.c0 + i];
-            if (cp[i].status == QMI_OK)
+            if (cp[i].status == QMI_OK && !(left && std::binary_search(left->begin(), left->end(),
+                                                                       g.c0 + i)))
                 ctx->stats.pair_items += (double)n * (double)(n - 1) / 2.0 * (double)F1;
         }
     }
@@ -887,7 +1026,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         // same bits, so tuning never changes a result) on the largest curves of this group (the
         // first in LPT order) over a slice of the same frequency plan, into a scratch output, and
         // keep the fastest for this length bucket.
-        const int pc = std::min(nc, 48);
+        const int pc = std::min(n_pairs, 48);
         FreqPlan probe = fp;
         probe.count = (int32_t)std::min<int64_t>(F1, 64 * 24);
         // The kernel writes slot s of curve c (a curve id, not its rank in the work order) at
@@ -902,11 +1041,11 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         int best_v = 0;
         for (int v = 0; v < nvar; ++v) {
             HIP_OK(ctx,
-                   launch_pairs<R>(st, dcp, dorder, pc, probe, t, K, rd, rp, ks, pout, v, 0));
+                   launch_pairs<R>(st, dcp, dorder + n_modes, pc, probe, t, K, rd, rp, ks, pout, v, 0));
             HIP_OK(ctx, hipEventRecord(e0, st));
             for (int rep = 0; rep < 2; ++rep)
                 HIP_OK(ctx,
-                       launch_pairs<R>(st, dcp, dorder, pc, probe, t, K, rd, rp, ks, pout, v, 0));
+                       launch_pairs<R>(st, dcp, dorder + n_modes, pc, probe, t, K, rd, rp, ks, pout, v, 0));
             HIP_OK(ctx, hipEventRecord(e1, st));
             HIP_OK(ctx, hipEventSynchronize(e1));
             float ms = 0.f;
@@ -1004,10 +1143,25 @@ int run_call(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs) {
     } scratch_off{ctx};
     ctx->ev_used = 0;
     std::vector<int32_t> pair_ev;
+    std::vector<int32_t> left;
     for (const Group& g : groups) {
-        rc = (cs.kp->precision == QMI_PREC_FP64) ? run_group<double>(ctx, b, cs, g, pair_ev)
-                                                 : run_group<float>(ctx, b, cs, g, pair_ev);
+        left.clear();
+        rc = (cs.kp->precision == QMI_PREC_FP64)
+                 ? run_group<double>(ctx, b, cs, g, pair_ev, true, &left)
+                 : run_group<float>(ctx, b, cs, g, pair_ev, false, &left);
         if (rc) return rc;
+        // Curves that the mode sums left (known only once their widths are): runs of neighbours
+        // by the pair sums, within the memory that the group was planned for.
+        for (size_t i = 0; i < left.size();) {
+            size_t j = i + 1;
+            while (j < left.size() && left[j] == left[j - 1] + 1) ++j;
+            const Group sub{left[i], left[j - 1] + 1, b->offsets[left[i]],
+                            b->offsets[left[j - 1] + 1]};
+            ctx->ws_used = 0;
+            rc = run_group<float>(ctx, b, cs, sub, pair_ev, true, nullptr);
+            if (rc) return rc;
+            i = j;
+        }
     }
     // Timing from the events (all complete: every group synchronised).
     float ms = 0.f;

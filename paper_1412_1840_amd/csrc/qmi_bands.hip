@@ -422,7 +422,7 @@ bands_best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__
     r.coarse_best = NAN;
     r.n = P.n;
     r.status = P.status;
-    r.reserved = 0;
+    r.reserved = P.sparse;  // nonzero: the host searches the curve again by the pair sums
     r.n_peaks = sfound[0];
     const int s = ss[0];
     if (P.status != 0 || s == 0x7fffffff) {

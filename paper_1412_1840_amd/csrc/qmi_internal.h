@@ -54,7 +54,58 @@ struct CurveParams {
     double bk;     // diagonal value of the stored K table (B rounded to the kernel type)
     double sjc;    // sum_{i<j} K(i,j)            (FP64, from the stored K table)
     int64_t pqoff; // first piece of this curve in a one-piece-per-workgroup launch's partial sums
+    int32_t sparse; // set by nodes_kernel: magnitudes too scattered for the mode sums
+    int32_t pad;
 };
+
+// Mode sums (qmi_modes.hip).  Samples are taken in magnitude order in blocks of 32 that reach the
+// same two blocks of 16 nodes; a block and each of its node blocks make a 16 x 32 operand of the
+// matrix unit, in two half-precision parts.
+// Harmonics are kept until the rest of the series is below this share of the kernel's value where
+// phases coincide (1): a third of half a unit in the last place of single precision.
+constexpr double kModeTail = 1e-8;
+constexpr int kModeGroup = 7;      // harmonics per pass over the samples
+constexpr int kModeCapMax = 256;     // most harmonics (sigma_t from 0.03)
+// Blocks that a curve may use before the pair sums are faster; the host gives a curve to the mode
+// sums when its whole blocks and two more fit, and nodes_kernel gives it back when its samples are
+// so scattered over node blocks that they need more than these.  Measured per curve and frequency
+// (4096 frequencies, batches): the pair sums take 9.2e-5 n^2 + 0.008 n + 0.25 ns, the mode sums
+// 0.1 ns per block and group of harmonics, so they meet at n = 40, 72, 290 and 520 for sigma_t =
+// 0.6, 0.3, 0.1 and 0.05 (2, 3, 9 and 17 groups).  n / 5 bounds the tables by the size of the pair
+// sums' table of kernel values.
+inline int mode_room(int n, int groups) {
+    const int room = (int)((9.2e-4 * n * n + 0.08 * n + 2.5) / groups);
+    return room < n / 5 ? room : n / 5;
+}
+constexpr int kModeMaxBlocks = QMI_MAX_N / 5;
+// Coefficients stored per curve (whole groups).
+__host__ __device__ constexpr int mode_stride(int cap) {
+    return (cap + kModeGroup - 1) / kModeGroup * kModeGroup;
+}
+
+struct ModeCurve {
+    int64_t boff;   // first of its cap blocks
+    int32_t cap;    // blocks there is room for; 0: the curve is left to the pair sums
+    int32_t blocks; // blocks in use
+    int32_t groups; // passes over the samples; 0: left to the pair sums
+    int32_t pad;
+    double c0;      // coefficient of the constant term
+    double sj0;     // w sum_q b_q^2
+    double n0;      // p sum_q b_q
+};
+
+struct ModeDev {
+    ModeCurve* curves; // [curve]
+    double* ts;        // [block][32] times in magnitude order
+    int32_t* rows;     // [block] first node block, counted among the curve's
+    void* frag;        // [block][node block][hi, lo][64 lanes] 8 half-precision values
+    double* part;      // [block][node block][16] sums of U over the block's samples
+    double* b;         // [node block (from 2 boff)][16] sums of U over all samples
+    double* coef;      // [curve][mode_stride(mode_cap)]
+    int32_t mode_cap;  // coefficients there is room for (past the harmonics kept)
+    int32_t max_groups; // most groups of harmonics of any curve
+};
+size_t nodes_lds(int max_n, int mode_cap);
 
 // Interleaved partial sums of a column's terms over a wave's rows (row m goes to partial
 // m mod kPartials), combined at the end of the column: the pair kernel and the column-sum tables
@@ -104,6 +155,16 @@ struct PeakOut {
     int32_t* npk;      // [curve]
     double* win;       // [curve][top_k][2]
     int32_t* argmax;   // [curve]
+};
+
+// Refined points of a curve too close to the best for the mode sums' errors to tell them apart
+// (best_kernel), scored again in FP64 (mode_ties_kernel).
+constexpr int kTieMax = 32;
+struct TieDev {
+    int32_t* count;  // [curve] listed points, 0 where one is clearly the best; nullptr: no lists
+    int32_t* slot;   // [curve][kTieMax] their slots
+    double* score;   // [curve][kTieMax] their FP64 scores
+    const ModeCurve* curves;
 };
 
 // Spurious-period masks (Sec. 6.1), passed to the selection kernels by value.  A candidate (f, s)
@@ -208,12 +269,29 @@ constexpr int kRemSlots = kLanes / 32;
 hipError_t launch_pairs_rows(hipStream_t st, const CurveParams* cp, const int32_t* order,
                              int n_work_curves, const FreqPlan& fp, int slot0, const double* t,
                              const float* K, const double* rd, const PairOut& out);
+// Mode sums: launch_nodes prepares the curves (after the prologue), launch_modes runs a frequency
+// plan.  split_groups > 0 (with out.part, [rank][split_groups][count][3]): one harmonic group per
+// wave, then the epilogue kernel; 0: every group in one wave.  Both give the same bits.
+hipError_t launch_nodes(hipStream_t st, CurveParams* cp, int n_curves, int max_n, const double* t,
+                        const double* y, const ModeDev& md);
+hipError_t launch_modes(hipStream_t st, const CurveParams* cp, const int32_t* order,
+                        int n_work_curves, const FreqPlan& fp, const ModeDev& md,
+                        const PairOut& out, int split_groups);
 hipError_t launch_peaks(hipStream_t st, const CurveParams* cp, int n_curves, const double* coarse,
                         int n_coarse, double f0, double df, int top_k, int n_fine,
                         const MaskDev& md, const PeakOut& po);
 hipError_t launch_best(hipStream_t st, const CurveParams* cp, int n_curves, const double* coarse,
                        const double* coarse2, int n_coarse, const double* fine,
                        const double* fine2, int top_k, int n_fine, int score_kind, double f0,
-                       double df, const MaskDev& md, const PeakOut& po, DevResult* res);
+                       double df, const MaskDev& md, const PeakOut& po, const TieDev& tie,
+                       DevResult* res);
+// After launch_best with lists: their points scored in FP64, and the records of their curves
+// rewritten with the best by these scores.
+hipError_t launch_mode_ties(hipStream_t st, const CurveParams* cp, int n_curves,
+                            const FreqPlan& fp, const ModeDev& md, int score_kind,
+                            const TieDev& tie);
+hipError_t launch_best_of_ties(hipStream_t st, int n_curves, const double* fine,
+                               const double* fine2, int top_k, int n_fine, int score_kind,
+                               const PeakOut& po, const TieDev& tie, DevResult* res);
 
 }  // namespace qmi

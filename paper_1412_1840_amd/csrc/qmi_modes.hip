@@ -1,0 +1,850 @@
+// HIP kernels for gfx950 (MI355X): the pair x frequency sums of Protopapas et al.,
+// arXiv:1412.1840, as sums over harmonics and magnitude nodes (the mixed-precision path).
+//
+// Both kernels of the method (Sec. 2, Sec. 2.1) are sums of products of one-sample factors:
+//   periodic:  exp(-2 sin^2(x/2) / st^2) = sum_m c_m cos(m x),  c_0 = e^-k I_0(k),
+//              c_m = 2 e^-k I_m(k), k = 1 / st^2 (the Jacobi-Anger series; I_m decays faster than
+//              exponentially past m ~ k^(1/2)),
+//   Gaussian:  exp(-(y - y')^2 / (2 sy^2)) = w sum_q U_q(y) U_q(y'),  U_q(y) = exp(-((y - x_q)/sy)^2),
+//              the trapezoid rule of the Gaussian product integral on nodes x_q of spacing h sy,
+//              w = h sqrt(2/pi); its error is 2 exp(-pi^2 / (2 h^2)), and U_q is negligible a few
+//              sy away from its node.  Also p sum_q U_q(y) = 1, p = h / sqrt(pi).
+// With a_qm(f) = sum_i U_q(y_i) exp(2 pi i m f t_i) and b_q = a_q0 the sums over all ordered pairs
+// are
+//   sum K_y K_t / (A B) = w sum_m c_m sum_q |a_qm|^2
+//   sum K_t / A         =   sum_m c_m |p sum_q a_qm|^2
+//   sum_i r_i sum_j K_t / (A B) = sum_m c_m Re( conj(p sum_q a_qm) w sum_q b_q a_qm )
+// so that a frequency costs N x (harmonics) x (nodes near a sample) instead of N^2 / 2 pairs, and
+// the a_qm are a matrix product (nodes x samples) by (samples x frequencies and harmonics).  All
+// three sums come from the same a_qm, so that their rounding errors cancel to first order in the
+// QMI wherever time and magnitude are independent, and exactly where all phases coincide.
+#include <math.h>
+
+#include <algorithm>
+
+#include "qmi_internal.h"
+
+namespace qmi {
+
+namespace {
+
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef _Float16 half8v __attribute__((ext_vector_type(8)));
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef double double2v __attribute__((ext_vector_type(2)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+// Node spacing in units of sigma_y: the trapezoid error 2 exp(-pi^2 / (2 h^2)) is 5e-9 of a kernel
+// value and alternates in sign along the magnitudes, so that it averages out over the pairs.
+constexpr double kNodeStep = 0.5;
+constexpr double kNodeW = kNodeStep * 0.79788456080286535587989211986876;  // h sqrt(2/pi)
+constexpr double kNodeP = kNodeStep * 0.56418958354775628694807945156077;  // h / sqrt(pi)
+// A sample uses the 16-node blocks rb and rb + 1, rb chosen so that they hold at least the
+// 2 kReach + 1 nodes nearest to it (beyond, U < exp(-(8.5 h)^2) = 1.5e-8).
+constexpr int kReach = 8;
+// v_sin_f32 and v_cos_f32 round towards zero: measured over the whole circle, sin^2 + cos^2 is
+// 6.5e-8 below 1 on average.  A harmonic formed by k products from them has its |a|^2 short by
+// (k + 1) times that, which the coefficients make up for.
+constexpr double kTrigLoss = 6.5e-8;
+
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// --------------------------------------------------------------------------------------------
+// Preparation: sorted samples, node blocks, matrix fragments, node sums, coefficients.
+// --------------------------------------------------------------------------------------------
+
+constexpr int kNodesBlock = 256;
+
+__device__ double nodes_sum(double v, double* sh) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double s = 0.0;
+    for (int k = 0; k < kNodesBlock / 64; ++k) s += sh[k];
+    __syncthreads();
+    return s;
+}
+
+// Exclusive prefix sum of one value per thread; *total receives the sum.
+__device__ int nodes_scan(int v, int* sh, int* total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int s = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(s, o, 64);
+        if (lane >= o) s += u;
+    }
+    __syncthreads();
+    if (lane == 63) sh[w] = s;
+    __syncthreads();
+    int base = 0, all = 0;
+    for (int k = 0; k < kNodesBlock / 64; ++k) {
+        if (k < w) base += sh[k];
+        all += sh[k];
+    }
+    __syncthreads();
+    *total = all;
+    return base + s - v;
+}
+
+// One block per curve.  Dynamic LDS: pow2(max_n) x 12 bytes (keys, indices), at least the
+// coefficient tables.
+__global__ void __launch_bounds__(kNodesBlock)
+nodes_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
+             const double* __restrict__ y_all, ModeDev md) {
+    extern __shared__ double nsh[];
+    __shared__ double red[kNodesBlock / 64];
+    __shared__ int ired[kNodesBlock / 64];
+    __shared__ int g_first[kModeMaxBlocks + 1];  // first sample of each group
+    __shared__ int g_block[kModeMaxBlocks + 1];  // its first block of samples
+    __shared__ int g_row[kModeMaxBlocks];        // its first node block, counted among those in use
+    __shared__ int g_rb[kModeMaxBlocks];         // and by magnitude
+    const int c = blockIdx.x;
+    const CurveParams P = cp[c];
+    ModeCurve M = md.curves[c];
+    if (P.status != 0 || M.cap == 0) return;
+    const int n = P.n;
+    int m2 = 1;
+    while (m2 < n) m2 <<= 1;
+    double* key = nsh;
+    int32_t* idx = reinterpret_cast<int32_t*>(nsh + m2);
+    const double* t = t_all + P.off;
+    const double* y = y_all + P.off;
+    for (int i = threadIdx.x; i < m2; i += kNodesBlock) {
+        key[i] = i < n ? y[i] : INFINITY;
+        idx[i] = i < n ? i : 0x7fffffff;
+    }
+    __syncthreads();
+    for (int k = 2; k <= m2; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int i = threadIdx.x; i < m2; i += kNodesBlock) {
+                const int l = i ^ j;
+                if (l > i) {
+                    const double a = key[i], b = key[l];
+                    const int32_t ia = idx[i], ib = idx[l];
+                    const bool gt = (a > b) || (a == b && ia > ib);
+                    if (gt == ((i & k) == 0)) {
+                        key[i] = b;
+                        key[l] = a;
+                        idx[i] = ib;
+                        idx[l] = ia;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    }
+    const double y0 = key[0];
+    const double inv = 1.0 / (kNodeStep * P.sigma_y);
+    bool sparse = !((key[n - 1] - y0) * inv < 1e9);  // far more nodes than samples can use
+    // Position of a sample in node units, and its first node block.
+    auto pos = [&](int i) { return (key[i] - y0) * inv + (double)kReach; };
+    auto blk = [&](int i) { return ((int)rint(pos(i)) - kReach) >> 4; };
+    // Groups of samples with the same first node block, and the node blocks in use: a group brings
+    // two new ones, or one where the group before it starts one block lower.
+    int n_groups = 0, n_rows = 0, n_blocks = 0;
+    if (!sparse) {
+        const int per = (n + kNodesBlock - 1) / kNodesBlock;
+        const int i0 = min(n, (int)threadIdx.x * per), i1 = min(n, i0 + per);
+        int s = 0, all = 0;  // groups in the low, node blocks in the high half
+        for (int i = i0; i < i1; ++i) {
+            const int d = i == 0 ? 2 : min(2, blk(i) - blk(i - 1));
+            if (d > 0) s += 1 + (d << 16);
+        }
+        int e = nodes_scan(s, ired, &all);
+        n_groups = all & 0xffff;
+        n_rows = all >> 16;
+        sparse = n_groups > M.cap;
+        if (!sparse) {
+            for (int i = i0; i < i1; ++i) {
+                const int b = blk(i);
+                const int d = i == 0 ? 2 : min(2, b - blk(i - 1));
+                if (d <= 0) continue;
+                const int g = e & 0xffff;
+                e += 1 + (d << 16);
+                g_first[g] = i;
+                g_rb[g] = b;
+                g_row[g] = (e >> 16) - 2;
+            }
+            if (threadIdx.x == 0) g_first[n_groups] = n;
+            __syncthreads();
+            // Blocks of 32 samples: every group starts a new one.
+            const int gper = (n_groups + kNodesBlock - 1) / kNodesBlock;
+            const int a0 = min(n_groups, (int)threadIdx.x * gper), a1 = min(n_groups, a0 + gper);
+            int nb = 0;
+            for (int g = a0; g < a1; ++g) nb += (g_first[g + 1] - g_first[g] + 31) >> 5;
+            int f = nodes_scan(nb, ired, &n_blocks);
+            for (int g = a0; g < a1; ++g) {
+                g_block[g] = f;
+                f += (g_first[g + 1] - g_first[g] + 31) >> 5;
+            }
+            if (threadIdx.x == 0) g_block[n_groups] = n_blocks;
+            sparse = n_blocks > M.cap;
+        }
+        __syncthreads();
+    }
+    if (sparse) {
+        if (threadIdx.x == 0) {
+            md.curves[c].groups = 0;
+            cp[c].sparse = 1;
+        }
+        return;
+    }
+    auto group_of = [&](int block) {
+        int lo = 0, hi = n_groups - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (g_block[mid] <= block) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
+    // Times in magnitude order, every group padded to whole blocks.
+    double* ts = md.ts + 32 * M.boff;
+    int32_t* rows = md.rows + M.boff;
+    for (int q = threadIdx.x; q < 32 * n_blocks; q += kNodesBlock) {
+        const int g = group_of(q >> 5);
+        const int i = g_first[g] + q - 32 * g_block[g];
+        ts[q] = i < g_first[g + 1] ? t[idx[i]] : 0.0;
+        if ((q & 31) == 0) rows[q >> 5] = g_row[g];
+    }
+    // Fragments of U in the operand layout of the 16x16x32 matrix instruction: lane l holds node
+    // l mod 16 and samples 8 (l / 16) ... + 7 of the block, as a high and a low half-precision
+    // part; and each node's sum over the block's samples.
+    half8v* frag = reinterpret_cast<half8v*>(md.frag) + M.boff * 256;
+    double* part = md.part + M.boff * 32;
+    double* bsum = md.b + M.boff * 32;
+    const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
+    for (int r = wave; r < 2 * n_blocks; r += kNodesBlock / 64) {
+        const int blk_r = r >> 1, g = group_of(blk_r);
+        const double node = (double)(16 * (g_rb[g] + (r & 1)) + (lane & 15));
+        const int s0 = g_first[g] + 32 * (blk_r - g_block[g]) + 8 * (lane >> 4);
+        const int s_end = g_first[g + 1];
+        half8v h, l;
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            double v = 0.0;
+            if (s0 + j < s_end) {
+                const double d = (node - pos(s0 + j)) * kNodeStep;
+                v = exp(-d * d);
+            }
+            s += v;
+            h[j] = (_Float16)(float)v;
+            l[j] = (_Float16)(float)(v - (double)(float)h[j]);
+        }
+        frag[(int64_t)r * 128 + lane] = h;
+        frag[(int64_t)r * 128 + 64 + lane] = l;
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (lane < 16) part[(int64_t)r * 16 + lane] = s;
+    }
+    __syncthreads();
+    double sq = 0.0, sb = 0.0;
+    for (int q = threadIdx.x; q < 16 * n_rows; q += kNodesBlock) {
+        const int row = q >> 4;
+        double b = 0.0;
+        for (int g = 0; g < n_groups; ++g) {
+            const int k = row - g_row[g];
+            if (k < 0) break;
+            if (k > 1) continue;
+            for (int r = g_block[g]; r < g_block[g + 1]; ++r)
+                b += part[(int64_t)(2 * r + k) * 16 + (q & 15)];
+        }
+        bsum[q] = b;
+        sq = fma(b, b, sq);
+        sb += b;
+    }
+    sq = nodes_sum(sq, red);
+    sb = nodes_sum(sb, red);
+    // Coefficients of the periodic kernel's cosine series by the trapezoid rule over the circle
+    // (exact up to the coefficients past L - m), and the number of harmonics to keep.
+    const int cap = md.mode_cap, L = 3 * cap + 32;
+    double* ev = nsh;
+    double* ct = nsh + L;
+    const double kap = 1.0 / (P.sigma_t * P.sigma_t);
+    for (int j = threadIdx.x; j < L; j += kNodesBlock) {
+        const double co = cospi(2.0 * (double)j / (double)L);
+        ct[j] = co;
+        ev[j] = exp(kap * (co - 1.0));
+    }
+    __syncthreads();
+    double* coef = md.coef + (int64_t)c * mode_stride(cap);
+    double* cs = ct + L;  // [cap + 1]
+    for (int m = threadIdx.x; m <= cap; m += kNodesBlock) {
+        double s = 0.0;
+        int k = 0;
+        for (int j = 0; j < L; ++j) {
+            s = fma(ev[j], ct[k], s);
+            k += m;
+            if (k >= L) k -= L;
+        }
+        cs[m] = (m ? 2.0 : 1.0) * s / (double)L;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int m = cap;
+        double tail = 0.0;
+        for (; m > 1; --m) {
+            tail += cs[m];
+            if (tail > kModeTail) break;
+        }
+        m = min(m, md.max_groups * kModeGroup);
+        ired[0] = m;
+        M.groups = (m + kModeGroup - 1) / kModeGroup;
+        M.blocks = n_blocks;
+        M.c0 = cs[0];
+        M.sj0 = kNodeW * sq;
+        M.n0 = kNodeP * sb;
+        md.curves[c] = M;
+        const double N = (double)n;
+        cp[c].ipy = P.B * M.sj0 / (N * N);
+    }
+    __syncthreads();
+    // Coefficient of harmonic m at m - 1; zero past the last one kept.
+    const int keep = ired[0];
+    for (int m = threadIdx.x + 1; m <= mode_stride(cap); m += kNodesBlock)
+        coef[m - 1] = m <= keep ? cs[m] : 0.0;
+}
+
+// --------------------------------------------------------------------------------------------
+// Mode sums
+// --------------------------------------------------------------------------------------------
+
+__device__ __forceinline__ double mode_slot_freq(const FreqPlan& fp, int c, int s, bool& active) {
+    active = s < fp.count;
+    if (!active) return 0.0;
+    if (fp.kind == 0) return __dadd_rn(fp.f0, __dmul_rn((double)s, fp.df));
+    if (fp.kind == 1) return fp.list[s];
+    if (fp.kind == 3) {
+        const double v = fp.list[(int64_t)c * fp.stride + s];
+        active = v == v;
+        return active ? v : 0.0;
+    }
+    const int p = s / fp.n_fine, m = s - p * fp.n_fine;
+    if (p >= fp.npk[c]) {
+        active = false;
+        return 0.0;
+    }
+    const double* w = fp.win + ((int64_t)c * fp.top_k + p) * 2;
+    return __dadd_rn(w[0], __dmul_rn((double)m, w[1]));
+}
+
+__device__ __forceinline__ void mode_nan(int64_t o, const PairOut& out) {
+    out.score[o] = NAN;
+    if (out.score2) out.score2[o] = NAN;
+    if (out.ips) out.ips[o * 3 + 0] = out.ips[o * 3 + 1] = out.ips[o * 3 + 2] = NAN;
+}
+
+// V_J, IP_t, V_C and the scores from the three sums over ordered pairs without their constants.
+__device__ __forceinline__ void mode_scores(const CurveParams& P, double SJ, double ST, double SC,
+                                            int64_t o, const PairOut& out) {
+    const double N = (double)P.n;
+    const double VJ = P.A * P.B * SJ / (N * N);
+    const double IPt = P.A * ST / (N * N);
+    const double VC = P.A * P.B * SC / (N * N * N);
+    const double VM = P.ipy * IPt;
+    const double q = log(VJ) + log(VM) - 2.0 * log(VC);
+    const double nckp = sqrt(N * P.sigma_t) / P.ipy * (VJ - VM);
+    out.score[o] = out.score_kind == 0 ? q : nckp;
+    if (out.score2) out.score2[o] = out.score_kind == 0 ? nckp : q;
+    if (out.ips) {
+        out.ips[o * 3 + 0] = VJ;
+        out.ips[o * 3 + 1] = IPt;
+        out.ips[o * 3 + 2] = VC;
+    }
+}
+
+__device__ __forceinline__ void lds_add(double* p, double v) {
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+
+// Eight single-precision values as a high and a low half-precision part (each rounded to nearest:
+// together at least 22 bits).  minus_one is -1 in a scalar register whose value the compiler does
+// not know, so that value minus high part is one v_fma_mix_f32 (v_fma_mixlo/hi_f16, which would
+// also convert it, issue at half rate).
+__device__ __forceinline__ void split8(const float (&v)[8], float minus_one, half8v& h,
+                                       half8v& l) {
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+        const float2v x = {v[j], v[j + 1]};
+        const half2v a = __builtin_convertvector(x, half2v);
+        const float2v r = {fmaf((float)a.x, minus_one, v[j]),
+                           fmaf((float)a.y, minus_one, v[j + 1])};
+        const half2v b = __builtin_convertvector(r, half2v);
+        h[j] = a.x;
+        h[j + 1] = a.y;
+        l[j] = b.x;
+        l[j + 1] = b.y;
+    }
+}
+
+// A copy that the compiler does not see through (an identity lane permutation), so that the
+// accumulator that takes another one's sums over keeps its own registers in the loop.
+__device__ __forceinline__ float4v copy4(float4v x) {
+    float4v y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        y[r] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x[r]), 0xe4, 0xf, 0xf, true));
+    return y;
+}
+
+__device__ __forceinline__ float4v mfma(half8v a, half8v b, float4v c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+
+// One wave = (curve, 16 frequency slots): lane l works for slot l mod 16 and, in every block of 32
+// samples (in magnitude order), for the samples 8 (l / 16) ... + 7.  Per block it forms
+// exp(2 pi i m f t) of its eight samples for the kModeGroup harmonics of a group, splits them into
+// two half-precision parts and feeds them as the B operand to the matrix unit: hi*hi + hi*lo +
+// lo*hi with the U fragments of the block's two 16-node blocks as A, accumulated in FP32 over the
+// few blocks that a node meets.  Because samples are sorted, a node block that no later sample
+// reaches is folded into the FP64 sums (sum_q a^2, sum_q a, sum_q b a, per lane in LDS) and its
+// registers are taken over by the next.
+// The harmonic groups of a slot are summed in order; with SPLIT a wave runs one group and stores
+// its sums for mode_epilogue_kernel, which adds them in the same order.
+//
+// Why this shape: N^2 / 2 pairs become N x 21 harmonics x 32 nodes (sigma_t 0.3) on the matrix
+// unit.  Seven harmonics are what 256 registers of two waves per SIMD hold (112 accumulators); the
+// 16 x 16 x 32 instruction takes a lane's own eight samples as its B operand, so that the
+// harmonics go from the recurrence to the matrix unit without LDS.  Bound: per block and group a
+// wave issues 84 MFMAs (17 cycles each) and about 460 other VALU instructions (two thirds of them
+// conversions, FP64 and sines at 5 to 9 cycles), and the two overlap only in part (a conversion
+// issued between MFMAs costs 2.7 of its 4.8 cycles): 3100 cycles of a SIMD.  Measured, 768 survey
+// curves (N 300..1000), 20 000 + 10 x 1000 frequencies: 125 ms against 1033 ms by the pair sums,
+// 8.2 times; one curve of 8192 samples at 1000 frequencies 1.7 against 7.6 ms.  Errors against
+// FP64 are below the pair sums' (QMI 3e-9 against 5e-8 rms at N = 617), but for V_J, IP_t and V_C
+// where most phases coincide and N > 2000 (5e-8 against 1e-8: FP32 accumulation over more blocks).
+constexpr int kModeWaves = 4;
+constexpr int kModeThreads = 64 * kModeWaves;
+constexpr int kMS = 5;  // FP64 sums per harmonic and lane
+
+template <bool SPLIT>
+__global__ void __launch_bounds__(kModeThreads, 2)
+modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ order, FreqPlan fp,
+             ModeDev md, int n_work, int xcd_grouped, int gmax, PairOut out) {
+    __shared__ double S_all[kModeWaves][kModeGroup * kMS][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = uni((int)(threadIdx.x >> 6));
+    const int tiles = (fp.count + kLanes - 1) / kLanes;
+    int rank, tile, g0 = 0;
+    unsigned blk = blockIdx.x;
+    if (SPLIT) {
+        rank = (int)(blk / (unsigned)(gmax * tiles));
+        const int rem = (int)(blk - (unsigned)rank * (gmax * tiles));
+        g0 = rem / tiles;
+        tile = rem - g0 * tiles;
+    } else if (xcd_grouped) {
+        const int xcd = (int)(blk % kXcds);
+        const int seq = (int)(blk / kXcds);
+        rank = (seq / tiles) * kXcds + xcd;
+        tile = seq - (seq / tiles) * tiles;
+    } else {
+        rank = (int)(blk / tiles);
+        tile = (int)(blk - (unsigned)rank * tiles);
+    }
+    if (rank >= n_work) return;
+    const int c = order[rank];
+    const CurveParams P = cp[c];
+    const int n16 = lane & 15, kg = lane >> 4;
+    const int slot = tile * kLanes + wave * 16 + n16;
+    if (tile * kLanes + wave * 16 >= fp.count) return;
+    bool active;
+    const double f = mode_slot_freq(fp, c, slot, active);
+    const int64_t obase = (int64_t)c * fp.count + slot;
+    if (P.status != 0) {
+        if (active && kg == 0 && g0 == 0 && !SPLIT) mode_nan(obase, out);
+        return;
+    }
+    const ModeCurve M = md.curves[c];
+    const int g_end = SPLIT ? min(g0 + 1, M.groups) : M.groups;
+    if (g0 >= g_end) return;  // no such group, or a curve left to the pair sums
+    const double* ts = md.ts + 32 * M.boff + 8 * kg;
+    const half8v* frag = reinterpret_cast<const half8v*>(md.frag) + M.boff * 256 + lane;
+    const double* bq = md.b + M.boff * 32 + 4 * kg;
+    const int32_t* rows = md.rows + M.boff;
+    const double* coef = md.coef + (int64_t)c * mode_stride(md.mode_cap);
+    double (*S)[64] = S_all[wave];
+    const double loss = f != 0.0 ? kTrigLoss : 0.0;  // at f = 0 every value is exactly 1
+    float minus_one = -1.0f;
+    asm volatile("" : "+s"(minus_one));
+
+    double SJ = M.c0 * M.sj0, ST = M.c0 * M.n0 * M.n0, SC = M.c0 * M.n0 * M.sj0;
+    if (SPLIT) SJ = ST = SC = 0.0;
+    for (int g = g0; g < g_end; ++g) {
+        const int m0 = g * kModeGroup + 1;
+        float4v acc[2][kModeGroup][2];
+        const float4v zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int m = 0; m < kModeGroup; ++m) {
+            acc[0][m][0] = acc[0][m][1] = acc[1][m][0] = acc[1][m][1] = zero;
+#pragma unroll
+            for (int q = 0; q < kMS; ++q) S[m * kMS + q][lane] = 0.0;
+        }
+        int wb = 0;  // node block held by acc[0]
+        // Folds harmonic m of the node block whose sums are (ac, as) and node sums b.
+        auto fold = [&](int m, const float4v& ac, const float4v& as, const double (&b)[4]) {
+            double sq = 0.0, ca = 0.0, sa = 0.0, cb = 0.0, sb = 0.0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double x = (double)ac[r], z = (double)as[r];
+                sq = fma(x, x, sq);
+                sq = fma(z, z, sq);
+                ca += x;
+                sa += z;
+                cb = fma(b[r], x, cb);
+                sb = fma(b[r], z, sb);
+            }
+            lds_add(&S[m * kMS + 0][lane], sq);
+            lds_add(&S[m * kMS + 1][lane], ca);
+            lds_add(&S[m * kMS + 2][lane], sa);
+            lds_add(&S[m * kMS + 3][lane], cb);
+            lds_add(&S[m * kMS + 4][lane], sb);
+        };
+        auto load_b = [&](int row, double (&b)[4]) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) b[r] = bq[(int64_t)row * 16 + r];
+        };
+        for (int kb = 0; kb < M.blocks; ++kb) {
+            const int row = uni(rows[kb]);
+            while (wb < row) {  // at most two steps
+                double b[4];
+                load_b(wb, b);
+#pragma unroll
+                for (int m = 0; m < kModeGroup; ++m) {
+                    fold(m, acc[0][m][0], acc[0][m][1], b);
+                    acc[0][m][0] = copy4(acc[1][m][0]);
+                    acc[0][m][1] = copy4(acc[1][m][1]);
+                    acc[1][m][0] = acc[1][m][1] = zero;
+                }
+                ++wb;
+            }
+            const half8v* fk = frag + (int64_t)kb * 256;
+            const half8v a0h = fk[0], a0l = fk[64], a1h = fk[128], a1l = fk[192];
+            const double2v* tp = reinterpret_cast<const double2v*>(ts + 32 * kb);
+            double tv[8];
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) {
+                const double2v v = tp[j / 2];
+                tv[j] = v.x;
+                tv[j + 1] = v.y;
+            }
+            // z_m = exp(2 pi i m f t): z_m0 from its own phase, z_m0+1 = z_m0 z_1, and on from
+            // there by z_m+1 = 2 cos(2 pi f t) z_m - z_m-1, one multiply-add per value.
+            float c1[8], s1[8], C[8], Sn[8], Cp[8], Sp[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                tv[j] = fma(f, tv[j], -rint(f * tv[j]));  // the phase, in turns
+                const float q = (float)tv[j];
+                c1[j] = __builtin_amdgcn_cosf(q);
+                s1[j] = __builtin_amdgcn_sinf(q);
+            }
+            if (g > 0) {
+                const double md0 = (double)m0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float q = (float)fma(md0, tv[j], -rint(md0 * tv[j]));
+                    C[j] = __builtin_amdgcn_cosf(q);
+                    Sn[j] = __builtin_amdgcn_sinf(q);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    C[j] = c1[j];
+                    Sn[j] = s1[j];
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < kModeGroup; ++m) {
+                half8v h, l;
+                split8(C, minus_one, h, l);
+                acc[0][m][0] = mfma(a0h, h, acc[0][m][0]);
+                acc[1][m][0] = mfma(a1h, h, acc[1][m][0]);
+                acc[0][m][0] = mfma(a0h, l, acc[0][m][0]);
+                acc[1][m][0] = mfma(a1h, l, acc[1][m][0]);
+                acc[0][m][0] = mfma(a0l, h, acc[0][m][0]);
+                acc[1][m][0] = mfma(a1l, h, acc[1][m][0]);
+                split8(Sn, minus_one, h, l);
+                acc[0][m][1] = mfma(a0h, h, acc[0][m][1]);
+                acc[1][m][1] = mfma(a1h, h, acc[1][m][1]);
+                acc[0][m][1] = mfma(a0h, l, acc[0][m][1]);
+                acc[1][m][1] = mfma(a1h, l, acc[1][m][1]);
+                acc[0][m][1] = mfma(a0l, h, acc[0][m][1]);
+                acc[1][m][1] = mfma(a1l, h, acc[1][m][1]);
+                if (m == 0) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        Cp[j] = C[j];
+                        Sp[j] = Sn[j];
+                        C[j] = fmaf(Cp[j], c1[j], -(Sp[j] * s1[j]));
+                        Sn[j] = fmaf(Cp[j], s1[j], Sp[j] * c1[j]);
+                        c1[j] += c1[j];
+                    }
+                } else if (m + 1 < kModeGroup) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const float x = fmaf(c1[j], C[j], -Cp[j]);
+                        const float y = fmaf(c1[j], Sn[j], -Sp[j]);
+                        Cp[j] = C[j];
+                        Sp[j] = Sn[j];
+                        C[j] = x;
+                        Sn[j] = y;
+                    }
+                }
+            }
+        }
+        {
+            double b0[4], b1[4];
+            load_b(wb, b0);
+            load_b(wb + 1, b1);
+#pragma unroll
+            for (int m = 0; m < kModeGroup; ++m) {
+                fold(m, acc[0][m][0], acc[0][m][1], b0);
+                fold(m, acc[1][m][0], acc[1][m][1], b1);
+            }
+        }
+        // The four lanes of a slot hold a quarter of its nodes each: lane group kg adds them for
+        // the harmonics kg, kg + 4, ... and forms their terms.
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        double gj = 0.0, gt = 0.0, gc = 0.0;
+        for (int m = kg; m < kModeGroup; m += 4) {
+            double v[kMS];
+#pragma unroll
+            for (int q = 0; q < kMS; ++q) {
+                v[q] = 0.0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[q] += S[m * kMS + q][n16 + 16 * k];
+            }
+            const double cm = coef[m0 - 1 + m] * (1.0 + loss * (double)(m + 1));
+            const double ca = kNodeP * v[1], sa = kNodeP * v[2];
+            gj = fma(cm, kNodeW * v[0], gj);
+            gt = fma(cm, ca * ca + sa * sa, gt);
+            gc = fma(cm, kNodeW * (ca * v[3] + sa * v[4]), gc);
+        }
+        for (int o = 16; o < 64; o <<= 1) {
+            gj += __shfl_xor(gj, o, 64);
+            gt += __shfl_xor(gt, o, 64);
+            gc += __shfl_xor(gc, o, 64);
+        }
+        SJ += gj;
+        ST += gt;
+        SC += gc;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (kg != 0 || !active) return;
+    if (SPLIT) {
+        double* pp = out.part + (((int64_t)rank * gmax + g0) * fp.count + slot) * 3;
+        pp[0] = SJ;
+        pp[1] = ST;
+        pp[2] = SC;
+        return;
+    }
+    mode_scores(P, SJ, ST, SC, obase, out);
+}
+
+constexpr int kModeEpiBlock = 256;
+
+__global__ void __launch_bounds__(kModeEpiBlock)
+mode_epilogue_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ order,
+                     FreqPlan fp, ModeDev md, int n_work, int gmax, PairOut out) {
+    const int64_t idx = (int64_t)blockIdx.x * kModeEpiBlock + threadIdx.x;
+    const int64_t rank = idx / fp.count;
+    if (rank >= n_work) return;
+    const int slot = (int)(idx - rank * fp.count);
+    const int c = order[rank];
+    const CurveParams P = cp[c];
+    bool active;
+    (void)mode_slot_freq(fp, c, slot, active);
+    if (!active) return;
+    const int64_t obase = (int64_t)c * fp.count + slot;
+    if (P.status != 0) {
+        mode_nan(obase, out);
+        return;
+    }
+    const ModeCurve M = md.curves[c];
+    if (M.groups == 0) return;
+    double SJ = M.c0 * M.sj0, ST = M.c0 * M.n0 * M.n0, SC = M.c0 * M.n0 * M.sj0;
+    for (int g = 0; g < M.groups; ++g) {
+        const double* pp = out.part + ((rank * gmax + g) * fp.count + slot) * 3;
+        SJ += pp[0];
+        ST += pp[1];
+        SC += pp[2];
+    }
+    mode_scores(P, SJ, ST, SC, obase, out);
+}
+
+// --------------------------------------------------------------------------------------------
+// Near ties of a search in FP64
+// --------------------------------------------------------------------------------------------
+
+// On a flat maximum neighbouring refined points differ by less than the mixed sums' errors, which
+// are independent from point to point.  best_kernel lists the points of such a curve, and this
+// kernel forms their scores once more with the same node values, but harmonics, products and sums
+// in FP64: what is left is an error that does not change from point to point.  One workgroup per
+// (curve, listed point).  Lane = (cosine or sine, one of the block's two node blocks, node); the
+// four waves take 6 of every 24 harmonics each.  A point costs about 20 us of one workgroup (600
+// samples, 21 harmonics, bound by LDS reads of the harmonics); one curve in ten has a list.
+constexpr int kTieThreads = 256;
+constexpr int kTiePerWave = 6;
+constexpr int kTieModes = 4 * kTiePerWave;
+
+__global__ void __launch_bounds__(kTieThreads)
+mode_ties_kernel(const CurveParams* __restrict__ cp, FreqPlan fp, ModeDev md, int score_kind,
+                 TieDev tie) {
+    __shared__ double z[kTieModes][32][2];
+    __shared__ double red[4][3];
+    const int c = blockIdx.x, k = blockIdx.y;
+    if (k >= tie.count[c]) return;
+    const CurveParams P = cp[c];
+    const ModeCurve M = md.curves[c];
+    const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
+    const int r = lane & 15, nb = (lane >> 4) & 1, cs = lane >> 5;
+    bool active;
+    const double f = mode_slot_freq(fp, c, tie.slot[c * kTieMax + k], active);
+    const double* ts = md.ts + 32 * M.boff;
+    const half8v* frag = reinterpret_cast<const half8v*>(md.frag) + M.boff * 256 + nb * 128 + r;
+    const double* bq = md.b + M.boff * 32 + r;
+    const int32_t* rows = md.rows + M.boff;
+    const double* coef = md.coef + (int64_t)c * mode_stride(md.mode_cap);
+    const int keep = M.groups * kModeGroup;  // coefficients past the last harmonic are zero
+    double SJ = 0.0, ST = 0.0, SC = 0.0;
+    for (int base = 0; base < keep; base += kTieModes) {
+        double a[kTiePerWave], sq[kTiePerWave], sa[kTiePerWave], sb[kTiePerWave];
+#pragma unroll
+        for (int m = 0; m < kTiePerWave; ++m) a[m] = sq[m] = sa[m] = sb[m] = 0.0;
+        // Folds the lower node block (lanes nb = 0) and moves the upper one down.
+        auto fold = [&](int row) {
+            const double b = nb == 0 ? bq[(int64_t)row * 16] : 0.0;
+#pragma unroll
+            for (int m = 0; m < kTiePerWave; ++m) {
+                if (nb == 0) {
+                    sq[m] = fma(a[m], a[m], sq[m]);
+                    sa[m] += a[m];
+                    sb[m] = fma(b, a[m], sb[m]);
+                }
+                const double up = __shfl_xor(a[m], 16, 64);
+                a[m] = nb == 0 ? up : 0.0;
+            }
+        };
+        int wb = 0;
+        for (int kb = 0; kb < M.blocks; ++kb) {
+            __syncthreads();  // the previous block's harmonics have been read
+            {
+                const int i = threadIdx.x & 31, g = threadIdx.x >> 5;
+                const double t = ts[32 * kb + i];
+                const double p = fma(f, t, -rint(f * t));
+                for (int q = 0; q < kTieModes / 8; ++q) {
+                    const int m = g * (kTieModes / 8) + q;
+                    const double md0 = (double)(base + m + 1);
+                    double sn, cn;
+                    sincospi(2.0 * fma(md0, p, -rint(md0 * p)), &sn, &cn);
+                    z[m][i][0] = cn;
+                    z[m][i][1] = sn;
+                }
+            }
+            __syncthreads();
+            const int row = uni(rows[kb]);
+            while (wb < row) fold(wb++);
+            for (int g = 0; g < 4; ++g) {
+                const half8v h = frag[(int64_t)kb * 256 + 16 * g];
+                const half8v l = frag[(int64_t)kb * 256 + 64 + 16 * g];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const double u = (double)(float)h[j] + (double)(float)l[j];
+#pragma unroll
+                    for (int m = 0; m < kTiePerWave; ++m)
+                        a[m] = fma(u, z[wave * kTiePerWave + m][8 * g + j][cs], a[m]);
+                }
+            }
+        }
+        fold(wb);
+        fold(wb + 1);
+#pragma unroll
+        for (int m = 0; m < kTiePerWave; ++m) {
+            // Sums over the nodes: the 32 lanes of cosines and of sines; then over both.
+            for (int o = 16; o > 0; o >>= 1) {
+                sq[m] += __shfl_xor(sq[m], o, 64);
+                sa[m] += __shfl_xor(sa[m], o, 64);
+                sb[m] += __shfl_xor(sb[m], o, 64);
+            }
+            double tt = kNodeP * sa[m] * (kNodeP * sa[m]);
+            double cc = kNodeP * sa[m] * (kNodeW * sb[m]);
+            const double q2 = sq[m] + __shfl_xor(sq[m], 32, 64);
+            tt += __shfl_xor(tt, 32, 64);
+            cc += __shfl_xor(cc, 32, 64);
+            const int at = base + wave * kTiePerWave + m;
+            const double cm = at < keep ? coef[at] : 0.0;
+            SJ = fma(cm, kNodeW * q2, SJ);
+            ST = fma(cm, tt, ST);
+            SC = fma(cm, cc, SC);
+        }
+    }
+    if (lane == 0) {
+        red[wave][0] = SJ;
+        red[wave][1] = ST;
+        red[wave][2] = SC;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    SJ = M.c0 * M.sj0;
+    ST = M.c0 * M.n0 * M.n0;
+    SC = M.c0 * M.n0 * M.sj0;
+    for (int w = 0; w < 4; ++w) {
+        SJ += red[w][0];
+        ST += red[w][1];
+        SC += red[w][2];
+    }
+    const PairOut out{tie.score, nullptr, nullptr, score_kind, 0, nullptr};
+    mode_scores(P, SJ, ST, SC, (int64_t)c * kTieMax + k, out);
+}
+
+}  // namespace
+
+size_t nodes_lds(int max_n, int mode_cap) {
+    int m = 1;
+    while (m < max_n) m <<= 1;
+    return std::max((size_t)m * 12, (size_t)(2 * (3 * mode_cap + 32) + mode_cap + 1) * 8);
+}
+
+hipError_t launch_nodes(hipStream_t st, CurveParams* cp, int n_curves, int max_n, const double* t,
+                        const double* y, const ModeDev& md) {
+    if (n_curves <= 0) return hipSuccess;
+    nodes_kernel<<<n_curves, kNodesBlock, nodes_lds(max_n, md.mode_cap), st>>>(cp, t, y, md);
+    return hipGetLastError();
+}
+
+hipError_t launch_mode_ties(hipStream_t st, const CurveParams* cp, int n_curves,
+                            const FreqPlan& fp, const ModeDev& md, int score_kind,
+                            const TieDev& tie) {
+    if (n_curves <= 0) return hipSuccess;
+    mode_ties_kernel<<<dim3(n_curves, kTieMax), kTieThreads, 0, st>>>(cp, fp, md, score_kind, tie);
+    return hipGetLastError();
+}
+
+hipError_t launch_modes(hipStream_t st, const CurveParams* cp, const int32_t* order,
+                        int n_work_curves, const FreqPlan& fp, const ModeDev& md,
+                        const PairOut& out, int split_groups) {
+    if (n_work_curves <= 0 || fp.count <= 0) return hipSuccess;
+    const int64_t tiles = (fp.count + kLanes - 1) / kLanes;
+    if (split_groups > 0 && out.part) {
+        const int64_t blocks = (int64_t)n_work_curves * split_groups * tiles;
+        modes_kernel<true><<<(unsigned)blocks, kModeThreads, 0, st>>>(
+            cp, order, fp, md, n_work_curves, 0, split_groups, out);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const int64_t threads = (int64_t)n_work_curves * fp.count;
+        mode_epilogue_kernel<<<(unsigned)((threads + kModeEpiBlock - 1) / kModeEpiBlock),
+                               kModeEpiBlock, 0, st>>>(cp, order, fp, md, n_work_curves,
+                                                       split_groups, out);
+        return hipGetLastError();
+    }
+    const int xcd = n_work_curves >= 8 * kXcds;
+    const int64_t rows = xcd ? (int64_t)(n_work_curves + kXcds - 1) / kXcds * kXcds
+                             : (int64_t)n_work_curves;
+    modes_kernel<false><<<(unsigned)(rows * tiles), kModeThreads, 0, st>>>(
+        cp, order, fp, md, n_work_curves, xcd, 0, out);
+    return hipGetLastError();
+}
+
+}  // namespace qmi

@@ -168,14 +168,23 @@ peaks_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coar
 
 constexpr int kBestBlock = 256;
 
+// Twice the largest error of a mode-sum score seen against FP64 (QMI: 1e-7 at 40 samples, 5e-8 and
+// less from 100 on; nCKP = sqrt(N st) / IP_y (V_J - V_M) with relative errors of the V's of the
+// same size): points closer to the best than this are compared in FP64.
+__device__ __forceinline__ double tie_margin(const CurveParams& P, int score_kind, double best) {
+    constexpr double e = 2e-7;
+    return score_kind == 0 ? e : e * (fabs(best) + 2.0 * P.A * sqrt((double)P.n * P.sigma_t));
+}
+
 __global__ void __launch_bounds__(kBestBlock)
 best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coarse,
             const double* __restrict__ coarse2, int F,
             const double* __restrict__ fine, const double* __restrict__ fine2, int top_k,
-            int n_fine, int score_kind, double f0, double df, MaskDev md, PeakOut po,
+            int n_fine, int score_kind, double f0, double df, MaskDev md, PeakOut po, TieDev tie,
             DevResult* __restrict__ res) {
     __shared__ double sq[kBestBlock], sf[kBestBlock];
     __shared__ int ss[kBestBlock];
+    __shared__ int n_ties;
     const int c = blockIdx.x;
     const CurveParams P = cp[c];
     const int npk = (top_k > 0 && n_fine > 0 && P.status == 0) ? po.npk[c] : 0;
@@ -207,6 +216,33 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
         }
         __syncthreads();
     }
+    // The points that the mode sums cannot tell from the best (tie_margin), where there are any
+    // besides it; with more than kTieMax the margin is halved until they fit.
+    if (tie.count && P.status == 0 && npk > 0 && ss[0] != 0x7fffffff &&
+        tie.curves[c].groups > 0) {
+        double margin = tie_margin(P, score_kind, sq[0]);
+        int found = kTieMax + 1;
+        while (found > kTieMax) {
+            __syncthreads();
+            if (threadIdx.x == 0) n_ties = 0;
+            __syncthreads();
+            for (int s = threadIdx.x; s < npk * n_fine; s += kBestBlock) {
+                const double v = fine[(int64_t)c * S + s];
+                if (!(v >= sq[0] - margin)) continue;
+                const double* w = po.win + ((int64_t)c * top_k + s / n_fine) * 2;
+                if (in_mask(md, __dadd_rn(w[0], __dmul_rn((double)(s % n_fine), w[1])), v)) continue;
+                const int at = atomicAdd(&n_ties, 1);
+                if (at < kTieMax) tie.slot[c * kTieMax + at] = s;
+            }
+            __syncthreads();
+            found = n_ties;
+            margin = margin > 1e-15 * fabs(sq[0]) ? 0.5 * margin : -1.0;
+            if (margin < 0.0 && found > kTieMax) found = 1;  // equal values: the first one
+        }
+        if (threadIdx.x == 0) tie.count[c] = found > 1 ? found : 0;
+    } else if (tie.count && threadIdx.x == 0) {
+        tie.count[c] = 0;
+    }
     if (threadIdx.x != 0) return;
     DevResult r;
     r.sigma_y = P.sigma_y;
@@ -214,7 +250,7 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
     r.psnr = P.psnr;
     r.n = P.n;
     r.status = P.status;
-    r.reserved = 0;
+    r.reserved = P.sparse;  // nonzero: the host searches the curve again by the pair sums
     r.n_peaks = npk;
     const int am = (P.status == 0) ? po.argmax[c] : -1;
     r.coarse_argmax = am;
@@ -248,6 +284,42 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
     res[c] = r;
 }
 
+// The record of a curve with a list of near ties: the point with the highest FP64 score (ties to
+// the lower frequency, then the lower peak rank), with its scores as the refinement formed them.
+__global__ void best_of_ties_kernel(int n_curves, const double* __restrict__ fine,
+                                    const double* __restrict__ fine2, int top_k, int n_fine,
+                                    int score_kind, PeakOut po, TieDev tie,
+                                    DevResult* __restrict__ res) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= n_curves || tie.count[c] == 0) return;
+    const int64_t S = (int64_t)top_k * n_fine;
+    double bq = NAN, bf = INFINITY;
+    int bs = 0x7fffffff;
+    for (int k = 0; k < tie.count[c]; ++k) {
+        const double v = tie.score[c * kTieMax + k];
+        const int s = tie.slot[c * kTieMax + k];
+        const double* w = po.win + ((int64_t)c * top_k + s / n_fine) * 2;
+        const double fr = __dadd_rn(w[0], __dmul_rn((double)(s % n_fine), w[1]));
+        if ((v == v) &&
+            (!(bq == bq) || v > bq || (v == bq && (fr < bf || (fr == bf && s < bs))))) {
+            bq = v;
+            bf = fr;
+            bs = s;
+        }
+    }
+    if (bs == 0x7fffffff) return;
+    DevResult& r = res[c];
+    r.f_best = bf;
+    r.period = 1.0 / bf;
+    r.score = fine[(int64_t)c * S + bs];
+    const double other = fine2 ? fine2[(int64_t)c * S + bs] : NAN;
+    r.score_qmi = score_kind == 0 ? r.score : other;
+    r.score_nckp = score_kind == 0 ? other : r.score;
+    r.coarse_index = po.peak_k[(int64_t)c * top_k + bs / n_fine];
+    r.peak_rank = bs / n_fine;
+    r.fine_index = bs % n_fine;
+}
+
 }  // namespace
 
 hipError_t launch_peaks(hipStream_t st, const CurveParams* cp, int n_curves, const double* coarse,
@@ -272,10 +344,20 @@ hipError_t launch_peaks(hipStream_t st, const CurveParams* cp, int n_curves, con
 hipError_t launch_best(hipStream_t st, const CurveParams* cp, int n_curves, const double* coarse,
                        const double* coarse2, int n_coarse, const double* fine,
                        const double* fine2, int top_k, int n_fine, int score_kind, double f0,
-                       double df, const MaskDev& md, const PeakOut& po, DevResult* res) {
+                       double df, const MaskDev& md, const PeakOut& po, const TieDev& tie,
+                       DevResult* res) {
     if (n_curves <= 0) return hipSuccess;
     best_kernel<<<n_curves, kBestBlock, 0, st>>>(cp, coarse, coarse2, n_coarse, fine, fine2, top_k,
-                                                  n_fine, score_kind, f0, df, md, po, res);
+                                                  n_fine, score_kind, f0, df, md, po, tie, res);
+    return hipGetLastError();
+}
+
+hipError_t launch_best_of_ties(hipStream_t st, int n_curves, const double* fine,
+                               const double* fine2, int top_k, int n_fine, int score_kind,
+                               const PeakOut& po, const TieDev& tie, DevResult* res) {
+    if (n_curves <= 0) return hipSuccess;
+    best_of_ties_kernel<<<(n_curves + 63) / 64, 64, 0, st>>>(n_curves, fine, fine2, top_k, n_fine,
+                                                             score_kind, po, tie, res);
     return hipGetLastError();
 }
 
