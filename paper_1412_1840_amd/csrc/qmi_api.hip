@@ -442,7 +442,6 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     int64_t mblocks = 0;
     int64_t all_k = 0, all_p = 0, all_ks = 0;  // the pair sums' tables if they took every curve
     int32_t n_modes = 0;  // curves whose sums are taken over modes
-    int max_mode_n = 2;
     const bool rule_t = kp->sigma_t == QMI_SIGMA_T_SKEWNESS;
     const double min_sigma_t = !rule_t ? kp->sigma_t
                                : kp->skew_lambda > 0.0 ? kp->skew_lambda : QMI_SKEW_LAMBDA;
@@ -476,14 +475,14 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             all_p += np;
             all_ks += (int64_t)((p.n + kPassR - 1) / kPassR) * kWaves * p.n;
         }
-        const int room = mode_groups > 0 ? mode_room(p.n, mode_groups) : 0;
-        if (p.status == QMI_OK && room >= (p.n + 31) / 32 + 2) {
+        const int whole = (p.n + 31) / 32 + 2;
+        if (p.status == QMI_OK && mode_groups > 0 && whole <= mode_even(p.n, mode_groups) &&
+            whole <= p.n / 5) {
             ModeCurve& m = mc[i];
-            m.cap = room;
+            m.cap = mode_room(p.n, mode_groups);
             m.boff = mblocks;
             mblocks += m.cap;
             ++n_modes;
-            max_mode_n = std::max(max_mode_n, p.n);
             max_n = std::max(max_n, p.n);
         } else if (p.status == QMI_OK) {
             p.npad = (int32_t)round_up(p.n, kPass);
@@ -775,8 +774,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             if (events) record(ctx);
         };
         rec();  // device section start
-        HIP_OK(ctx, launch_prologue(st, dcp, nc, max_n, t, y, e, skew_lambda, skew_mu));
-        if (n_modes) HIP_OK(ctx, launch_nodes(st, dcp, nc, max_mode_n, t, y, md));
+        HIP_OK(ctx, launch_prepare(st, dcp, nc, max_n, t, y, e, skew_lambda, skew_mu, md));
         if (n_pairs) {
             HIP_OK(ctx, launch_gram<R>(st, dcp, nc, rows, drow, y, K, rp, rd));
             HIP_OK(ctx, launch_gram_finalize<R>(st, dcp, nc, rd, rp));
@@ -866,7 +864,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             u(dres), (uint64_t)(bp != nullptr), dbits(bd.f_lo), dbits(bd.df),
             (uint64_t)bd.n_grid, (uint64_t)bd.n_bands, (uint64_t)bd.n_keep, (uint64_t)bd.n_trials,
             (uint64_t)bd.stride, u(bd.ts), u(bd.ys), u(bd.band_t), u(bd.band_cnt), u(bd.band_id),
-            u(bd.S), u(bd.trials), u(bd.trial_k), (uint64_t)n_modes, (uint64_t)max_mode_n,
+            u(bd.S), u(bd.trials), u(bd.trial_k), (uint64_t)n_modes,
             (uint64_t)mode_groups, (uint64_t)max_pieces, (uint64_t)split1, (uint64_t)split2,
             (uint64_t)msplit1, (uint64_t)msplit2, u(dpart), u(md.curves), u(md.ts), u(md.rows),
             u(md.frag), u(md.part), u(md.b), u(md.coef), u(tie.count), u(tie.slot), u(tie.score)};

@@ -9,6 +9,8 @@
 
 namespace qmi {
 
+typedef _Float16 half8v __attribute__((ext_vector_type(8)));
+
 // Pair-kernel geometry.  A work item is (curve, tile of kLanes frequency slots); one lane owns one
 // frequency.  The pair triangle i < j is walked in passes of kPass rows; inside a pass wave w owns
 // the interleaved rows base + w + kWaves*m (m < rows per wave), so every wave has nearly the same
@@ -66,23 +68,35 @@ struct CurveParams {
 constexpr double kModeTail = 1e-8;
 constexpr int kModeGroup = 7;      // harmonics per pass over the samples
 constexpr int kModeCapMax = 256;     // most harmonics (sigma_t from 0.03)
-// Blocks that a curve may use before the pair sums are faster; the host gives a curve to the mode
-// sums when its whole blocks and two more fit, and nodes_kernel gives it back when its samples are
-// so scattered over node blocks that they need more than these.  Measured per curve and frequency
-// (4096 frequencies, batches): the pair sums take 9.2e-5 n^2 + 0.008 n + 0.25 ns, the mode sums
-// 0.1 ns per block and group of harmonics, so they meet at n = 40, 72, 290 and 520 for sigma_t =
-// 0.6, 0.3, 0.1 and 0.05 (2, 3, 9 and 17 groups).  n / 5 bounds the tables by the size of the pair
-// sums' table of kernel values.
+// Blocks with which the mode sums take the pair sums' time; the host gives a curve to the mode sums
+// when its whole blocks and two more are no more than that.  Measured per curve and frequency (4096
+// frequencies, batches): the pair sums take 9.2e-5 n^2 + 0.008 n + 0.25 ns, the mode sums 0.1 ns
+// per block and group of harmonics, so they meet at n = 40, 72, 290 and 520 for sigma_t = 0.6, 0.3,
+// 0.1 and 0.05 (2, 3, 9 and 17 groups).
+inline int mode_even(int n, int groups) {
+    return (int)((9.2e-4 * n * n + 0.08 * n + 2.5) / groups);
+}
+// Blocks a curve has room for: the preparation gives a curve back to the pair sums when its samples
+// are so scattered over node blocks that they need more.  Twice the blocks of equal time, since
+// such a curve runs in launches of its own; n / 5 bounds the tables by the size of the pair sums'
+// table of kernel values.
 inline int mode_room(int n, int groups) {
-    const int room = (int)((9.2e-4 * n * n + 0.08 * n + 2.5) / groups);
+    const int room = 2 * mode_even(n, groups);
     return room < n / 5 ? room : n / 5;
 }
-constexpr int kModeMaxBlocks = QMI_MAX_N / 5;
 // Coefficients stored per curve (whole groups).
 __host__ __device__ constexpr int mode_stride(int cap) {
     return (cap + kModeGroup - 1) / kModeGroup * kModeGroup;
 }
 
+// Node spacing in units of sigma_y: the trapezoid error 2 exp(-pi^2 / (2 h^2)) is 5e-9 of a kernel
+// value and alternates in sign along the magnitudes, so that it averages out over the pairs.
+constexpr double kNodeStep = 0.5;
+constexpr double kNodeW = kNodeStep * 0.79788456080286535587989211986876;  // h sqrt(2/pi)
+constexpr double kNodeP = kNodeStep * 0.56418958354775628694807945156077;  // h / sqrt(pi)
+// A sample uses the 16-node blocks rb and rb + 1, rb chosen so that they hold at least the
+// 2 kReach + 1 nodes nearest to it (beyond, U < exp(-(8.5 h)^2) = 1.5e-8).
+constexpr int kReach = 8;
 struct ModeCurve {
     int64_t boff;   // first of its cap blocks
     int32_t cap;    // blocks there is room for; 0: the curve is left to the pair sums
@@ -105,7 +119,6 @@ struct ModeDev {
     int32_t mode_cap;  // coefficients there is room for (past the harmonics kept)
     int32_t max_groups; // most groups of harmonics of any curve
 };
-size_t nodes_lds(int max_n, int mode_cap);
 
 // Interleaved partial sums of a column's terms over a wave's rows (row m goes to partial
 // m mod kPartials), combined at the end of the column: the pair kernel and the column-sum tables
@@ -209,7 +222,6 @@ struct BandsDev {
     double* trials;       // [curve][n_keep * n_trials] trial frequencies, NaN = none
     int32_t* trial_k;     // [curve][n_keep * n_trials] their grid indices, -1 = none
 };
-size_t bands_prep_lds(int max_n);
 hipError_t launch_bands(hipStream_t st, const CurveParams* cp, int n_curves, int max_n,
                         const double* t, const double* y, const BandsDev& bd);
 hipError_t launch_bands_best(hipStream_t st, const CurveParams* cp, int n_curves,
@@ -227,7 +239,6 @@ struct PrepDev {
     double* y_out;
     double* e_out;
 };
-size_t whiten_lds(int max_n);
 hipError_t launch_prep(hipStream_t st, int n_curves, const int64_t* offsets, const double* t,
                        const double* y, const double* e, const PrepDev& pd);
 hipError_t launch_whiten(hipStream_t st, int n_curves, int max_n, const int64_t* offsets,
@@ -235,11 +246,12 @@ hipError_t launch_whiten(hipStream_t st, int n_curves, int max_n, const int64_t*
                          const int32_t* status, double* y_out);
 
 // Launchers (qmi_kernels.hip).  All launch on `st` and return hipGetLastError().
-// skew_lambda, skew_mu: constants of the sigma_t rule, applied to curves whose sigma_t is
-// QMI_SIGMA_T_SKEWNESS.
-hipError_t launch_prologue(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
-                           const double* t, const double* y, const double* e, double skew_lambda,
-                           double skew_mu);
+// Per-curve preparation (qmi_prepare.hip): kernel widths and pSNR, and with md.curves the node
+// tables of the curves summed over modes.  skew_lambda, skew_mu: constants of the sigma_t rule,
+// applied to curves whose sigma_t is QMI_SIGMA_T_SKEWNESS.
+hipError_t launch_prepare(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
+                          const double* t, const double* y, const double* e, double skew_lambda,
+                          double skew_mu, const ModeDev& md);
 template <typename R>
 hipError_t launch_gram(hipStream_t st, CurveParams* cp, int n_curves, int64_t total_rows,
                        const int64_t* row_curve_start, const double* y, R* K, double* rp,
@@ -269,11 +281,9 @@ constexpr int kRemSlots = kLanes / 32;
 hipError_t launch_pairs_rows(hipStream_t st, const CurveParams* cp, const int32_t* order,
                              int n_work_curves, const FreqPlan& fp, int slot0, const double* t,
                              const float* K, const double* rd, const PairOut& out);
-// Mode sums: launch_nodes prepares the curves (after the prologue), launch_modes runs a frequency
-// plan.  split_groups > 0 (with out.part, [rank][split_groups][count][3]): one harmonic group per
-// wave, then the epilogue kernel; 0: every group in one wave.  Both give the same bits.
-hipError_t launch_nodes(hipStream_t st, CurveParams* cp, int n_curves, int max_n, const double* t,
-                        const double* y, const ModeDev& md);
+// Mode sums of a frequency plan.  split_groups > 0 (with out.part,
+// [rank][split_groups][count][3]): one harmonic group per wave, then the epilogue kernel; 0: every
+// group in one wave.  Both give the same bits.
 hipError_t launch_modes(hipStream_t st, const CurveParams* cp, const int32_t* order,
                         int n_work_curves, const FreqPlan& fp, const ModeDev& md,
                         const PairOut& out, int split_groups);

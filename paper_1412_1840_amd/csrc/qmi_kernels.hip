@@ -1,5 +1,5 @@
-// HIP kernels for gfx950 (MI355X): prologue (kernel widths, pSNR), magnitude Gram matrix, column
-// K sums and the pair x frequency sums (the hot path).  The peak search and best-of kernels are in
+// HIP kernels for gfx950 (MI355X): magnitude Gram matrix, column K sums and the pair x frequency
+// sums (FP64 mode, and mixed mode where the mode sums do not pay).  The peak search and best-of kernels are in
 // qmi_search.hip.
 //
 // Method: Protopapas et al., arXiv:1412.1840.  Gaussian kernel (Sec. 2), periodic kernel and the
@@ -15,7 +15,6 @@ namespace qmi {
 namespace {
 
 constexpr double kLog2e = 1.4426950408889634073599246810018921;
-constexpr double kInvSqrt2Pi = 0.39894228040143267793994605993438187;
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ float uniform(float v) {
@@ -49,131 +48,6 @@ __device__ double block_sum(double v, double* sh) {
     double r = sh[0];
     __syncthreads();
     return r;
-}
-
-// In-LDS bitonic sort of n values (padded to a power of two with +inf) by one block.
-template <int BLOCK>
-__device__ void block_sort(double* a, int n) {
-    int m = 1;
-    while (m < n) m <<= 1;
-    for (int i = n + threadIdx.x; i < m; i += BLOCK) a[i] = INFINITY;
-    __syncthreads();
-    for (int k = 2; k <= m; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < m; i += BLOCK) {
-                int l = i ^ j;
-                if (l > i) {
-                    double x = a[i], y = a[l];
-                    bool up = (i & k) == 0;
-                    if ((x > y) == up) {
-                        a[i] = y;
-                        a[l] = x;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// Quantile by linear interpolation at position (n-1) p of sorted a[0..n).
-__device__ double sorted_quantile(const double* a, int n, double p) {
-    double h = (n - 1) * p;
-    int lo = (int)floor(h);
-    int hi = lo + 1 < n ? lo + 1 : n - 1;
-    return a[lo] + (h - lo) * (a[hi] - a[lo]);
-}
-
-__device__ double sorted_median(const double* a, int n) {
-    return (n & 1) ? a[n / 2] : 0.5 * (a[n / 2 - 1] + a[n / 2]);
-}
-
-// --------------------------------------------------------------------------------------------
-// Prologue: validity, sigma_y (Silverman or median error bar), sigma_t (given, or the skewness
-// rule of Sec. 3), pSNR, A, B.  One block per curve.
-// --------------------------------------------------------------------------------------------
-
-constexpr int kPrologueBlock = 256;
-
-__global__ void __launch_bounds__(kPrologueBlock)
-prologue_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t,
-                const double* __restrict__ y, const double* __restrict__ e, double skew_lambda,
-                double skew_mu) {
-    extern __shared__ double sbuf[];  // [QMI_MAX_N rounded to pow2] + 64 scratch
-    __shared__ double red[kPrologueBlock / 64 + 1];
-    __shared__ int bad;
-    const int c = blockIdx.x;
-    CurveParams P = cp[c];
-    const int n = P.n;
-    if (P.status != 0) return;
-    if (threadIdx.x == 0) bad = 0;
-    __syncthreads();
-    const double* tc = t + P.off;
-    const double* yc = y + P.off;
-    const double* ec = P.has_e ? e + P.off : nullptr;
-    for (int i = threadIdx.x; i < n; i += kPrologueBlock) {
-        bool ok = isfinite(tc[i]) && isfinite(yc[i]);
-        if (ec) ok = ok && isfinite(ec[i]);
-        if (!ok) bad = 1;
-    }
-    __syncthreads();
-    if (bad || n < 2) {
-        if (threadIdx.x == 0) cp[c].status = -1;  // QMI_EINVAL
-        return;
-    }
-    // Mean and sample deviation of y.
-    double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += kPrologueBlock) s += yc[i];
-    const double mean = block_sum<kPrologueBlock>(s, red) / n;
-    s = 0.0;
-    for (int i = threadIdx.x; i < n; i += kPrologueBlock) {
-        double d = yc[i] - mean;
-        s += d * d;
-    }
-    const double sdev = sqrt(block_sum<kPrologueBlock>(s, red) / (n - 1));
-    // Quartiles of y.
-    for (int i = threadIdx.x; i < n; i += kPrologueBlock) sbuf[i] = yc[i];
-    block_sort<kPrologueBlock>(sbuf, n);
-    const double iqr = sorted_quantile(sbuf, n, 0.75) - sorted_quantile(sbuf, n, 0.25);
-    // sigma_t rule (Sec. 3): S = (Q3 + Q1 - 2 Q2) / (Q3 - Q1) with Q2 the median and Q1, Q3 the
-    // medians of the lower and upper n / 2 sorted magnitudes; S = 0 when Q3 = Q1.
-    double sigma_t = P.sigma_t;
-    if (!(sigma_t > 0.0)) {
-        const int h = n / 2;
-        const double q1 = sorted_median(sbuf, h), q2 = sorted_median(sbuf, n);
-        const double q3 = sorted_median(sbuf + (n - h), h);
-        const double S = (q3 == q1) ? 0.0 : (q3 + q1 - 2.0 * q2) / (q3 - q1);
-        sigma_t = skew_lambda + 0.5 * exp(-skew_mu * S * S);
-    }
-    __syncthreads();
-    double med_e = NAN;
-    if (ec) {
-        for (int i = threadIdx.x; i < n; i += kPrologueBlock) sbuf[i] = ec[i];
-        block_sort<kPrologueBlock>(sbuf, n);
-        med_e = sorted_median(sbuf, n);
-    }
-    if (threadIdx.x != 0) return;
-    double sy = 0.0;
-    int status = 0;
-    if (P.sigma_y_rule > 0.0) {
-        sy = P.sigma_y_rule;
-    } else if (P.sigma_y_rule == -1.0) {
-        if (sdev == 0.0) {
-            status = -4;  // QMI_EDEGENERATE
-        } else {
-            double spread = (iqr == 0.0) ? sdev : fmin(sdev, iqr / 1.34);
-            sy = 0.9 * spread * pow((double)n, -0.2);
-        }
-    } else {
-        if (!(med_e > 0.0)) status = ec ? -4 : -1;
-        sy = med_e;
-    }
-    cp[c].status = status;
-    cp[c].sigma_y = status ? NAN : sy;
-    cp[c].sigma_t = sigma_t;
-    cp[c].A = kInvSqrt2Pi / sigma_t;
-    cp[c].B = status ? NAN : kInvSqrt2Pi / sy;
-    cp[c].psnr = (ec && med_e > 0.0) ? 0.7413 * iqr / med_e : NAN;
 }
 
 // --------------------------------------------------------------------------------------------
@@ -1002,17 +876,6 @@ pairs_rows_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict_
 // --------------------------------------------------------------------------------------------
 // Launchers
 // --------------------------------------------------------------------------------------------
-
-hipError_t launch_prologue(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
-                           const double* t, const double* y, const double* e, double skew_lambda,
-                           double skew_mu) {
-    if (n_curves <= 0) return hipSuccess;
-    int m = 1;
-    while (m < max_n) m <<= 1;
-    size_t shm = sizeof(double) * (size_t)m;
-    prologue_kernel<<<n_curves, kPrologueBlock, shm, st>>>(cp, t, y, e, skew_lambda, skew_mu);
-    return hipGetLastError();
-}
 
 template <typename R>
 hipError_t launch_gram(hipStream_t st, CurveParams* cp, int n_curves, int64_t total_rows,

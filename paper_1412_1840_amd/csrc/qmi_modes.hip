@@ -20,8 +20,6 @@
 // QMI wherever time and magnitude are independent, and exactly where all phases coincide.
 #include <math.h>
 
-#include <algorithm>
-
 #include "qmi_internal.h"
 
 namespace qmi {
@@ -29,282 +27,16 @@ namespace qmi {
 namespace {
 
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 typedef float float2v __attribute__((ext_vector_type(2)));
 typedef double double2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-// Node spacing in units of sigma_y: the trapezoid error 2 exp(-pi^2 / (2 h^2)) is 5e-9 of a kernel
-// value and alternates in sign along the magnitudes, so that it averages out over the pairs.
-constexpr double kNodeStep = 0.5;
-constexpr double kNodeW = kNodeStep * 0.79788456080286535587989211986876;  // h sqrt(2/pi)
-constexpr double kNodeP = kNodeStep * 0.56418958354775628694807945156077;  // h / sqrt(pi)
-// A sample uses the 16-node blocks rb and rb + 1, rb chosen so that they hold at least the
-// 2 kReach + 1 nodes nearest to it (beyond, U < exp(-(8.5 h)^2) = 1.5e-8).
-constexpr int kReach = 8;
 // v_sin_f32 and v_cos_f32 round towards zero: measured over the whole circle, sin^2 + cos^2 is
 // 6.5e-8 below 1 on average.  A harmonic formed by k products from them has its |a|^2 short by
 // (k + 1) times that, which the coefficients make up for.
 constexpr double kTrigLoss = 6.5e-8;
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// --------------------------------------------------------------------------------------------
-// Preparation: sorted samples, node blocks, matrix fragments, node sums, coefficients.
-// --------------------------------------------------------------------------------------------
-
-constexpr int kNodesBlock = 256;
-
-__device__ double nodes_sum(double v, double* sh) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double s = 0.0;
-    for (int k = 0; k < kNodesBlock / 64; ++k) s += sh[k];
-    __syncthreads();
-    return s;
-}
-
-// Exclusive prefix sum of one value per thread; *total receives the sum.
-__device__ int nodes_scan(int v, int* sh, int* total) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int s = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        const int u = __shfl_up(s, o, 64);
-        if (lane >= o) s += u;
-    }
-    __syncthreads();
-    if (lane == 63) sh[w] = s;
-    __syncthreads();
-    int base = 0, all = 0;
-    for (int k = 0; k < kNodesBlock / 64; ++k) {
-        if (k < w) base += sh[k];
-        all += sh[k];
-    }
-    __syncthreads();
-    *total = all;
-    return base + s - v;
-}
-
-// One block per curve.  Dynamic LDS: pow2(max_n) x 12 bytes (keys, indices), at least the
-// coefficient tables.
-__global__ void __launch_bounds__(kNodesBlock)
-nodes_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
-             const double* __restrict__ y_all, ModeDev md) {
-    extern __shared__ double nsh[];
-    __shared__ double red[kNodesBlock / 64];
-    __shared__ int ired[kNodesBlock / 64];
-    __shared__ int g_first[kModeMaxBlocks + 1];  // first sample of each group
-    __shared__ int g_block[kModeMaxBlocks + 1];  // its first block of samples
-    __shared__ int g_row[kModeMaxBlocks];        // its first node block, counted among those in use
-    __shared__ int g_rb[kModeMaxBlocks];         // and by magnitude
-    const int c = blockIdx.x;
-    const CurveParams P = cp[c];
-    ModeCurve M = md.curves[c];
-    if (P.status != 0 || M.cap == 0) return;
-    const int n = P.n;
-    int m2 = 1;
-    while (m2 < n) m2 <<= 1;
-    double* key = nsh;
-    int32_t* idx = reinterpret_cast<int32_t*>(nsh + m2);
-    const double* t = t_all + P.off;
-    const double* y = y_all + P.off;
-    for (int i = threadIdx.x; i < m2; i += kNodesBlock) {
-        key[i] = i < n ? y[i] : INFINITY;
-        idx[i] = i < n ? i : 0x7fffffff;
-    }
-    __syncthreads();
-    for (int k = 2; k <= m2; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < m2; i += kNodesBlock) {
-                const int l = i ^ j;
-                if (l > i) {
-                    const double a = key[i], b = key[l];
-                    const int32_t ia = idx[i], ib = idx[l];
-                    const bool gt = (a > b) || (a == b && ia > ib);
-                    if (gt == ((i & k) == 0)) {
-                        key[i] = b;
-                        key[l] = a;
-                        idx[i] = ib;
-                        idx[l] = ia;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-    const double y0 = key[0];
-    const double inv = 1.0 / (kNodeStep * P.sigma_y);
-    bool sparse = !((key[n - 1] - y0) * inv < 1e9);  // far more nodes than samples can use
-    // Position of a sample in node units, and its first node block.
-    auto pos = [&](int i) { return (key[i] - y0) * inv + (double)kReach; };
-    auto blk = [&](int i) { return ((int)rint(pos(i)) - kReach) >> 4; };
-    // Groups of samples with the same first node block, and the node blocks in use: a group brings
-    // two new ones, or one where the group before it starts one block lower.
-    int n_groups = 0, n_rows = 0, n_blocks = 0;
-    if (!sparse) {
-        const int per = (n + kNodesBlock - 1) / kNodesBlock;
-        const int i0 = min(n, (int)threadIdx.x * per), i1 = min(n, i0 + per);
-        int s = 0, all = 0;  // groups in the low, node blocks in the high half
-        for (int i = i0; i < i1; ++i) {
-            const int d = i == 0 ? 2 : min(2, blk(i) - blk(i - 1));
-            if (d > 0) s += 1 + (d << 16);
-        }
-        int e = nodes_scan(s, ired, &all);
-        n_groups = all & 0xffff;
-        n_rows = all >> 16;
-        sparse = n_groups > M.cap;
-        if (!sparse) {
-            for (int i = i0; i < i1; ++i) {
-                const int b = blk(i);
-                const int d = i == 0 ? 2 : min(2, b - blk(i - 1));
-                if (d <= 0) continue;
-                const int g = e & 0xffff;
-                e += 1 + (d << 16);
-                g_first[g] = i;
-                g_rb[g] = b;
-                g_row[g] = (e >> 16) - 2;
-            }
-            if (threadIdx.x == 0) g_first[n_groups] = n;
-            __syncthreads();
-            // Blocks of 32 samples: every group starts a new one.
-            const int gper = (n_groups + kNodesBlock - 1) / kNodesBlock;
-            const int a0 = min(n_groups, (int)threadIdx.x * gper), a1 = min(n_groups, a0 + gper);
-            int nb = 0;
-            for (int g = a0; g < a1; ++g) nb += (g_first[g + 1] - g_first[g] + 31) >> 5;
-            int f = nodes_scan(nb, ired, &n_blocks);
-            for (int g = a0; g < a1; ++g) {
-                g_block[g] = f;
-                f += (g_first[g + 1] - g_first[g] + 31) >> 5;
-            }
-            if (threadIdx.x == 0) g_block[n_groups] = n_blocks;
-            sparse = n_blocks > M.cap;
-        }
-        __syncthreads();
-    }
-    if (sparse) {
-        if (threadIdx.x == 0) {
-            md.curves[c].groups = 0;
-            cp[c].sparse = 1;
-        }
-        return;
-    }
-    auto group_of = [&](int block) {
-        int lo = 0, hi = n_groups - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (g_block[mid] <= block) lo = mid; else hi = mid - 1;
-        }
-        return lo;
-    };
-    // Times in magnitude order, every group padded to whole blocks.
-    double* ts = md.ts + 32 * M.boff;
-    int32_t* rows = md.rows + M.boff;
-    for (int q = threadIdx.x; q < 32 * n_blocks; q += kNodesBlock) {
-        const int g = group_of(q >> 5);
-        const int i = g_first[g] + q - 32 * g_block[g];
-        ts[q] = i < g_first[g + 1] ? t[idx[i]] : 0.0;
-        if ((q & 31) == 0) rows[q >> 5] = g_row[g];
-    }
-    // Fragments of U in the operand layout of the 16x16x32 matrix instruction: lane l holds node
-    // l mod 16 and samples 8 (l / 16) ... + 7 of the block, as a high and a low half-precision
-    // part; and each node's sum over the block's samples.
-    half8v* frag = reinterpret_cast<half8v*>(md.frag) + M.boff * 256;
-    double* part = md.part + M.boff * 32;
-    double* bsum = md.b + M.boff * 32;
-    const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
-    for (int r = wave; r < 2 * n_blocks; r += kNodesBlock / 64) {
-        const int blk_r = r >> 1, g = group_of(blk_r);
-        const double node = (double)(16 * (g_rb[g] + (r & 1)) + (lane & 15));
-        const int s0 = g_first[g] + 32 * (blk_r - g_block[g]) + 8 * (lane >> 4);
-        const int s_end = g_first[g + 1];
-        half8v h, l;
-        double s = 0.0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            double v = 0.0;
-            if (s0 + j < s_end) {
-                const double d = (node - pos(s0 + j)) * kNodeStep;
-                v = exp(-d * d);
-            }
-            s += v;
-            h[j] = (_Float16)(float)v;
-            l[j] = (_Float16)(float)(v - (double)(float)h[j]);
-        }
-        frag[(int64_t)r * 128 + lane] = h;
-        frag[(int64_t)r * 128 + 64 + lane] = l;
-        s += __shfl_xor(s, 16, 64);
-        s += __shfl_xor(s, 32, 64);
-        if (lane < 16) part[(int64_t)r * 16 + lane] = s;
-    }
-    __syncthreads();
-    double sq = 0.0, sb = 0.0;
-    for (int q = threadIdx.x; q < 16 * n_rows; q += kNodesBlock) {
-        const int row = q >> 4;
-        double b = 0.0;
-        for (int g = 0; g < n_groups; ++g) {
-            const int k = row - g_row[g];
-            if (k < 0) break;
-            if (k > 1) continue;
-            for (int r = g_block[g]; r < g_block[g + 1]; ++r)
-                b += part[(int64_t)(2 * r + k) * 16 + (q & 15)];
-        }
-        bsum[q] = b;
-        sq = fma(b, b, sq);
-        sb += b;
-    }
-    sq = nodes_sum(sq, red);
-    sb = nodes_sum(sb, red);
-    // Coefficients of the periodic kernel's cosine series by the trapezoid rule over the circle
-    // (exact up to the coefficients past L - m), and the number of harmonics to keep.
-    const int cap = md.mode_cap, L = 3 * cap + 32;
-    double* ev = nsh;
-    double* ct = nsh + L;
-    const double kap = 1.0 / (P.sigma_t * P.sigma_t);
-    for (int j = threadIdx.x; j < L; j += kNodesBlock) {
-        const double co = cospi(2.0 * (double)j / (double)L);
-        ct[j] = co;
-        ev[j] = exp(kap * (co - 1.0));
-    }
-    __syncthreads();
-    double* coef = md.coef + (int64_t)c * mode_stride(cap);
-    double* cs = ct + L;  // [cap + 1]
-    for (int m = threadIdx.x; m <= cap; m += kNodesBlock) {
-        double s = 0.0;
-        int k = 0;
-        for (int j = 0; j < L; ++j) {
-            s = fma(ev[j], ct[k], s);
-            k += m;
-            if (k >= L) k -= L;
-        }
-        cs[m] = (m ? 2.0 : 1.0) * s / (double)L;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int m = cap;
-        double tail = 0.0;
-        for (; m > 1; --m) {
-            tail += cs[m];
-            if (tail > kModeTail) break;
-        }
-        m = min(m, md.max_groups * kModeGroup);
-        ired[0] = m;
-        M.groups = (m + kModeGroup - 1) / kModeGroup;
-        M.blocks = n_blocks;
-        M.c0 = cs[0];
-        M.sj0 = kNodeW * sq;
-        M.n0 = kNodeP * sb;
-        md.curves[c] = M;
-        const double N = (double)n;
-        cp[c].ipy = P.B * M.sj0 / (N * N);
-    }
-    __syncthreads();
-    // Coefficient of harmonic m at m - 1; zero past the last one kept.
-    const int keep = ired[0];
-    for (int m = threadIdx.x + 1; m <= mode_stride(cap); m += kNodesBlock)
-        coef[m - 1] = m <= keep ? cs[m] : 0.0;
-}
 
 // --------------------------------------------------------------------------------------------
 // Mode sums
@@ -800,19 +532,6 @@ mode_ties_kernel(const CurveParams* __restrict__ cp, FreqPlan fp, ModeDev md, in
 }
 
 }  // namespace
-
-size_t nodes_lds(int max_n, int mode_cap) {
-    int m = 1;
-    while (m < max_n) m <<= 1;
-    return std::max((size_t)m * 12, (size_t)(2 * (3 * mode_cap + 32) + mode_cap + 1) * 8);
-}
-
-hipError_t launch_nodes(hipStream_t st, CurveParams* cp, int n_curves, int max_n, const double* t,
-                        const double* y, const ModeDev& md) {
-    if (n_curves <= 0) return hipSuccess;
-    nodes_kernel<<<n_curves, kNodesBlock, nodes_lds(max_n, md.mode_cap), st>>>(cp, t, y, md);
-    return hipGetLastError();
-}
 
 hipError_t launch_mode_ties(hipStream_t st, const CurveParams* cp, int n_curves,
                             const FreqPlan& fp, const ModeDev& md, int score_kind,

@@ -1,0 +1,418 @@
+// HIP kernel for gfx950 (MI355X): the per-curve preparation of the sums of Protopapas et al.,
+// arXiv:1412.1840 - kernel widths (Sec. 2, Sec. 3), pSNR (Sec. 5.2), and the node tables of the mode
+// sums (qmi_modes.hip).  One workgroup per curve.
+#include <math.h>
+
+#include <algorithm>
+
+#include "qmi_internal.h"
+#include "qmi_sort.h"
+
+namespace qmi {
+
+namespace {
+
+constexpr double kInvSqrt2Pi = 0.39894228040143267793994605993438187;
+
+// Sums over a curve are formed by the first kSumThreads threads whatever the block (a curve's
+// results do not depend on the longest curve of its batch): wave shuffles, then the waves in order.
+constexpr int kSumThreads = 256;
+
+__device__ double block_sum(double v, double* sh) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0 && threadIdx.x < kSumThreads) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double s = 0.0;
+    for (int k = 0; k < kSumThreads / 64; ++k) s += sh[k];
+    __syncthreads();
+    return s;
+}
+
+// Exclusive prefix sum of one value per thread; *total receives the sum.
+template <int BLOCK>
+__device__ int block_scan(int v, int* sh, int* total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int s = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(s, o, 64);
+        if (lane >= o) s += u;
+    }
+    __syncthreads();
+    if (lane == 63) sh[w] = s;
+    __syncthreads();
+    int base = 0, all = 0;
+    for (int k = 0; k < BLOCK / 64; ++k) {
+        if (k < w) base += sh[k];
+        all += sh[k];
+    }
+    __syncthreads();
+    *total = all;
+    return base + s - v;
+}
+
+// Quantile by linear interpolation at position (n-1) p of sorted a[0..n).
+__device__ double sorted_quantile(const double* a, int n, double p) {
+    double h = (n - 1) * p;
+    int lo = (int)floor(h);
+    int hi = lo + 1 < n ? lo + 1 : n - 1;
+    return a[lo] + (h - lo) * (a[hi] - a[lo]);
+}
+
+__device__ double sorted_median(const double* a, int n) {
+    return (n & 1) ? a[n / 2] : 0.5 * (a[n / 2 - 1] + a[n / 2]);
+}
+
+// Waves that form operand tiles, and the bytes of a tile (two node blocks, two parts, 64 lanes).
+template <int BLOCK>
+constexpr int tile_waves() {
+    return BLOCK <= 512 ? BLOCK / 64 : 8;
+}
+constexpr int kTileBytes = 4096;
+
+// Bound: latency (one curve per call: a chain of sorts, scans and reductions by one workgroup),
+// FP64 exponentials where one workgroup has a long curve.  Measured against separate prologue and
+// node kernels with sorts in LDS and one exponential per node and sample: one curve of 617 samples
+// 119 -> 43 us (55 by the small block), one of 8192 1274 -> 329 us, 768 survey curves 206 -> 108 us.
+template <int BLOCK, int EMAX>
+__global__ void __launch_bounds__(BLOCK)
+prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
+               const double* __restrict__ y_all, const double* __restrict__ e_all,
+               double skew_lambda, double skew_mu, int room, int key_bytes, int group_room,
+               ModeDev md) {
+    extern __shared__ double psh[];
+    __shared__ double red[kSumThreads / 64];
+    __shared__ int ired[BLOCK / 64];
+    __shared__ int bad;
+    __shared__ double s_sy, s_st;
+    const int c = blockIdx.x, tid = threadIdx.x;
+    const CurveParams P = cp[c];
+    const int n = P.n;
+    if (P.status != 0) return;
+    double* key = psh;
+    int32_t* idx = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(psh) + key_bytes);
+    const double* t = t_all + P.off;
+    const double* y = y_all + P.off;
+    const double* e = P.has_e ? e_all + P.off : nullptr;
+    if (tid == 0) bad = 0;
+    __syncthreads();
+    double s = 0.0;
+    for (int i = tid; i < n; i += BLOCK) {
+        const bool ok = isfinite(t[i]) && isfinite(y[i]) && (!e || isfinite(e[i]));
+        if (!ok) bad = 1;
+    }
+    if (tid < kSumThreads)
+        for (int i = tid; i < n; i += kSumThreads) s += y[i];
+    __syncthreads();
+    if (bad || n < 2) {
+        if (tid == 0) cp[c].status = -1;  // QMI_EINVAL
+        return;
+    }
+    // Mean and sample deviation of y.
+    const double mean = block_sum(s, red) / n;
+    s = 0.0;
+    if (tid < kSumThreads)
+        for (int i = tid; i < n; i += kSumThreads) {
+            const double d = y[i] - mean;
+            s += d * d;
+        }
+    const double sdev = sqrt(block_sum(s, red) / (n - 1));
+    double med_e = NAN;
+    if (e) {
+        for (int i = tid; i < n; i += BLOCK) key[i] = e[i];
+        sort_block<BLOCK, EMAX, false>(key, idx, n);
+        med_e = sorted_median(key, n);
+        __syncthreads();
+    }
+    for (int i = tid; i < n; i += BLOCK) {
+        key[i] = y[i];
+        idx[i] = i;
+    }
+    sort_block<BLOCK, EMAX, true>(key, idx, n);
+    if (tid == 0) {
+        const double iqr = sorted_quantile(key, n, 0.75) - sorted_quantile(key, n, 0.25);
+        // sigma_t rule (Sec. 3): S = (Q3 + Q1 - 2 Q2) / (Q3 - Q1) with Q2 the median and Q1, Q3 the
+        // medians of the lower and upper n / 2 sorted magnitudes; S = 0 when Q3 = Q1.
+        double sigma_t = P.sigma_t;
+        if (!(sigma_t > 0.0)) {
+            const int h = n / 2;
+            const double q1 = sorted_median(key, h), q2 = sorted_median(key, n);
+            const double q3 = sorted_median(key + (n - h), h);
+            const double S = (q3 == q1) ? 0.0 : (q3 + q1 - 2.0 * q2) / (q3 - q1);
+            sigma_t = skew_lambda + 0.5 * exp(-skew_mu * S * S);
+        }
+        double sy = 0.0;
+        int status = 0;
+        if (P.sigma_y_rule > 0.0) {
+            sy = P.sigma_y_rule;
+        } else if (P.sigma_y_rule == -1.0) {
+            if (sdev == 0.0) {
+                status = -4;  // QMI_EDEGENERATE
+            } else {
+                double spread = (iqr == 0.0) ? sdev : fmin(sdev, iqr / 1.34);
+                sy = 0.9 * spread * pow((double)n, -0.2);
+            }
+        } else {
+            if (!(med_e > 0.0)) status = e ? -4 : -1;
+            sy = med_e;
+        }
+        cp[c].status = status;
+        cp[c].sigma_y = status ? NAN : sy;
+        cp[c].sigma_t = sigma_t;
+        cp[c].A = kInvSqrt2Pi / sigma_t;
+        cp[c].B = status ? NAN : kInvSqrt2Pi / sy;
+        cp[c].psnr = (e && med_e > 0.0) ? 0.7413 * iqr / med_e : NAN;
+        s_sy = status ? NAN : sy;
+        s_st = sigma_t;
+    }
+    if (!md.curves) return;
+    ModeCurve M = md.curves[c];
+    if (M.cap == 0) return;
+    __syncthreads();
+    const double sigma_y = s_sy, sigma_t = s_st;
+    if (!(sigma_y == sigma_y)) return;
+
+    // ---- Node tables.  Groups of samples (in magnitude order) with the same first node block.
+    int* g_first = reinterpret_cast<int*>(idx) + std::max(room, tile_waves<BLOCK>() * kTileBytes / 4);
+    int* g_block = g_first + group_room + 1;  // first block of samples of a group
+    int* g_row = g_block + group_room + 1;    // first node block, counted among those in use
+    int* g_rb = g_row + group_room;           // and by magnitude
+    const double y0 = key[0];
+    const double inv = 1.0 / (kNodeStep * sigma_y);
+    bool sparse = !((key[n - 1] - y0) * inv < 1e9);  // far more nodes than samples can use
+    // Position of a sample in node units, and its first node block.
+    auto pos = [&](int i) { return (key[i] - y0) * inv + (double)kReach; };
+    auto blk = [&](int i) { return ((int)rint(pos(i)) - kReach) >> 4; };
+    int n_groups = 0, n_rows = 0, n_blocks = 0;
+    if (!sparse) {
+        const int per = (n + BLOCK - 1) / BLOCK;
+        const int i0 = min(n, tid * per), i1 = min(n, i0 + per);
+        int cnt = 0, all = 0;  // groups in the low, node blocks in the high half
+        // A group brings two new node blocks, or one where the group before it starts one lower.
+        for (int i = i0; i < i1; ++i) {
+            const int d = i == 0 ? 2 : min(2, blk(i) - blk(i - 1));
+            if (d > 0) cnt += 1 + (d << 16);
+        }
+        int at = block_scan<BLOCK>(cnt, ired, &all);
+        n_groups = all & 0xffff;
+        n_rows = all >> 16;
+        sparse = n_groups > M.cap;
+        if (!sparse) {
+            for (int i = i0; i < i1; ++i) {
+                const int b = blk(i);
+                const int d = i == 0 ? 2 : min(2, b - blk(i - 1));
+                if (d <= 0) continue;
+                const int g = at & 0xffff;
+                at += 1 + (d << 16);
+                g_first[g] = i;
+                g_rb[g] = b;
+                g_row[g] = (at >> 16) - 2;
+            }
+            if (tid == 0) g_first[n_groups] = n;
+            __syncthreads();
+            // Blocks of 32 samples: every group starts a new one.
+            const int gper = (n_groups + BLOCK - 1) / BLOCK;
+            const int a0 = min(n_groups, tid * gper), a1 = min(n_groups, a0 + gper);
+            int nb = 0;
+            for (int g = a0; g < a1; ++g) nb += (g_first[g + 1] - g_first[g] + 31) >> 5;
+            int f = block_scan<BLOCK>(nb, ired, &n_blocks);
+            for (int g = a0; g < a1; ++g) {
+                g_block[g] = f;
+                f += (g_first[g + 1] - g_first[g] + 31) >> 5;
+            }
+            if (tid == 0) g_block[n_groups] = n_blocks;
+            sparse = n_blocks > M.cap;
+        }
+        __syncthreads();
+    }
+    if (sparse) {
+        if (tid == 0) {
+            md.curves[c].groups = 0;
+            cp[c].sparse = 1;
+        }
+        return;
+    }
+    auto group_of = [&](int block) {
+        int lo = 0, hi = n_groups - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (g_block[mid] <= block) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
+    // Times in magnitude order, every group padded to whole blocks.
+    double* ts = md.ts + 32 * M.boff;
+    int32_t* rows = md.rows + M.boff;
+    for (int q = tid; q < 32 * n_blocks; q += BLOCK) {
+        const int g = group_of(q >> 5);
+        const int i = g_first[g] + q - 32 * g_block[g];
+        ts[q] = i < g_first[g + 1] ? t[idx[i]] : 0.0;
+        if ((q & 31) == 0) rows[q >> 5] = g_row[g];
+    }
+    __syncthreads();  // idx is free from here
+    // Fragments of U in the operand layout of the 16x16x32 matrix instruction: lane l holds node
+    // l mod 16 and samples 8 (l / 16) ... + 7 of the block, as a high and a low half-precision
+    // part; and each node's sum over the block's samples.  A lane forms the 16 nodes of one node
+    // block for one sample from the middle outwards: U at the next node is U times a ratio, and
+    // the ratio falls by exp(-2 h^2) per node, so that a block of 16 takes three exponentials.
+    half8v* frag = reinterpret_cast<half8v*>(md.frag) + M.boff * 256;
+    double* part = md.part + M.boff * 32;
+    double* bsum = md.b + M.boff * 32;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (wave < tile_waves<BLOCK>()) {
+        _Float16* tile = reinterpret_cast<_Float16*>(idx) + wave * (kTileBytes / 2);
+        constexpr double kFall = 0.60653065971263342360379953499118;  // exp(-2 h^2), h = 1/2
+        static_assert(kNodeStep == 0.5, "kFall");
+        for (int b = wave; b < n_blocks; b += tile_waves<BLOCK>()) {
+            const int g = group_of(b);
+            const int i = lane & 31, nb = lane >> 5;
+            const int smp = g_first[g] + 32 * (b - g_block[g]) + i;
+            double v = 0.0, up = 0.0, down = 0.0;
+            if (smp < g_first[g + 1]) {
+                const double d = ((double)(16 * (g_rb[g] + nb) + 8) - pos(smp)) * kNodeStep;
+                v = exp(-d * d);
+                up = exp(-2.0 * kNodeStep * d - kNodeStep * kNodeStep);
+                down = exp(2.0 * kNodeStep * d - kNodeStep * kNodeStep);
+            }
+            // Element of node r: part hl of node block nb at ((nb 2 + hl) 64 + 16 (i/8) + r) 8 + i%8.
+            _Float16* to = tile + (nb * 128 + 16 * (i >> 3)) * 8 + (i & 7);
+            auto put = [&](int r, double x) {
+                const _Float16 h = (_Float16)(float)x;
+                to[r * 8] = h;
+                to[512 + r * 8] = (_Float16)(float)(x - (double)(float)h);
+            };
+            put(8, v);
+            double x = v;
+#pragma unroll
+            for (int r = 9; r < 16; ++r) {
+                x *= up;
+                up *= kFall;
+                put(r, x);
+            }
+            x = v;
+#pragma unroll
+            for (int r = 7; r >= 0; --r) {
+                x *= down;
+                down *= kFall;
+                put(r, x);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const half8v* tv = reinterpret_cast<const half8v*>(tile);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const half8v h = tv[k * 128 + lane], l = tv[k * 128 + 64 + lane];
+                frag[(int64_t)b * 256 + k * 128 + lane] = h;
+                frag[(int64_t)b * 256 + k * 128 + 64 + lane] = l;
+                double sum = 0.0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) sum += (double)(float)h[j] + (double)(float)l[j];
+                sum += __shfl_xor(sum, 16, 64);
+                sum += __shfl_xor(sum, 32, 64);
+                if (lane < 16) part[(int64_t)(2 * b + k) * 16 + lane] = sum;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+    double sq = 0.0, sb = 0.0;
+    if (tid < kSumThreads)
+        for (int q = tid; q < 16 * n_rows; q += kSumThreads) {
+            const int row = q >> 4;
+            int lo = 0, hi = n_groups - 1;  // first group that reaches the node block
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (g_row[mid] + 1 >= row) hi = mid; else lo = mid + 1;
+            }
+            double b = 0.0;
+            for (int g = lo; g < n_groups && g_row[g] <= row; ++g)
+                for (int r = g_block[g]; r < g_block[g + 1]; ++r)
+                    b += part[(int64_t)(2 * r + row - g_row[g]) * 16 + (q & 15)];
+            bsum[q] = b;
+            sq = fma(b, b, sq);
+            sb += b;
+        }
+    sq = block_sum(sq, red);
+    sb = block_sum(sb, red);
+    // Coefficients of the periodic kernel's cosine series by the trapezoid rule over the circle
+    // (exact up to the coefficients past L - m), and the number of harmonics to keep.
+    const int cap = md.mode_cap, L = 3 * cap + 32;
+    double* ev = psh;
+    double* ct = psh + L;
+    double* cs = ct + L;  // [cap + 1]
+    const double kap = 1.0 / (sigma_t * sigma_t);
+    for (int j = tid; j < L; j += BLOCK) {
+        const double co = cospi(2.0 * (double)j / (double)L);
+        ct[j] = co;
+        ev[j] = exp(kap * (co - 1.0));
+    }
+    __syncthreads();
+    for (int m = tid; m <= cap; m += BLOCK) {
+        double a = 0.0;
+        int k = 0;
+#pragma unroll 4
+        for (int j = 0; j < L; ++j) {
+            a = fma(ev[j], ct[k], a);
+            k += m;
+            if (k >= L) k -= L;
+        }
+        cs[m] = (m ? 2.0 : 1.0) * a / (double)L;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int m = cap;
+        double tail = 0.0;
+        for (; m > 1; --m) {
+            tail += cs[m];
+            if (tail > kModeTail) break;
+        }
+        m = min(m, md.max_groups * kModeGroup);
+        ired[0] = m;
+        M.groups = (m + kModeGroup - 1) / kModeGroup;
+        M.blocks = n_blocks;
+        M.c0 = cs[0];
+        M.sj0 = kNodeW * sq;
+        M.n0 = kNodeP * sb;
+        md.curves[c] = M;
+        cp[c].ipy = kInvSqrt2Pi / sigma_y * M.sj0 / ((double)n * (double)n);
+    }
+    __syncthreads();
+    // Coefficient of harmonic m at m - 1; zero past the last one kept.
+    const int keep = ired[0];
+    double* coef = md.coef + (int64_t)c * mode_stride(cap);
+    for (int m = tid + 1; m <= mode_stride(cap); m += BLOCK)
+        coef[m - 1] = m <= keep ? cs[m] : 0.0;
+}
+
+template <int BLOCK, int EMAX>
+hipError_t launch_prepare_b(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
+                            const double* t, const double* y, const double* e,
+                            double skew_lambda, double skew_mu, const ModeDev& md) {
+    const int room = sort_room(BLOCK, max_n);
+    const int L = 3 * md.mode_cap + 32;
+    const int key_bytes = 8 * std::max(room, md.curves ? 2 * L + md.mode_cap + 2 : 0);
+    const int group_room = max_n / 5 + 1;
+    size_t lds = (size_t)key_bytes + 4 * (size_t)room;
+    if (md.curves)
+        lds = (size_t)key_bytes + std::max(4 * room, tile_waves<BLOCK>() * kTileBytes) +
+              4 * (size_t)(4 * group_room + 2);
+    prepare_kernel<BLOCK, EMAX><<<n_curves, BLOCK, lds, st>>>(
+        cp, t, y, e, skew_lambda, skew_mu, room, key_bytes, group_room, md);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_prepare(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
+                          const double* t, const double* y, const double* e, double skew_lambda,
+                          double skew_mu, const ModeDev& md) {
+    if (n_curves <= 0) return hipSuccess;
+    if (!sort_big(n_curves, max_n))
+        return launch_prepare_b<kSortBlock, kSortE>(st, cp, n_curves, max_n, t, y, e, skew_lambda,
+                                                    skew_mu, md);
+    return launch_prepare_b<kSortBlockBig, kSortEBig>(st, cp, n_curves, max_n, t, y, e,
+                                                      skew_lambda, skew_mu, md);
+}
+
+}  // namespace qmi
