@@ -641,6 +641,11 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             tie = TieDev{dptr<int32_t>(ctx, qmi_ctx::kTieCnt),
                          dptr<int32_t>(ctx, qmi_ctx::kTieSlot),
                          dptr<double>(ctx, qmi_ctx::kTieScore), md.curves};
+        if (refine) {
+            const qmi_search* q = cs.search;
+            md.win_width = q->n_coarse > 1 ? 2.0 * (q->f_max - q->f_min) / (q->n_coarse - 1) : 0.0;
+            md.n_fine = n_fine;
+        }
         md.mode_cap = mode_cap;
         md.max_groups = mode_groups;
         HIP_OK(ctx, hipMemcpyAsync(md.curves, mc.data(), nc * sizeof(ModeCurve), h2d, st));
@@ -830,6 +835,8 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
                 if (n_modes)
                     HIP_OK(ctx, launch_modes(st, dcp, dorder, n_modes, ff, md, fm,
                                              msplit2 ? mode_groups : 0));
+                if (md.win_width > 0.0)
+                    HIP_OK(ctx, launch_mode_windows(st, dcp, nc, ff, md, fm));
                 HIP_OK(ctx, launch_pairs<R>(st, dcp, dorder + n_modes, n_pairs, ff, t, K, rd, rp,
                                             ks, fo, variant, split2 ? max_pieces : 0));
                 rec();

@@ -102,7 +102,8 @@ struct ModeCurve {
     int32_t cap;    // blocks there is room for; 0: the curve is left to the pair sums
     int32_t blocks; // blocks in use
     int32_t groups; // passes over the samples; 0: left to the pair sums
-    int32_t pad;
+    int32_t nodes;  // frequencies per refinement window whose sums the window's points are
+                    // interpolated from; 0: every point is summed
     double c0;      // coefficient of the constant term
     double sj0;     // w sum_q b_q^2
     double n0;      // p sum_q b_q
@@ -118,7 +119,15 @@ struct ModeDev {
     double* coef;      // [curve][mode_stride(mode_cap)]
     int32_t mode_cap;  // coefficients there is room for (past the harmonics kept)
     int32_t max_groups; // most groups of harmonics of any curve
+    double win_width;  // width of a refinement window (0: no refinement)
+    int32_t n_fine;    // its points
+    int32_t pad;
 };
+// Interpolated refinement windows (mode_window_kernel): most frequencies per window, and the error
+// allowed, as a share of the periodic kernel's value where phases coincide.
+constexpr int kWinNodesMax = 512;
+constexpr double kWinTol = 1e-10;
+
 
 // Interleaved partial sums of a column's terms over a wave's rows (row m goes to partial
 // m mod kPartials), combined at the end of the column: the pair kernel and the column-sum tables
@@ -287,6 +296,10 @@ hipError_t launch_pairs_rows(hipStream_t st, const CurveParams* cp, const int32_
 hipError_t launch_modes(hipStream_t st, const CurveParams* cp, const int32_t* order,
                         int n_work_curves, const FreqPlan& fp, const ModeDev& md,
                         const PairOut& out, int split_groups);
+// The refinement windows of the curves with nodes > 0: every point's scores from the node sums that
+// launch_modes left in out.score and out.score2.
+hipError_t launch_mode_windows(hipStream_t st, const CurveParams* cp, int n_curves,
+                               const FreqPlan& fp, const ModeDev& md, const PairOut& out);
 hipError_t launch_peaks(hipStream_t st, const CurveParams* cp, int n_curves, const double* coarse,
                         int n_coarse, double f0, double df, int top_k, int n_fine,
                         const MaskDev& md, const PeakOut& po);

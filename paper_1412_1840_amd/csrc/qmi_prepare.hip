@@ -85,6 +85,7 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
     __shared__ int ired[BLOCK / 64];
     __shared__ int bad;
     __shared__ double s_sy, s_st;
+    __shared__ double s_lo[BLOCK / 64], s_hi[BLOCK / 64];
     const int c = blockIdx.x, tid = threadIdx.x;
     const CurveParams P = cp[c];
     const int n = P.n;
@@ -96,10 +97,21 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
     const double* e = P.has_e ? e_all + P.off : nullptr;
     if (tid == 0) bad = 0;
     __syncthreads();
-    double s = 0.0;
+    double s = 0.0, t_lo = INFINITY, t_hi = -INFINITY;
     for (int i = tid; i < n; i += BLOCK) {
-        const bool ok = isfinite(t[i]) && isfinite(y[i]) && (!e || isfinite(e[i]));
+        const double ti = t[i];
+        const bool ok = isfinite(ti) && isfinite(y[i]) && (!e || isfinite(e[i]));
         if (!ok) bad = 1;
+        t_lo = fmin(t_lo, ti);
+        t_hi = fmax(t_hi, ti);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        t_lo = fmin(t_lo, __shfl_xor(t_lo, o, 64));
+        t_hi = fmax(t_hi, __shfl_xor(t_hi, o, 64));
+    }
+    if ((tid & 63) == 0) {
+        s_lo[tid >> 6] = t_lo;
+        s_hi[tid >> 6] = t_hi;
     }
     if (tid < kSumThreads)
         for (int i = tid; i < n; i += kSumThreads) s += y[i];
@@ -359,6 +371,29 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
         }
         cs[m] = (m ? 2.0 : 1.0) * a / (double)L;
     }
+    // Frequencies per refinement window.  Harmonic m of the sums runs through at most
+    // w = pi m T W (T the curve's time span, W the window) radians from the window's middle to its
+    // end, and its Chebyshev coefficients fall below eps past the degree
+    // w + s (w/2)^(1/3) + 0.12 s^2 / (w/2)^(1/3), s = (3/2 ln(2/eps))^(2/3) (the Bessel functions
+    // J_d(w) past their turning point; checked against them for w in [0.01, 600], eps in
+    // [1e-11, 0.1]: never short, at most a tenth over from w = 10 on).
+    if (tid == 0) ired[1] = 0;
+    __syncthreads();
+    if (md.win_width > 0.0) {
+        double lo = s_lo[0], hi = s_hi[0];
+        for (int k = 1; k < BLOCK / 64; ++k) {
+            lo = fmin(lo, s_lo[k]);
+            hi = fmax(hi, s_hi[k]);
+        }
+        for (int m = tid; m <= cap; m += BLOCK) {
+            if (m == 0 || cs[m] <= kWinTol) continue;
+            const double w = M_PI * m * (hi - lo) * md.win_width;
+            const double q = 1.5 * log(2.0 * cs[m] / kWinTol);
+            const double r = cbrt(q), h = fmax(cbrt(0.5 * w), 0.6);
+            const double d = w + r * r * cbrt(0.5 * w) + 0.12 * r * r * r * r / h;
+            atomicMax(&ired[1], d < 1e6 ? (int)d + 2 : 1000000);
+        }
+    }
     __syncthreads();
     if (tid == 0) {
         int m = cap;
@@ -371,6 +406,9 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
         ired[0] = m;
         M.groups = (m + kModeGroup - 1) / kModeGroup;
         M.blocks = n_blocks;
+        // Windows are interpolated where that takes at most half of their points (whose score
+        // arrays hold the node sums meanwhile).
+        M.nodes = (ired[1] > 0 && ired[1] <= kWinNodesMax && 2 * ired[1] <= md.n_fine) ? ired[1] : 0;
         M.c0 = cs[0];
         M.sj0 = kNodeW * sq;
         M.n0 = kNodeP * sb;

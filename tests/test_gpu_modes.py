@@ -143,3 +143,40 @@ def test_near_ties_are_decided_in_fp64(ctx, score, n, count, n_fine):
     # Two points of the FP64 mode itself are apart by its own rounding, 1e-13.
     assert not far, [(k, mixed["fine_index"][k], ref["fine_index"][k]) for k in far]
     np.testing.assert_allclose(mixed["score"], ref["score"], rtol=QMI_TOL)
+
+
+@pytest.mark.parametrize("score", [qmi.SCORE_QMI, qmi.SCORE_NCKP])
+@pytest.mark.parametrize("sigma_t,n,n_coarse,n_fine,top_k", [
+    (0.3, 97, 4000, 1000, 10),  # about 200 frequencies per window
+    (0.3, 617, 4000, 401, 3),  # just enough points to interpolate, and just too few
+    (0.3, 617, 4000, 380, 3),
+    (0.3, 130, 50000, 41, 10),  # narrow windows, small odd series
+    (0.6, 90, 300000, 24, 2),
+    (2.0, 64, 2000, 2001, 1),
+    (0.1, 400, 4000, 1300, 4),  # 9 groups, about 500 frequencies: both launch forms below
+    (0.1, 400, 400, 1000, 2),  # windows too wide: every point is summed
+])
+def test_interpolated_windows(ctx, sigma_t, n, n_coarse, n_fine, top_k, score):
+    """Refined records where the windows' sums are interpolated, against the search in double
+    precision, alone and in a batch (the other launch form).  A truncated series is off by at most
+    2e-10 of a kernel value per harmonic, far below the sums' own errors: 2e-7 of QMI and of the
+    potentials, the bound by which points close to the best are told apart."""
+    curves = [synth.survey_batch_curve(500 + k, n=n - (k % 3)) for k in range(40)]
+    b = synth.pack(curves)
+    kw = dict(f_min=1e-3, f_max=8.0, n_coarse=n_coarse, top_k=top_k, n_fine=n_fine, score=score)
+    few = slice(0, int(b.offsets[3]))
+    one, _ = ctx.best_period(b.offsets[:4], b.t[few], b.y[few], b.e[few], sigma_t, **kw)
+    ref, _ = ctx.best_period(b.offsets[:4], b.t[few], b.y[few], b.e[few], sigma_t,
+                             precision=qmi.PREC_FP64, **kw)
+    many, _ = ctx.best_period(b.offsets, b.t, b.y, b.e, sigma_t, **kw)
+    for r in (one, many):
+        for k in range(3):
+            for s in ("score_qmi", "score_nckp"):
+                tol = 2e-7
+                if s == "score_nckp":
+                    tol *= abs(ref[s][k]) + 2 / np.sqrt(2 * np.pi) * np.sqrt(curves[k].n / sigma_t)
+                assert abs(r[s][k] - ref[s][k]) <= tol, (k, s, r[s][k] - ref[s][k])
+            assert r["coarse_index"][k] == ref["coarse_index"][k]
+            assert abs(r["f_best"][k] - ref["f_best"][k]) <= 1e-12 * ref["f_best"][k]
+    for name in ("f_best", "score", "fine_index"):
+        np.testing.assert_array_equal(one[name], many[name][:3])
