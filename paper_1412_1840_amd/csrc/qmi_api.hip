@@ -825,7 +825,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         } else if (!cs.periodogram) {
             const qmi_search* s = cs.search;
             HIP_OK(ctx, launch_peaks(st, dcp, nc, coarse, s->n_coarse, fp.f0, fp.df, top_k,
-                                     std::max(n_fine, 2), ctx->masks, pk));
+                                     std::max(n_fine, 2), ctx->masks, pk, fine, F2));
             if (refine) {
                 PairOut fo{fine, fine2, nullptr, score_kind, 0, split2 ? dpart : nullptr};
                 if (events) pair_event_idx.push_back(ctx->ev_used);

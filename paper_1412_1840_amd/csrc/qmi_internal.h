@@ -300,9 +300,11 @@ hipError_t launch_modes(hipStream_t st, const CurveParams* cp, const int32_t* or
 // launch_modes left in out.score and out.score2.
 hipError_t launch_mode_windows(hipStream_t st, const CurveParams* cp, int n_curves,
                                const FreqPlan& fp, const ModeDev& md, const PairOut& out);
+// parts: nullable scratch of a split scan, parts_stride doubles per curve.
 hipError_t launch_peaks(hipStream_t st, const CurveParams* cp, int n_curves, const double* coarse,
                         int n_coarse, double f0, double df, int top_k, int n_fine,
-                        const MaskDev& md, const PeakOut& po);
+                        const MaskDev& md, const PeakOut& po, double* parts,
+                        int64_t parts_stride);
 hipError_t launch_best(hipStream_t st, const CurveParams* cp, int n_curves, const double* coarse,
                        const double* coarse2, int n_coarse, const double* fine,
                        const double* fine2, int top_k, int n_fine, int score_kind, double f0,
