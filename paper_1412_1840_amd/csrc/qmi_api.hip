@@ -20,6 +20,7 @@
 
 #include "../../include/qmi.h"
 #include "qmi_internal.h"
+#include "qmi_stage.h"
 
 using namespace qmi;
 
@@ -54,15 +55,15 @@ struct qmi_ctx {
     int ev_used = 0;
     // Device buffers, grown on demand.
     enum {
-        kT, kY, kE, kCP, kOrder, kRowStart, kK, kR, kRP, kRD, kKS, kCoarse, kCoarse2, kFine, kFine2,
-        kIps, kPeakK, kNpk, kWin, kArgmax, kRes, kFreqs, kProbe, kTS, kYS, kBandT, kBandCnt,
-        kBandId, kS, kTrials, kTrialK, kPOff, kPStIn, kPCnt, kPSt, kPDet, kPTo, kPYo, kPEo,
-        kPPer, kPart, kModeC, kModeTs, kModeRows, kModeFrag, kModePart, kModeB, kModeCoef, kTieCnt, kTieSlot,
-        kTieScore, kNumBufs
+        kUp, kK, kR, kRP, kRD, kKS, kCoarse, kCoarse2, kFine, kFine2, kIps, kPeakK, kNpk, kWin,
+        kArgmax, kRes, kProbe, kTS, kYS, kBandT, kBandCnt, kBandId, kS, kTrials, kTrialK, kPCnt,
+        kPSt, kPDet, kPTo, kPYo, kPEo, kPart, kModeTs, kModeRows, kModeFrag, kModePart, kModeB,
+        kModeCoef, kTieCnt, kTieSlot, kTieScore, kNumBufs
     };
     Buf bufs[kNumBufs];
     static_assert(kNumBufs <= 64, "one bit per buffer in in_use");
     uint64_t in_use = 0;  // bit per buffer ensured by the current operation
+    Stage stage;          // page-locked memory of the host copies
     // Scratch mode (qmi_periodogram_noalloc): the current call takes its buffers from the
     // device's static scratch array by bump allocation instead of from bufs.
     char* ws_base = nullptr;
@@ -280,16 +281,41 @@ int check_batch(qmi_ctx* ctx, const qmi_batch* b, bool need_e) {
 }
 
 // Host-side per-curve status from the lengths (and, for host arrays, the sample values).
+bool all_finite(const double* x, int64_t n) {
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;  // x 0 is 0, or NaN for an infinity or a NaN
+    int64_t i = 0;
+    for (; i + 4 <= n; i += 4) {
+        s0 += x[i] * 0.0;
+        s1 += x[i + 1] * 0.0;
+        s2 += x[i + 2] * 0.0;
+        s3 += x[i + 3] * 0.0;
+    }
+    for (; i < n; ++i) s0 += x[i] * 0.0;
+    return (s0 + s1) + (s2 + s3) == 0.0;
+}
+
 int32_t host_curve_status(const qmi_batch* b, int32_t k, bool host_arrays) {
     const int64_t a = b->offsets[k], n = b->offsets[k + 1] - a;
     if (n < 2 || n > QMI_MAX_N) return QMI_EINVAL;
-    if (host_arrays) {
-        for (int64_t i = a; i < a + n; ++i) {
-            if (!std::isfinite(b->t[i]) || !std::isfinite(b->y[i])) return QMI_EINVAL;
-            if (b->e && !std::isfinite(b->e[i])) return QMI_EINVAL;
-        }
-    }
+    if (host_arrays && !(all_finite(b->t + a, n) && all_finite(b->y + a, n) &&
+                         (!b->e || all_finite(b->e + a, n))))
+        return QMI_EINVAL;
     return QMI_OK;
+}
+
+// status(k) of curves [c0, c1) with about `samples` samples in all, into out[k - c0].
+template <typename F>
+void curve_statuses(int32_t c0, int32_t c1, int64_t samples, int32_t* out, const F& status) {
+    constexpr int32_t kGrain = 32;
+    const int64_t parts = (c1 - c0 + kGrain - 1) / kGrain;
+    auto part = [&](int64_t q) {
+        const int32_t lo = c0 + (int32_t)q * kGrain, hi = std::min(c1, lo + kGrain);
+        for (int32_t k = lo; k < hi; ++k) out[k - c0] = status(k);
+    };
+    if ((size_t)samples * 8 >= kTeamBytes)
+        run_team(parts, part);
+    else
+        for (int64_t q = 0; q < parts; ++q) part(q);
 }
 
 // A contiguous group of curves [c0, c1) processed by one device section.
@@ -455,12 +481,15 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     const int mode_cap = mode_groups * kModeGroup + 8;
     constexpr int kPassR = kWaves * rows_per_wave<R>();
     int max_n = 2, max_pieces = 0;
+    std::vector<int32_t> status(nc);
+    curve_statuses(g.c0, g.c1, cs.dev_inputs ? 0 : ns, status.data(),
+                   [&](int32_t k) { return host_curve_status(b, k, !cs.dev_inputs); });
     for (int32_t i = 0; i < nc; ++i) {
         const int32_t k = g.c0 + i;
         const int64_t a = b->offsets[k], n = b->offsets[k + 1] - a;
         CurveParams& p = cp[i];
         std::memset(&p, 0, sizeof(p));
-        p.status = host_curve_status(b, k, !cs.dev_inputs);
+        p.status = status[i];
         p.off = a - g.s0;
         p.n = (int32_t)std::min<int64_t>(n, QMI_MAX_N);
         p.has_e = b->e != nullptr;
@@ -532,14 +561,20 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     }
 #define ENSURE(id, bytes) \
     if ((rc = acquire(ctx, id, (bytes))) != QMI_OK) return rc
+    // What the host hands over, in one buffer and one copy.
+    Upload up;
+    const size_t at_cp = up.add(cp.data(), nc * sizeof(CurveParams));
+    const size_t at_order = up.add(order.data(), nc * sizeof(int32_t));
+    const size_t at_row = up.add(row_start.data(), nc * sizeof(int64_t));
+    const size_t at_mc = n_modes ? up.add(mc.data(), nc * sizeof(ModeCurve)) : 0;
+    size_t at_f = 0, at_t = 0, at_y = 0, at_e = 0;
     if (!cs.dev_inputs) {
-        ENSURE(qmi_ctx::kT, ns * 8);
-        ENSURE(qmi_ctx::kY, ns * 8);
-        if (b->e) ENSURE(qmi_ctx::kE, ns * 8);
+        if (cs.periodogram) at_f = up.add(cs.freqs, F1 * 8);
+        at_t = up.add(b->t + g.s0, ns * 8);
+        at_y = up.add(b->y + g.s0, ns * 8);
+        if (b->e) at_e = up.add(b->e + g.s0, ns * 8);
     }
-    ENSURE(qmi_ctx::kCP, nc * sizeof(CurveParams));
-    ENSURE(qmi_ctx::kOrder, nc * sizeof(int32_t));
-    ENSURE(qmi_ctx::kRowStart, nc * sizeof(int64_t));
+    ENSURE(qmi_ctx::kUp, up.total);
     if (n_pairs) {
         ENSURE(qmi_ctx::kK, std::max<int64_t>(koff, 1) * sizeof(R));
         ENSURE(qmi_ctx::kRP, std::max<int64_t>(poff, 1) * 8);
@@ -547,7 +582,6 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         ENSURE(qmi_ctx::kKS, std::max<int64_t>(ksoff, 1) * sizeof(R));
     }
     if (n_modes) {
-        ENSURE(qmi_ctx::kModeC, nc * sizeof(ModeCurve));
         ENSURE(qmi_ctx::kModeTs, mblocks * 256);
         ENSURE(qmi_ctx::kModeRows, mblocks * 4);
         ENSURE(qmi_ctx::kModeFrag, mblocks * 4096);
@@ -586,7 +620,6 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         ENSURE(qmi_ctx::kArgmax, nc * sizeof(int32_t));
         ENSURE(qmi_ctx::kRes, nc * sizeof(DevResult));
     }
-    if (cs.periodogram && !cs.dev_inputs) ENSURE(qmi_ctx::kFreqs, F1 * 8);
 #undef ENSURE
     // A launch with fewer (curve, 64-frequency tile) items than this cannot fill the chip's 512
     // workgroup slots several times over; it runs one (pass, column segment) piece per workgroup
@@ -609,28 +642,21 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     double* dpart = (split1 || split2 || msplit1 || msplit2) ? dptr<double>(ctx, qmi_ctx::kPart) : nullptr;
 
     hipStream_t st = ctx->stream;
-    const double* t = cs.dev_inputs ? b->t + g.s0 : dptr<double>(ctx, qmi_ctx::kT);
-    const double* y = cs.dev_inputs ? b->y + g.s0 : dptr<double>(ctx, qmi_ctx::kY);
-    const double* e = b->e ? (cs.dev_inputs ? b->e + g.s0 : dptr<double>(ctx, qmi_ctx::kE))
-                           : nullptr;
-    if (!cs.dev_inputs) {
-        HIP_OK(ctx, hipMemcpyAsync((void*)t, b->t + g.s0, ns * 8, hipMemcpyHostToDevice, st));
-        HIP_OK(ctx, hipMemcpyAsync((void*)y, b->y + g.s0, ns * 8, hipMemcpyHostToDevice, st));
-        if (e)
-            HIP_OK(ctx, hipMemcpyAsync((void*)e, b->e + g.s0, ns * 8, hipMemcpyHostToDevice, st));
-    }
-    CurveParams* dcp = dptr<CurveParams>(ctx, qmi_ctx::kCP);
-    int32_t* dorder = dptr<int32_t>(ctx, qmi_ctx::kOrder);
-    int64_t* drow = dptr<int64_t>(ctx, qmi_ctx::kRowStart);
-    const hipMemcpyKind h2d = hipMemcpyHostToDevice;
-    HIP_OK(ctx, hipMemcpyAsync(dcp, cp.data(), nc * sizeof(CurveParams), h2d, st));
-    HIP_OK(ctx, hipMemcpyAsync(dorder, order.data(), nc * sizeof(int32_t), h2d, st));
-    if (n_pairs)
-        HIP_OK(ctx, hipMemcpyAsync(drow, row_start.data(), nc * sizeof(int64_t), h2d, st));
+    char* dup = dptr<char>(ctx, qmi_ctx::kUp);
+    auto in = [&](const double* dev, size_t at) {
+        return cs.dev_inputs ? dev + g.s0 : reinterpret_cast<const double*>(dup + at);
+    };
+    const double* t = in(b->t, at_t);
+    const double* y = in(b->y, at_y);
+    const double* e = b->e ? in(b->e, at_e) : nullptr;
+    CurveParams* dcp = reinterpret_cast<CurveParams*>(dup + at_cp);
+    int32_t* dorder = reinterpret_cast<int32_t*>(dup + at_order);
+    int64_t* drow = reinterpret_cast<int64_t*>(dup + at_row);
+    HIP_OK(ctx, upload(ctx->stage, up, dup, ctx->device, st, !ctx->ws_base));
     ModeDev md{};
     TieDev tie{};
     if (n_modes) {
-        md.curves = dptr<ModeCurve>(ctx, qmi_ctx::kModeC);
+        md.curves = reinterpret_cast<ModeCurve*>(dup + at_mc);
         md.ts = dptr<double>(ctx, qmi_ctx::kModeTs);
         md.rows = dptr<int32_t>(ctx, qmi_ctx::kModeRows);
         md.frag = dptr<char>(ctx, qmi_ctx::kModeFrag);
@@ -648,17 +674,10 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         }
         md.mode_cap = mode_cap;
         md.max_groups = mode_groups;
-        HIP_OK(ctx, hipMemcpyAsync(md.curves, mc.data(), nc * sizeof(ModeCurve), h2d, st));
     }
     const double* dfreqs = nullptr;
-    if (cs.periodogram) {
-        if (cs.dev_inputs) {
-            dfreqs = cs.freqs;
-        } else {
-            dfreqs = dptr<double>(ctx, qmi_ctx::kFreqs);
-            HIP_OK(ctx, hipMemcpyAsync((void*)dfreqs, cs.freqs, F1 * 8, hipMemcpyHostToDevice, st));
-        }
-    }
+    if (cs.periodogram)
+        dfreqs = cs.dev_inputs ? cs.freqs : reinterpret_cast<const double*>(dup + at_f);
 
     R* K = n_pairs ? dptr<R>(ctx, qmi_ctx::kK) : nullptr;
     double* rp = n_pairs ? dptr<double>(ctx, qmi_ctx::kRP) : nullptr;
@@ -931,17 +950,14 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
 
     // Results back to the caller.
     if (cs.periodogram) {
-        if (!cs.dev_outputs) {
-            HIP_OK(ctx, hipMemcpyAsync(cs.score_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8,
-                                       hipMemcpyDeviceToHost, st));
-            if (cs.ips_out)
-                HIP_OK(ctx, hipMemcpyAsync(cs.ips_out + (int64_t)g.c0 * F1 * 3, po.ips,
-                                           nc * F1 * 24, hipMemcpyDeviceToHost, st));
-        }
         std::vector<CurveParams> cpo(nc);
-        HIP_OK(ctx, hipMemcpyAsync(cpo.data(), dcp, nc * sizeof(CurveParams),
-                                   hipMemcpyDeviceToHost, st));
-        HIP_OK(ctx, hipStreamSynchronize(st));
+        Download dn;
+        dn.add(cpo.data(), dcp, nc * sizeof(CurveParams));
+        if (!cs.dev_outputs) {
+            dn.add(cs.score_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8);
+            if (cs.ips_out) dn.add(cs.ips_out + (int64_t)g.c0 * F1 * 3, po.ips, nc * F1 * 24);
+        }
+        HIP_OK(ctx, download(ctx->stage, dn, st, !ctx->ws_base));
         for (int32_t i = 0; i < nc; ++i)
             if (cpo[i].status == QMI_OK && cpo[i].sparse) left->push_back(g.c0 + i);
         for (int32_t i = 0; i < nc; ++i) {
@@ -962,23 +978,20 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         }
     } else {
         static_assert(sizeof(DevResult) == sizeof(qmi_result), "result layout");
-        HIP_OK(ctx, hipMemcpyAsync(cs.out + g.c0, dptr<DevResult>(ctx, qmi_ctx::kRes),
-                                   nc * sizeof(DevResult), hipMemcpyDeviceToHost, st));
+        Download dn;
+        dn.add(cs.out + g.c0, dres, nc * sizeof(DevResult));
         if (cs.coarse_out) {
             if (cs.dev_outputs)
                 HIP_OK(ctx, hipMemcpyAsync(cs.coarse_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8,
                                            hipMemcpyDeviceToDevice, st));
             else
-                HIP_OK(ctx, hipMemcpyAsync(cs.coarse_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8,
-                                           hipMemcpyDeviceToHost, st));
+                dn.add(cs.coarse_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8);
         }
         if (bp && cs.trials_out)
-            HIP_OK(ctx, hipMemcpyAsync(cs.trials_out + (int64_t)g.c0 * F1, bd.trials,
-                                       nc * F1 * 8, hipMemcpyDeviceToHost, st));
+            dn.add(cs.trials_out + (int64_t)g.c0 * F1, bd.trials, nc * F1 * 8);
         if (bp && cs.scores_out)
-            HIP_OK(ctx, hipMemcpyAsync(cs.scores_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8,
-                                       hipMemcpyDeviceToHost, st));
-        HIP_OK(ctx, hipStreamSynchronize(st));
+            dn.add(cs.scores_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8);
+        HIP_OK(ctx, download(ctx->stage, dn, st, !ctx->ws_base));
         if (bp && (cs.trials_out || cs.scores_out)) {
             // Empty trial slots are never scored: report them as NaN in both outputs.
             std::vector<double> tr;
@@ -1330,6 +1343,7 @@ int qmi_create(qmi_ctx** out, int hip_device, size_t hbm_budget_bytes, void* hip
         return QMI_EDEVICE;
     }
     ctx->budget = hbm_budget_bytes ? hbm_budget_bytes : (size_t)(0.8 * (double)free_b);
+    (void)ctx->stage.grow(kStageMin, ctx->stream);  // (without it: pageable copies)
     *out = ctx.release();
     return QMI_OK;
 }
@@ -1343,6 +1357,7 @@ void qmi_destroy(qmi_ctx* ctx) {
     if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
     for (auto& b : ctx->bufs)
         if (b.p) (void)hipFree(b.p);
+    ctx->stage.release();
     for (hipEvent_t e : ctx->ev) (void)hipEventDestroy(e);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
@@ -1523,35 +1538,34 @@ int qmi_bands_best_period(qmi_ctx* ctx, const qmi_batch* batch, const qmi_kernel
 
 namespace {
 
-// Uploads a host batch (arrays, offsets) and the per-curve host statuses; returns max N of the
-// valid curves through *max_n.
+// A host batch on the device: arrays, offsets, the per-curve host statuses and, for whitening, the
+// periods.
+struct BatchDev {
+    const int64_t* offsets;
+    const double *t, *y, *e, *periods;
+    const int32_t* status;
+    int max_n;  // longest valid curve
+};
 int upload_batch(qmi_ctx* ctx, const qmi_batch* b, const std::vector<int32_t>& status,
-                 int* max_n) {
+                 const double* periods, BatchDev* out) {
     const int32_t nc = b->n_curves;
     const int64_t ns = b->offsets[nc];
-    int rc;
-    if ((rc = ensure(ctx, qmi_ctx::kT, std::max<int64_t>(ns, 1) * 8)) != QMI_OK) return rc;
-    if ((rc = ensure(ctx, qmi_ctx::kY, std::max<int64_t>(ns, 1) * 8)) != QMI_OK) return rc;
-    if (b->e && (rc = ensure(ctx, qmi_ctx::kE, std::max<int64_t>(ns, 1) * 8)) != QMI_OK) return rc;
-    if ((rc = ensure(ctx, qmi_ctx::kPOff, (nc + 1) * 8)) != QMI_OK) return rc;
-    if ((rc = ensure(ctx, qmi_ctx::kPStIn, nc * 4)) != QMI_OK) return rc;
-    hipStream_t st = ctx->stream;
-    HIP_OK(ctx, hipMemcpyAsync(dptr<double>(ctx, qmi_ctx::kT), b->t, ns * 8,
-                               hipMemcpyHostToDevice, st));
-    HIP_OK(ctx, hipMemcpyAsync(dptr<double>(ctx, qmi_ctx::kY), b->y, ns * 8,
-                               hipMemcpyHostToDevice, st));
-    if (b->e)
-        HIP_OK(ctx, hipMemcpyAsync(dptr<double>(ctx, qmi_ctx::kE), b->e, ns * 8,
-                                   hipMemcpyHostToDevice, st));
-    HIP_OK(ctx, hipMemcpyAsync(dptr<int64_t>(ctx, qmi_ctx::kPOff), b->offsets, (nc + 1) * 8,
-                               hipMemcpyHostToDevice, st));
-    HIP_OK(ctx, hipMemcpyAsync(dptr<int32_t>(ctx, qmi_ctx::kPStIn), status.data(), nc * 4,
-                               hipMemcpyHostToDevice, st));
-    int mx = 1;
+    Upload up;
+    const size_t at_off = up.add(b->offsets, (nc + 1) * 8), at_st = up.add(status.data(), nc * 4);
+    const size_t at_p = periods ? up.add(periods, nc * 8) : 0;
+    const size_t at_t = up.add(b->t, ns * 8), at_y = up.add(b->y, ns * 8);
+    const size_t at_e = b->e ? up.add(b->e, ns * 8) : 0;
+    const int rc = ensure(ctx, qmi_ctx::kUp, up.total);
+    if (rc != QMI_OK) return rc;
+    char* d = dptr<char>(ctx, qmi_ctx::kUp);
+    HIP_OK(ctx, upload(ctx->stage, up, d, ctx->device, ctx->stream, true));
+    auto array = [&](size_t at) { return reinterpret_cast<const double*>(d + at); };
+    *out = BatchDev{reinterpret_cast<const int64_t*>(d + at_off), array(at_t), array(at_y),
+                    b->e ? array(at_e) : nullptr, periods ? array(at_p) : nullptr,
+                    reinterpret_cast<const int32_t*>(d + at_st), 1};
     for (int32_t k = 0; k < nc; ++k)
         if (status[k] == QMI_OK)
-            mx = std::max<int>(mx, (int)(b->offsets[k + 1] - b->offsets[k]));
-    *max_n = mx;
+            out->max_n = std::max<int>(out->max_n, (int)(b->offsets[k + 1] - b->offsets[k]));
     return QMI_OK;
 }
 
@@ -1579,16 +1593,19 @@ int preprocess_call(qmi_ctx* ctx, const qmi_batch* b, const qmi_preprocess_param
     if (nc == 0) return QMI_OK;
     const int64_t ns = b->offsets[nc];
     std::vector<int32_t> st_in(nc);
-    for (int32_t k = 0; k < nc; ++k) {
-        st_in[k] = host_curve_status(b, k, true);
-        if (st_in[k] == QMI_OK && pp->detrend)
-            for (int64_t i = b->offsets[k]; i < b->offsets[k + 1]; ++i)
-                if (!(b->e[i] > 0.0)) st_in[k] = QMI_EINVAL;  // chi^2 weights need e > 0
-    }
+    curve_statuses(0, nc, ns, st_in.data(), [&](int32_t k) {
+        int32_t st = host_curve_status(b, k, true);
+        if (st == QMI_OK && pp->detrend) {  // chi^2 weights need e > 0
+            bool good = true;
+            for (int64_t i = b->offsets[k]; i < b->offsets[k + 1]; ++i) good &= b->e[i] > 0.0;
+            if (!good) st = QMI_EINVAL;
+        }
+        return st;
+    });
     HIP_OK(ctx, hipSetDevice(ctx->device));
     begin_use(ctx);
-    int max_n = 0;
-    if ((rc = upload_batch(ctx, b, st_in, &max_n)) != QMI_OK) return rc;
+    BatchDev bd{};
+    if ((rc = upload_batch(ctx, b, st_in, nullptr, &bd)) != QMI_OK) return rc;
     const int ids[] = {qmi_ctx::kPTo, qmi_ctx::kPYo, qmi_ctx::kPEo};
     for (int id : ids)
         if ((rc = ensure(ctx, id, std::max<int64_t>(ns, 1) * 8)) != QMI_OK) return rc;
@@ -1599,7 +1616,7 @@ int preprocess_call(qmi_ctx* ctx, const qmi_batch* b, const qmi_preprocess_param
     pd.error_cut = pp->error_cut ? 1 : 0;
     pd.detrend = pp->detrend ? 1 : 0;
     pd.min_samples = pp->min_samples;
-    pd.status_in = dptr<int32_t>(ctx, qmi_ctx::kPStIn);
+    pd.status_in = bd.status;
     pd.counts = dptr<int32_t>(ctx, qmi_ctx::kPCnt);
     pd.status = dptr<int32_t>(ctx, qmi_ctx::kPSt);
     pd.detrended = dptr<uint8_t>(ctx, qmi_ctx::kPDet);
@@ -1607,33 +1624,40 @@ int preprocess_call(qmi_ctx* ctx, const qmi_batch* b, const qmi_preprocess_param
     pd.y_out = dptr<double>(ctx, qmi_ctx::kPYo);
     pd.e_out = dptr<double>(ctx, qmi_ctx::kPEo);
     hipStream_t st = ctx->stream;
-    HIP_OK(ctx, launch_prep(st, nc, dptr<int64_t>(ctx, qmi_ctx::kPOff),
-                            dptr<double>(ctx, qmi_ctx::kT), dptr<double>(ctx, qmi_ctx::kY),
-                            b->e ? dptr<double>(ctx, qmi_ctx::kE) : nullptr, pd));
+    HIP_OK(ctx, launch_prep(st, nc, bd.offsets, bd.t, bd.y, bd.e, pd));
     std::vector<int32_t> cnt(nc), stt(nc);
     std::vector<uint8_t> det(nc);
-    std::vector<double> ht(ns), hy(ns), he(b->e ? ns : 0);
-    HIP_OK(ctx, hipMemcpyAsync(cnt.data(), pd.counts, nc * 4, hipMemcpyDeviceToHost, st));
-    HIP_OK(ctx, hipMemcpyAsync(stt.data(), pd.status, nc * 4, hipMemcpyDeviceToHost, st));
-    HIP_OK(ctx, hipMemcpyAsync(det.data(), pd.detrended, nc, hipMemcpyDeviceToHost, st));
-    HIP_OK(ctx, hipMemcpyAsync(ht.data(), pd.t_out, ns * 8, hipMemcpyDeviceToHost, st));
-    HIP_OK(ctx, hipMemcpyAsync(hy.data(), pd.y_out, ns * 8, hipMemcpyDeviceToHost, st));
-    if (b->e)
-        HIP_OK(ctx, hipMemcpyAsync(he.data(), pd.e_out, ns * 8, hipMemcpyDeviceToHost, st));
-    HIP_OK(ctx, hipStreamSynchronize(st));
-    // Dense output: each accepted curve's kept samples; rejected curves keep none.
-    int64_t o = 0;
+    Download small;
+    small.add(cnt.data(), pd.counts, nc * 4);
+    small.add(stt.data(), pd.status, nc * 4);
+    small.add(det.data(), pd.detrended, nc);
+    HIP_OK(ctx, download(ctx->stage, small, st, true));
     for (int32_t k = 0; k < nc; ++k) {
-        const int64_t a = b->offsets[k];
-        const int64_t m = stt[k] == QMI_OK ? cnt[k] : 0;
-        std::memcpy(t_out + o, ht.data() + a, m * 8);
-        std::memcpy(y_out + o, hy.data() + a, m * 8);
-        if (b->e) std::memcpy(e_out + o, he.data() + a, m * 8);
-        o += m;
-        offsets_out[k + 1] = o;
+        offsets_out[k + 1] = offsets_out[k] + (stt[k] == QMI_OK ? cnt[k] : 0);
         if (status_out) status_out[k] = stt[k];
         if (detrended_out) detrended_out[k] = det[k];
     }
+    // Dense output: each accepted curve's kept samples (the first of its span); rejected curves
+    // keep none.
+    const int64_t* off = b->offsets;
+    auto dense = [off, nc, offsets_out](double* to) {
+        return [=](const char* from, size_t at, size_t len) {
+            const int64_t lo = (int64_t)(at / 8), hi = lo + (int64_t)(len / 8);
+            int32_t k = (int32_t)(std::upper_bound(off, off + nc + 1, lo) - off) - 1;
+            for (; k < nc && off[k] < hi; ++k) {
+                const int64_t m = offsets_out[k + 1] - offsets_out[k];
+                const int64_t x0 = std::max(lo, off[k]), x1 = std::min(hi, off[k] + m);
+                if (x0 < x1)
+                    std::memcpy(to + offsets_out[k] + (x0 - off[k]), from + (x0 - lo) * 8,
+                                (x1 - x0) * 8);
+            }
+        };
+    };
+    Download dn;
+    dn.add(dense(t_out), pd.t_out, ns * 8);
+    dn.add(dense(y_out), pd.y_out, ns * 8);
+    if (b->e) dn.add(dense(e_out), pd.e_out, ns * 8);
+    HIP_OK(ctx, download(ctx->stage, dn, st, true));
     return QMI_OK;
 }
 
@@ -1651,25 +1675,22 @@ int whiten_call(qmi_ctx* ctx, const qmi_batch* b, const double* periods, int32_t
     if (nc == 0) return QMI_OK;
     const int64_t ns = b->offsets[nc];
     std::vector<int32_t> st_in(nc);
-    for (int32_t k = 0; k < nc; ++k) {
-        st_in[k] = host_curve_status(b, k, true);
-        if (!(periods[k] > 0.0) || !std::isfinite(periods[k])) st_in[k] = QMI_EINVAL;
-    }
+    curve_statuses(0, nc, ns, st_in.data(), [&](int32_t k) {
+        return periods[k] > 0.0 && std::isfinite(periods[k]) ? host_curve_status(b, k, true)
+                                                             : (int32_t)QMI_EINVAL;
+    });
     HIP_OK(ctx, hipSetDevice(ctx->device));
     begin_use(ctx);
-    int max_n = 0;
-    if ((rc = upload_batch(ctx, b, st_in, &max_n)) != QMI_OK) return rc;
+    BatchDev bd{};
+    if ((rc = upload_batch(ctx, b, st_in, periods, &bd)) != QMI_OK) return rc;
     if ((rc = ensure(ctx, qmi_ctx::kPYo, std::max<int64_t>(ns, 1) * 8)) != QMI_OK) return rc;
-    if ((rc = ensure(ctx, qmi_ctx::kPPer, nc * 8)) != QMI_OK) return rc;
     hipStream_t st = ctx->stream;
-    double* dper = dptr<double>(ctx, qmi_ctx::kPPer);
     double* dy = dptr<double>(ctx, qmi_ctx::kPYo);
-    HIP_OK(ctx, hipMemcpyAsync(dper, periods, nc * 8, hipMemcpyHostToDevice, st));
-    HIP_OK(ctx, launch_whiten(st, nc, max_n, dptr<int64_t>(ctx, qmi_ctx::kPOff),
-                              dptr<double>(ctx, qmi_ctx::kT), dptr<double>(ctx, qmi_ctx::kY), dper,
-                              window, dptr<int32_t>(ctx, qmi_ctx::kPStIn), dy));
-    HIP_OK(ctx, hipMemcpyAsync(y_out, dy, ns * 8, hipMemcpyDeviceToHost, st));
-    HIP_OK(ctx, hipStreamSynchronize(st));
+    HIP_OK(ctx, launch_whiten(st, nc, bd.max_n, bd.offsets, bd.t, bd.y, bd.periods, window,
+                              bd.status, dy));
+    Download dn;
+    dn.add(y_out, dy, ns * 8);
+    HIP_OK(ctx, download(ctx->stage, dn, st, true));
     for (int32_t k = 0; k < nc; ++k) {
         if (st_in[k] != QMI_OK)
             for (int64_t i = b->offsets[k]; i < b->offsets[k + 1]; ++i) y_out[i] = NAN;
