@@ -75,9 +75,9 @@ struct qmi_ctx {
     std::vector<uint64_t> graph_key;
     // Autotuner: pair-kernel variant per length bucket (-1: not tuned yet).
     int tuned[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
-    // Harmonic groups of the mode sums at the last call's (smallest) sigma_t.
-    double mode_sigma_t = 0.0;
-    int mode_groups = 0;
+    // Harmonic groups of the mode sums at the last call's (smallest) sigma_t: mixed, FP64.
+    double mode_sigma_t[2] = {0.0, 0.0};
+    int mode_groups[2] = {0, 0};
     // Spurious-period masks applied by the selection kernels (qmi_set_masks).
     qmi::MaskDev masks{};
     // Serving.
@@ -427,10 +427,10 @@ void record(qmi_ctx* ctx) {
     (void)hipEventRecord(ctx->ev[ctx->ev_used++], ctx->stream);
 }
 
-// Harmonics that the mode sums keep at a periodic-kernel width, as nodes_kernel counts them: the
+// Harmonics that the mode sums keep at a periodic-kernel width, as the preparation counts them: the
 // coefficients 2 e^-k I_m(k), k = 1 / sigma_t^2, by the trapezoid rule.
-int mode_count(double sigma_t) {
-    const int cap = (int)(7.0 / sigma_t) + 8, L = 3 * cap + 32;
+int mode_count(double sigma_t, double keep_tail) {
+    const int cap = (int)((keep_tail < 1e-12 ? 9.5 : 7.0) / sigma_t) + 12, L = 3 * cap + 32;
     const double kap = 1.0 / (sigma_t * sigma_t), turn = 2.0 * M_PI / L;
     std::vector<double> co(L), ev(L);
     for (int j = 0; j < L; ++j) {
@@ -442,7 +442,7 @@ int mode_count(double sigma_t) {
         double s = 0.0;
         for (int j = 0; j < L; ++j) s += ev[j] * co[(int64_t)m * j % L];
         tail += 2.0 * s / L;
-        if (tail > kModeTail) return m;
+        if (tail > keep_tail) return m;
     }
     return 1;
 }
@@ -471,14 +471,16 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     const bool rule_t = kp->sigma_t == QMI_SIGMA_T_SKEWNESS;
     const double min_sigma_t = !rule_t ? kp->sigma_t
                                : kp->skew_lambda > 0.0 ? kp->skew_lambda : QMI_SKEW_LAMBDA;
-    const bool mixed = kp->precision == QMI_PREC_MIXED && !pairs_only;
-    if (mixed && ctx->mode_sigma_t != min_sigma_t) {
-        ctx->mode_sigma_t = min_sigma_t;
-        ctx->mode_groups = min_sigma_t * kModeCapMax > 8.0
-                               ? (mode_count(min_sigma_t) + kModeGroup - 1) / kModeGroup : 0;
+    const bool modes = kp->precision != QMI_PREC_FOLD32 && !pairs_only;
+    const int per_group = fp64 ? kModeGroup64 : kModeGroup;
+    if (modes && ctx->mode_sigma_t[fp64] != min_sigma_t) {
+        ctx->mode_sigma_t[fp64] = min_sigma_t;
+        const int m = min_sigma_t * kModeCapMax > (fp64 ? 9.0 : 8.0)
+                          ? mode_count(min_sigma_t, fp64 ? kModeTail64 : kModeTail) : 0;
+        ctx->mode_groups[fp64] = (m + per_group - 1) / per_group;
     }
-    const int mode_groups = mixed ? ctx->mode_groups : 0;
-    const int mode_cap = mode_groups * kModeGroup + 8;
+    const int mode_groups = modes ? ctx->mode_groups[fp64] : 0;
+    const int mode_cap = mode_groups * per_group + 8;
     constexpr int kPassR = kWaves * rows_per_wave<R>();
     int max_n = 2, max_pieces = 0;
     std::vector<int32_t> status(nc);
@@ -505,10 +507,11 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             all_ks += (int64_t)((p.n + kPassR - 1) / kPassR) * kWaves * p.n;
         }
         const int whole = (p.n + 31) / 32 + 2;
-        if (p.status == QMI_OK && mode_groups > 0 && whole <= mode_even(p.n, mode_groups) &&
-            whole <= p.n / 5) {
+        if (p.status == QMI_OK && mode_groups > 0 &&
+            (fp64 ? mode64_takes(p.n, mode_groups)
+                  : whole <= mode_even(p.n, mode_groups) && whole <= p.n / 5)) {
             ModeCurve& m = mc[i];
-            m.cap = mode_room(p.n, mode_groups);
+            m.cap = fp64 ? mode64_room(p.n) : mode_room(p.n, mode_groups);
             m.boff = mblocks;
             mblocks += m.cap;
             ++n_modes;
@@ -582,12 +585,12 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         ENSURE(qmi_ctx::kKS, std::max<int64_t>(ksoff, 1) * sizeof(R));
     }
     if (n_modes) {
-        ENSURE(qmi_ctx::kModeTs, mblocks * 256);
+        ENSURE(qmi_ctx::kModeTs, mblocks * (fp64 ? 32 : 256));
         ENSURE(qmi_ctx::kModeRows, mblocks * 4);
-        ENSURE(qmi_ctx::kModeFrag, mblocks * 4096);
-        ENSURE(qmi_ctx::kModePart, mblocks * 256);
+        ENSURE(qmi_ctx::kModeFrag, mblocks * (fp64 ? 1024 : 4096));
+        if (!fp64) ENSURE(qmi_ctx::kModePart, mblocks * 256);
         ENSURE(qmi_ctx::kModeB, mblocks * 256);
-        if (refine) {
+        if (refine && !fp64) {
             ENSURE(qmi_ctx::kTieCnt, nc * 4);
             ENSURE(qmi_ctx::kTieSlot, nc * (int64_t)kTieMax * 4);
             ENSURE(qmi_ctx::kTieScore, nc * (int64_t)kTieMax * 8);
@@ -660,14 +663,14 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         md.ts = dptr<double>(ctx, qmi_ctx::kModeTs);
         md.rows = dptr<int32_t>(ctx, qmi_ctx::kModeRows);
         md.frag = dptr<char>(ctx, qmi_ctx::kModeFrag);
-        md.part = dptr<double>(ctx, qmi_ctx::kModePart);
+        if (!fp64) md.part = dptr<double>(ctx, qmi_ctx::kModePart);
         md.b = dptr<double>(ctx, qmi_ctx::kModeB);
         md.coef = dptr<double>(ctx, qmi_ctx::kModeCoef);
-        if (refine)
+        if (refine && !fp64)
             tie = TieDev{dptr<int32_t>(ctx, qmi_ctx::kTieCnt),
                          dptr<int32_t>(ctx, qmi_ctx::kTieSlot),
                          dptr<double>(ctx, qmi_ctx::kTieScore), md.curves};
-        if (refine) {
+        if (refine && !fp64) {
             const qmi_search* q = cs.search;
             md.win_width = q->n_coarse > 1 ? 2.0 * (q->f_max - q->f_min) / (q->n_coarse - 1) : 0.0;
             md.n_fine = n_fine;
@@ -793,12 +796,15 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
 
     // The device section: every kernel of the call, and the timing events around the pair kernels.
     // It contains no copies or allocations, so it can be captured into a hipGraph and replayed.
+    constexpr auto sum_modes = std::is_same<R, double>::value ? launch_modes64 : launch_modes;
     auto section = [&](bool events) -> int {
         auto rec = [&]() {
             if (events) record(ctx);
         };
         rec();  // device section start
-        HIP_OK(ctx, launch_prepare(st, dcp, nc, max_n, t, y, e, skew_lambda, skew_mu, md));
+        HIP_OK(ctx, launch_prepare(st, dcp, nc, max_n, t, y, e, skew_lambda, skew_mu,
+                                   fp64 ? ModeDev{} : md));
+        if (fp64 && n_modes) HIP_OK(ctx, launch_prepare64(st, dcp, nc, max_n, t, y, md));
         if (n_pairs) {
             HIP_OK(ctx, launch_gram<R>(st, dcp, nc, rows, drow, y, K, rp, rd));
             HIP_OK(ctx, launch_gram_finalize<R>(st, dcp, nc, rd, rp));
@@ -811,7 +817,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             PairOut pm1 = po;
             pm1.part = msplit1 ? dpart : nullptr;
             if (n_modes)
-                HIP_OK(ctx, launch_modes(st, dcp, dorder, n_modes, fp, md, pm1,
+                HIP_OK(ctx, sum_modes(st, dcp, dorder, n_modes, fp, md, pm1,
                                          msplit1 ? mode_groups : 0));
             PairOut pc1 = po;
             pc1.part = split1 ? dpart : nullptr;
@@ -852,7 +858,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
                 PairOut fm = fo;
                 fm.part = msplit2 ? dpart : nullptr;
                 if (n_modes)
-                    HIP_OK(ctx, launch_modes(st, dcp, dorder, n_modes, ff, md, fm,
+                    HIP_OK(ctx, sum_modes(st, dcp, dorder, n_modes, ff, md, fm,
                                              msplit2 ? mode_groups : 0));
                 if (md.win_width > 0.0)
                     HIP_OK(ctx, launch_mode_windows(st, dcp, nc, ff, md, fm));
@@ -1165,7 +1171,7 @@ int run_call(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs) {
     for (const Group& g : groups) {
         left.clear();
         rc = (cs.kp->precision == QMI_PREC_FP64)
-                 ? run_group<double>(ctx, b, cs, g, pair_ev, true, &left)
+                 ? run_group<double>(ctx, b, cs, g, pair_ev, false, &left)
                  : run_group<float>(ctx, b, cs, g, pair_ev, false, &left);
         if (rc) return rc;
         // Curves that the mode sums left (known only once their widths are): runs of neighbours
@@ -1176,7 +1182,9 @@ int run_call(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs) {
             const Group sub{left[i], left[j - 1] + 1, b->offsets[left[i]],
                             b->offsets[left[j - 1] + 1]};
             ctx->ws_used = 0;
-            rc = run_group<float>(ctx, b, cs, sub, pair_ev, true, nullptr);
+            rc = (cs.kp->precision == QMI_PREC_FP64)
+                     ? run_group<double>(ctx, b, cs, sub, pair_ev, true, nullptr)
+                     : run_group<float>(ctx, b, cs, sub, pair_ev, true, nullptr);
             if (rc) return rc;
             i = j;
         }

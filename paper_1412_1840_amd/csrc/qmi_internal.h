@@ -97,6 +97,26 @@ constexpr double kNodeP = kNodeStep * 0.56418958354775628694807945156077;  // h 
 // A sample uses the 16-node blocks rb and rb + 1, rb chosen so that they hold at least the
 // 2 kReach + 1 nodes nearest to it (beyond, U < exp(-(8.5 h)^2) = 1.5e-8).
 constexpr int kReach = 8;
+// The mode sums in FP64 (qmi_modes64.hip): the same series and nodes, to the rounding of a double.
+// Blocks of four samples that reach the same eight quads of nodes (32 nodes; at least the
+// 2 kReach64 + 1 nearest to each sample: beyond, U < exp(-(14.5 h)^2) = 2e-15).
+constexpr double kModeTail64 = 1e-16;
+constexpr int kModeGroup64 = 4;
+constexpr double kNodeStep64 = 0.4;  // trapezoid error 8e-14 of a kernel value, alternating
+constexpr double kNodeW64 = kNodeStep64 * 0.79788456080286535587989211986876;
+constexpr double kNodeP64 = kNodeStep64 * 0.56418958354775628694807945156077;
+constexpr int kReach64 = 14;
+constexpr int kQuads64 = 8;
+// Four harmonics per pass take as long as five and half as long as six (whose sums spill): 1.09, 1.09
+// and 2.2 ms for 16 survey curves at 1024 frequencies.
+// Whether the host gives a curve to them.  Measured per curve and frequency (4096 frequencies,
+// batches): the mode sums take 0.0098 n + 0.04 ns per group of harmonics, the pair sums 4.7e-4 n^2;
+// they meet at n = 50, 95, 170, 480 and 1150 for sigma_t = 2, 0.6, 0.3, 0.1 and 0.05 (3, 5, 9, 23
+// and 46 groups).
+inline bool mode64_takes(int n, int groups) { return n >= 20 * groups + groups * groups / 10; }
+// Blocks a curve has room for: its own, half as many again lost to the ends of groups (more and it
+// is given back to the pair sums).
+inline int mode64_room(int n) { return n / 4 + n / 8 + 8; }
 struct ModeCurve {
     int64_t boff;   // first of its cap blocks
     int32_t cap;    // blocks there is room for; 0: the curve is left to the pair sums
@@ -296,6 +316,16 @@ hipError_t launch_pairs_rows(hipStream_t st, const CurveParams* cp, const int32_
 hipError_t launch_modes(hipStream_t st, const CurveParams* cp, const int32_t* order,
                         int n_work_curves, const FreqPlan& fp, const ModeDev& md,
                         const PairOut& out, int split_groups);
+hipError_t launch_mode_epilogue(hipStream_t st, const CurveParams* cp, const int32_t* order,
+                                int n_work_curves, const FreqPlan& fp, const ModeDev& md,
+                                const PairOut& out, int split_groups);
+// The same in FP64.  md: ts [block][4], rows the first node quad of a block (counted among the
+// curve's), frag [block][2][64 lanes] values of U, b [node quad (from 8 boff)][4].
+hipError_t launch_prepare64(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
+                            const double* t, const double* y, const ModeDev& md);
+hipError_t launch_modes64(hipStream_t st, const CurveParams* cp, const int32_t* order,
+                          int n_work_curves, const FreqPlan& fp, const ModeDev& md,
+                          const PairOut& out, int split_groups);
 // The refinement windows of the curves with nodes > 0: every point's scores from the node sums that
 // launch_modes left in out.score and out.score2.
 hipError_t launch_mode_windows(hipStream_t st, const CurveParams* cp, int n_curves,

@@ -22,7 +22,7 @@
 
 #include <algorithm>
 
-#include "qmi_internal.h"
+#include "qmi_modes.h"
 
 namespace qmi {
 
@@ -38,66 +38,9 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 // (k + 1) times that, which the coefficients make up for.
 constexpr double kTrigLoss = 6.5e-8;
 
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
 // --------------------------------------------------------------------------------------------
 // Mode sums
 // --------------------------------------------------------------------------------------------
-
-// Frequency of slot s of curve c.  nodes > 0 (refinement windows): slots are the Chebyshev nodes of
-// the curve's windows, nodes per window.
-__device__ __forceinline__ double mode_slot_freq(const FreqPlan& fp, int c, int s, int nodes,
-                                                 bool& active) {
-    if (nodes > 0) {
-        const int p = s / nodes, j = s - p * nodes;
-        active = p < fp.npk[c];
-        if (!active) return 0.0;
-        const double* w = fp.win + ((int64_t)c * fp.top_k + p) * 2;
-        const double half = 0.5 * w[1] * (double)(fp.n_fine - 1);
-        return w[0] + half * (1.0 + cospi(((double)j + 0.5) / (double)nodes));
-    }
-    active = s < fp.count;
-    if (!active) return 0.0;
-    if (fp.kind == 0) return __dadd_rn(fp.f0, __dmul_rn((double)s, fp.df));
-    if (fp.kind == 1) return fp.list[s];
-    if (fp.kind == 3) {
-        const double v = fp.list[(int64_t)c * fp.stride + s];
-        active = v == v;
-        return active ? v : 0.0;
-    }
-    const int p = s / fp.n_fine, m = s - p * fp.n_fine;
-    if (p >= fp.npk[c]) {
-        active = false;
-        return 0.0;
-    }
-    const double* w = fp.win + ((int64_t)c * fp.top_k + p) * 2;
-    return __dadd_rn(w[0], __dmul_rn((double)m, w[1]));
-}
-
-__device__ __forceinline__ void mode_nan(int64_t o, const PairOut& out) {
-    out.score[o] = NAN;
-    if (out.score2) out.score2[o] = NAN;
-    if (out.ips) out.ips[o * 3 + 0] = out.ips[o * 3 + 1] = out.ips[o * 3 + 2] = NAN;
-}
-
-// V_J, IP_t, V_C and the scores from the three sums over ordered pairs without their constants.
-__device__ __forceinline__ void mode_scores(const CurveParams& P, double SJ, double ST, double SC,
-                                            int64_t o, const PairOut& out) {
-    const double N = (double)P.n;
-    const double VJ = P.A * P.B * SJ / (N * N);
-    const double IPt = P.A * ST / (N * N);
-    const double VC = P.A * P.B * SC / (N * N * N);
-    const double VM = P.ipy * IPt;
-    const double q = log(VJ) + log(VM) - 2.0 * log(VC);
-    const double nckp = sqrt(N * P.sigma_t) / P.ipy * (VJ - VM);
-    out.score[o] = out.score_kind == 0 ? q : nckp;
-    if (out.score2) out.score2[o] = out.score_kind == 0 ? nckp : q;
-    if (out.ips) {
-        out.ips[o * 3 + 0] = VJ;
-        out.ips[o * 3 + 1] = IPt;
-        out.ips[o * 3 + 2] = VC;
-    }
-}
 
 // The sums of a window's nodes, kept where its points' scores will be: S_J and S_C in the first and
 // second half of the window's score entries, S_T among its entries of the other score.
@@ -109,10 +52,6 @@ __device__ __forceinline__ void store_node_sums(const FreqPlan& fp, int c, int s
     out.score[o] = SJ;
     out.score[o + nodes] = SC;
     out.score2[o] = ST;
-}
-
-__device__ __forceinline__ void lds_add(double* p, double v) {
-    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 // Eight single-precision values as a high and a low half-precision part (each rounded to nearest:
@@ -675,6 +614,15 @@ hipError_t launch_mode_ties(hipStream_t st, const CurveParams* cp, int n_curves,
     return hipGetLastError();
 }
 
+hipError_t launch_mode_epilogue(hipStream_t st, const CurveParams* cp, const int32_t* order,
+                                int n_work_curves, const FreqPlan& fp, const ModeDev& md,
+                                const PairOut& out, int split_groups) {
+    const int64_t threads = (int64_t)n_work_curves * fp.count;
+    mode_epilogue_kernel<<<(unsigned)((threads + kModeEpiBlock - 1) / kModeEpiBlock), kModeEpiBlock,
+                           0, st>>>(cp, order, fp, md, n_work_curves, split_groups, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_modes(hipStream_t st, const CurveParams* cp, const int32_t* order,
                         int n_work_curves, const FreqPlan& fp, const ModeDev& md,
                         const PairOut& out, int split_groups) {
@@ -686,11 +634,7 @@ hipError_t launch_modes(hipStream_t st, const CurveParams* cp, const int32_t* or
             cp, order, fp, md, n_work_curves, 0, split_groups, out);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        const int64_t threads = (int64_t)n_work_curves * fp.count;
-        mode_epilogue_kernel<<<(unsigned)((threads + kModeEpiBlock - 1) / kModeEpiBlock),
-                               kModeEpiBlock, 0, st>>>(cp, order, fp, md, n_work_curves,
-                                                       split_groups, out);
-        return hipGetLastError();
+        return launch_mode_epilogue(st, cp, order, n_work_curves, fp, md, out, split_groups);
     }
     const int xcd = n_work_curves >= 8 * kXcds;
     const int64_t rows = xcd ? (int64_t)(n_work_curves + kXcds - 1) / kXcds * kXcds

@@ -1,0 +1,245 @@
+// HIP kernel for gfx950 (MI355X): the mode sums (qmi_modes.hip) of Protopapas et al.,
+// arXiv:1412.1840, with every step in FP64 (QMI_PREC_FP64).
+#include <math.h>
+
+#include "qmi_modes.h"
+
+namespace qmi {
+
+namespace {
+
+typedef double double4v __attribute__((ext_vector_type(4)));
+
+// sin and cos of p turns, |p| <= 1/2: the Taylor series of both at the nearest quarter turn
+// (|r| <= 1/2 of a quarter; the first omitted terms are below 3e-19) and the quadrant identities.
+// 33 instructions, where sincospi takes 61.
+__device__ __forceinline__ void sincos_turns(double p, double* sn, double* cs) {
+    constexpr double S[9] = {1.5707963267948966, -0.6459640975062463, 0.07969262624616705,
+                             -0.004681754135318688, 0.00016044118478735983, -3.598843235212085e-06,
+                             5.692172921967927e-08, -6.688035109811468e-10, 6.0669357311061955e-12};
+    constexpr double C[9] = {1.0, -1.2337005501361697, 0.25366950790104803,
+                             -0.02086348076335296, 0.0009192602748394266, -2.5202042373060607e-05,
+                             4.710874778818172e-07, -6.386603083791852e-09, 6.565963114979473e-11};
+    const double x = 4.0 * p, q = rint(x), r = x - q, u = r * r;
+    double s = S[8], c = C[8];
+#pragma unroll
+    for (int k = 7; k >= 0; --k) {
+        s = fma(u, s, S[k]);
+        c = fma(u, c, C[k]);
+    }
+    s *= r;
+    const int iq = (int)q;
+    const double a = (iq & 1) ? c : s, b = (iq & 1) ? s : c;
+    *sn = (iq & 2) ? -a : a;
+    *cs = ((iq + 1) & 2) ? -b : b;
+}
+
+// One wave = (curve, 16 frequency slots): lane l works for slot l mod 16 and, in every block of 4
+// samples, for sample l / 16, whose harmonics it feeds as the B operand of the 16 x 16 x 4 matrix
+// instruction; the block's values of U in 32 nodes are two A operands.  The nodes are eight quads;
+// quad k keeps its sums in register k mod 4 of accumulator (k mod 8) / 4, a node per lane group
+// (row 4 i + l / 16 of the result is register i), and when the samples, in magnitude order, move on
+// past it, that register is folded into the lane's sums and taken over by quad k + 8.  So a sample
+// has 32 nodes of which it needs 29, and nothing moves between registers.
+//
+// Bound: FP64 arithmetic.  The matrix instruction takes 64 cycles of a SIMD and shares the FP64
+// units with the vector instructions (measured: 71 cycles of 2.4 GHz, 4.3 more for every fma beside
+// it), 16 of them and about 75 others per block and group of harmonics, 1500 cycles; measured 1700.
+// The pairs take 26 instructions each: N^2 / 2 of them against N times 32 nodes, 2 x 33 harmonics
+// (sigma_t 0.3) and the sines.  Measured, 16 survey curves, 1024 frequencies: 1.1 ms against 3.3
+// (1.15 with sincospi in place of sincos_turns).  Errors against extended precision are the pair
+// sums': QMI 0.5e-15 to 1.7e-15 rms against 0.5e-15 to 2e-15 at N = 300 to 1200 and sigma_t 0.3, and
+// less where both have more harmonics (sigma_t 0.1: 0.8e-15 against 5.8e-15).
+constexpr int kWaves64 = 4;
+constexpr int kThreads64 = 64 * kWaves64;
+constexpr int kS64 = 5;  // sums per harmonic and lane
+
+template <bool SPLIT>
+__global__ void __launch_bounds__(kThreads64, 2)
+modes64_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ order, FreqPlan fp,
+               ModeDev md, int n_work, int xcd_grouped, int gmax, PairOut out) {
+    __shared__ double S_all[kWaves64][kModeGroup64 * kS64][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = uni((int)(threadIdx.x >> 6));
+    const int tiles = (fp.count + kLanes - 1) / kLanes;
+    int rank, tile, g0 = 0;
+    const unsigned blk = blockIdx.x;
+    if (SPLIT) {
+        rank = (int)(blk / (unsigned)(gmax * tiles));
+        const int rem = (int)(blk - (unsigned)rank * (gmax * tiles));
+        g0 = rem / tiles;
+        tile = rem - g0 * tiles;
+    } else if (xcd_grouped) {
+        const int xcd = (int)(blk % kXcds);
+        const int seq = (int)(blk / kXcds);
+        rank = (seq / tiles) * kXcds + xcd;
+        tile = seq - (seq / tiles) * tiles;
+    } else {
+        rank = (int)(blk / tiles);
+        tile = (int)(blk - (unsigned)rank * tiles);
+    }
+    if (rank >= n_work) return;
+    const int c = order[rank];
+    const CurveParams P = cp[c];
+    const int n16 = lane & 15, kg = lane >> 4;
+    const int slot = tile * kLanes + wave * 16 + n16;
+    if (tile * kLanes + wave * 16 >= fp.count) return;
+    bool active;
+    const double f = mode_slot_freq(fp, c, slot, 0, active);
+    const int64_t obase = (int64_t)c * fp.count + slot;
+    if (P.status != 0) {
+        if (active && kg == 0 && g0 == 0 && !SPLIT) mode_nan(obase, out);
+        return;
+    }
+    const ModeCurve M = md.curves[c];
+    const int g_end = SPLIT ? min(g0 + 1, M.groups) : M.groups;
+    if (g0 >= g_end) return;  // no such group, or a curve left to the pair sums
+    const double* ts = md.ts + 4 * M.boff + kg;
+    const double* frag = reinterpret_cast<const double*>(md.frag) + 128 * M.boff + lane;
+    const double* bq = md.b + 32 * M.boff + kg;
+    const int32_t* rows = md.rows + M.boff;
+    const double* coef = md.coef + (int64_t)c * mode_stride(md.mode_cap);
+    double (*S)[64] = S_all[wave];
+
+    double SJ = M.c0 * M.sj0, ST = M.c0 * M.n0 * M.n0, SC = M.c0 * M.n0 * M.sj0;
+    if (SPLIT) SJ = ST = SC = 0.0;
+    for (int g = g0; g < g_end; ++g) {
+        const int m0 = g * kModeGroup64 + 1;
+        double4v acc[2][kModeGroup64][2];
+#pragma unroll
+        for (int m = 0; m < kModeGroup64; ++m) {
+            acc[0][m][0] = acc[0][m][1] = acc[1][m][0] = acc[1][m][1] = double4v{0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < kS64; ++q) S[m * kS64 + q][lane] = 0.0;
+        }
+        int wb = 0;  // first node quad in the registers
+        // Folds the quads before `row`.  One uniform branch per register, each quad's own: a loop
+        // over the quads would have the accumulators merged, and moved, at every turn.
+        auto retire_to = [&](int row) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 0; s < kQuads64; ++s) {
+                const int quad = wb + ((s - wb) & (kQuads64 - 1));
+                if (quad >= row) continue;
+                const double b = bq[4 * (int64_t)quad];
+#pragma unroll
+                for (int m = 0; m < kModeGroup64; ++m) {
+                    const double x = acc[s / 4][m][0][s % 4], z = acc[s / 4][m][1][s % 4];
+                    acc[s / 4][m][0][s % 4] = acc[s / 4][m][1][s % 4] = 0.0;
+                    lds_add(&S[m * kS64 + 0][lane], fma(x, x, z * z));
+                    lds_add(&S[m * kS64 + 1][lane], x);
+                    lds_add(&S[m * kS64 + 2][lane], z);
+                    lds_add(&S[m * kS64 + 3][lane], b * x);
+                    lds_add(&S[m * kS64 + 4][lane], b * z);
+                }
+            }
+            wb = row;
+        };
+        double a0 = frag[0], a1 = frag[64], t = ts[0];
+        for (int kb = 0; kb < M.blocks; ++kb) {
+            const int row = uni(rows[kb]);
+            if (wb < row) retire_to(row);
+            const double u0 = a0, u1 = a1;
+            const double p = fma(f, t, -rint(f * t));  // the phase, in turns
+            if (kb + 1 < M.blocks) {
+                a0 = frag[(int64_t)(kb + 1) * 128];
+                a1 = frag[(int64_t)(kb + 1) * 128 + 64];
+                t = ts[4 * (kb + 1)];
+            }
+            // z_m = exp(2 pi i m f t): z_m0 from its own phase, z_m0+1 = z_m0 z_1, and on from there
+            // by z_m+1 = 2 cos(2 pi f t) z_m - z_m-1.
+            double s1, c1, C, Sn;
+            sincos_turns(p, &s1, &c1);
+            C = c1;
+            Sn = s1;
+            if (g > 0) {
+                const double q = (double)m0 * p;
+                sincos_turns(q - rint(q), &Sn, &C);
+            }
+            double Cp = 0.0, Sp = 0.0;
+#pragma unroll
+            for (int m = 0; m < kModeGroup64; ++m) {
+                acc[0][m][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(u0, C, acc[0][m][0], 0, 0, 0);
+                acc[1][m][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(u1, C, acc[1][m][0], 0, 0, 0);
+                acc[0][m][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(u0, Sn, acc[0][m][1], 0, 0, 0);
+                acc[1][m][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(u1, Sn, acc[1][m][1], 0, 0, 0);
+                double x, y;
+                if (m == 0) {
+                    x = fma(C, c1, -(Sn * s1));
+                    y = fma(C, s1, Sn * c1);
+                    c1 += c1;
+                } else {
+                    x = fma(c1, C, -Cp);
+                    y = fma(c1, Sn, -Sp);
+                }
+                Cp = C;
+                Sp = Sn;
+                C = x;
+                Sn = y;
+            }
+        }
+        retire_to(wb + kQuads64);
+        // The four lanes of a slot hold a quarter of its nodes each: lane group kg adds them for
+        // the harmonics kg, kg + 4, ... and forms their terms.
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        double gj = 0.0, gt = 0.0, gc = 0.0;
+        for (int m = kg; m < kModeGroup64; m += 4) {
+            double v[kS64];
+#pragma unroll
+            for (int q = 0; q < kS64; ++q) {
+                v[q] = 0.0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[q] += S[m * kS64 + q][n16 + 16 * k];
+            }
+            const double cm = coef[m0 - 1 + m];
+            const double ca = kNodeP64 * v[1], sa = kNodeP64 * v[2];
+            gj = fma(cm, kNodeW64 * v[0], gj);
+            gt = fma(cm, ca * ca + sa * sa, gt);
+            gc = fma(cm, kNodeW64 * (ca * v[3] + sa * v[4]), gc);
+        }
+        for (int o = 16; o < 64; o <<= 1) {
+            gj += __shfl_xor(gj, o, 64);
+            gt += __shfl_xor(gt, o, 64);
+            gc += __shfl_xor(gc, o, 64);
+        }
+        SJ += gj;
+        ST += gt;
+        SC += gc;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (kg != 0 || !active) return;
+    if (SPLIT) {
+        double* pp = out.part + (((int64_t)rank * gmax + g0) * fp.count + slot) * 3;
+        pp[0] = SJ;
+        pp[1] = ST;
+        pp[2] = SC;
+        return;
+    }
+    mode_scores(P, SJ, ST, SC, obase, out);
+}
+
+}  // namespace
+
+hipError_t launch_modes64(hipStream_t st, const CurveParams* cp, const int32_t* order,
+                          int n_work_curves, const FreqPlan& fp, const ModeDev& md,
+                          const PairOut& out, int split_groups) {
+    if (n_work_curves <= 0 || fp.count <= 0) return hipSuccess;
+    const int64_t tiles = (fp.count + kLanes - 1) / kLanes;
+    if (split_groups > 0 && out.part) {
+        const int64_t blocks = (int64_t)n_work_curves * split_groups * tiles;
+        modes64_kernel<true><<<(unsigned)blocks, kThreads64, 0, st>>>(
+            cp, order, fp, md, n_work_curves, 0, split_groups, out);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        return launch_mode_epilogue(st, cp, order, n_work_curves, fp, md, out, split_groups);
+    }
+    const int xcd = n_work_curves >= 8 * kXcds;
+    const int64_t rows = xcd ? (int64_t)(n_work_curves + kXcds - 1) / kXcds * kXcds
+                             : (int64_t)n_work_curves;
+    modes64_kernel<false><<<(unsigned)(rows * tiles), kThreads64, 0, st>>>(
+        cp, order, fp, md, n_work_curves, xcd, 0, out);
+    return hipGetLastError();
+}
+
+}  // namespace qmi

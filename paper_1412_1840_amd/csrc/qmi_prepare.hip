@@ -63,6 +63,31 @@ __device__ double sorted_median(const double* a, int n) {
     return (n & 1) ? a[n / 2] : 0.5 * (a[n / 2 - 1] + a[n / 2]);
 }
 
+// Coefficients cs[0..cap] of the periodic kernel's cosine series by the trapezoid rule over the
+// circle (exact up to the coefficients past L - m).  ev, ct: L = 3 cap + 32 entries each.
+template <int BLOCK>
+__device__ void series_coefficients(double sigma_t, int cap, double* ev, double* ct, double* cs) {
+    const int L = 3 * cap + 32, tid = threadIdx.x;
+    const double kap = 1.0 / (sigma_t * sigma_t);
+    for (int j = tid; j < L; j += BLOCK) {
+        const double x = (double)j / (double)L, sn = sinpi(x);
+        ct[j] = cospi(2.0 * x);
+        ev[j] = exp(-2.0 * kap * sn * sn);  // (cos - 1 would lose kap roundings where it is small)
+    }
+    __syncthreads();
+    for (int m = tid; m <= cap; m += BLOCK) {
+        double a = 0.0;
+        int k = 0;
+#pragma unroll 4
+        for (int j = 0; j < L; ++j) {
+            a = fma(ev[j], ct[k], a);
+            k += m;
+            if (k >= L) k -= L;
+        }
+        cs[m] = (m ? 2.0 : 1.0) * a / (double)L;
+    }
+}
+
 // Waves that form operand tiles, and the bytes of a tile (two node blocks, two parts, 64 lanes).
 template <int BLOCK>
 constexpr int tile_waves() {
@@ -347,30 +372,12 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
         }
     sq = block_sum(sq, red);
     sb = block_sum(sb, red);
-    // Coefficients of the periodic kernel's cosine series by the trapezoid rule over the circle
-    // (exact up to the coefficients past L - m), and the number of harmonics to keep.
+    // Coefficients, and the number of harmonics to keep.
     const int cap = md.mode_cap, L = 3 * cap + 32;
     double* ev = psh;
     double* ct = psh + L;
     double* cs = ct + L;  // [cap + 1]
-    const double kap = 1.0 / (sigma_t * sigma_t);
-    for (int j = tid; j < L; j += BLOCK) {
-        const double co = cospi(2.0 * (double)j / (double)L);
-        ct[j] = co;
-        ev[j] = exp(kap * (co - 1.0));
-    }
-    __syncthreads();
-    for (int m = tid; m <= cap; m += BLOCK) {
-        double a = 0.0;
-        int k = 0;
-#pragma unroll 4
-        for (int j = 0; j < L; ++j) {
-            a = fma(ev[j], ct[k], a);
-            k += m;
-            if (k >= L) k -= L;
-        }
-        cs[m] = (m ? 2.0 : 1.0) * a / (double)L;
-    }
+    series_coefficients<BLOCK>(sigma_t, cap, ev, ct, cs);
     // Frequencies per refinement window.  Harmonic m of the sums runs through at most
     // w = pi m T W (T the curve's time span, W the window) radians from the window's middle to its
     // end, and its Chebyshev coefficients fall below eps past the degree
@@ -440,7 +447,197 @@ hipError_t launch_prepare_b(hipStream_t st, CurveParams* cp, int n_curves, int m
     return hipGetLastError();
 }
 
+// The node tables of the FP64 mode sums, as above but for exact operands: quads of nodes in place of
+// blocks of 16, blocks of 4 samples, the value of every node and sample by its own exponential.
+// Node quad k of a curve has its sums in register k mod 8 of the kernel, so that its values stand in
+// rows 4 (k mod 8) ... + 3 of the operands.  Bound: latency (sort, scans, reductions);
+// measured, 16 survey curves 47 us.
+template <int BLOCK, int EMAX>
+__global__ void __launch_bounds__(BLOCK)
+prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
+                 const double* __restrict__ y_all, int room, int key_bytes, int group_room,
+                 ModeDev md) {
+    extern __shared__ double psh[];
+    __shared__ double red[kSumThreads / 64];
+    __shared__ int ired[BLOCK / 64];
+    const int c = blockIdx.x, tid = threadIdx.x;
+    const CurveParams P = cp[c];
+    ModeCurve M = md.curves[c];
+    if (P.status != 0 || M.cap == 0) return;
+    const int n = P.n;
+    const double* t = t_all + P.off;
+    const double* y = y_all + P.off;
+    double* key = psh;
+    int32_t* idx = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(psh) + key_bytes);
+    int* g_first = reinterpret_cast<int*>(idx) + room;
+    int* g_block = g_first + group_room + 1;  // first block of samples of a group
+    int* g_row = g_block + group_room + 1;    // first node quad, counted among those in use
+    int* g_quad = g_row + group_room;         // and by magnitude
+    for (int i = tid; i < n; i += BLOCK) {
+        key[i] = y[i];
+        idx[i] = i;
+    }
+    sort_block<BLOCK, EMAX, true>(key, idx, n);
+    const double y0 = key[0], inv = 1.0 / (kNodeStep64 * P.sigma_y);
+    bool sparse = !((key[n - 1] - y0) * inv < 1e9);
+    auto pos = [&](int i) { return (key[i] - y0) * inv + (double)kReach64; };
+    auto quad = [&](int i) { return ((int)rint(pos(i)) - kReach64) >> 2; };
+    int n_groups = 0, n_rows = 0, n_blocks = 0;
+    if (!sparse) {
+        constexpr int kShift = 14;  // groups (at most 8192) below, quads (8 per group) above
+        static_assert(QMI_MAX_N < (1 << kShift) && QMI_MAX_N * kQuads64 < (1 << 17), "packed counts");
+        const int per = (n + BLOCK - 1) / BLOCK;
+        const int i0 = min(n, tid * per), i1 = min(n, i0 + per);
+        int cnt = 0, all = 0;
+        for (int i = i0; i < i1; ++i) {
+            const int d = i == 0 ? kQuads64 : min(kQuads64, quad(i) - quad(i - 1));
+            if (d > 0) cnt += 1 + (d << kShift);
+        }
+        int at = block_scan<BLOCK>(cnt, ired, &all);
+        n_groups = all & ((1 << kShift) - 1);
+        n_rows = all >> kShift;
+        sparse = n_groups > M.cap;
+        if (!sparse) {
+            for (int i = i0; i < i1; ++i) {
+                const int b = quad(i);
+                const int d = i == 0 ? kQuads64 : min(kQuads64, b - quad(i - 1));
+                if (d <= 0) continue;
+                const int g = at & ((1 << kShift) - 1);
+                at += 1 + (d << kShift);
+                g_first[g] = i;
+                g_quad[g] = b;
+                g_row[g] = (at >> kShift) - kQuads64;
+            }
+            if (tid == 0) g_first[n_groups] = n;
+            __syncthreads();
+            const int gper = (n_groups + BLOCK - 1) / BLOCK;
+            const int a0 = min(n_groups, tid * gper), a1 = min(n_groups, a0 + gper);
+            int nb = 0;
+            for (int g = a0; g < a1; ++g) nb += (g_first[g + 1] - g_first[g] + 3) >> 2;
+            int f = block_scan<BLOCK>(nb, ired, &n_blocks);
+            for (int g = a0; g < a1; ++g) {
+                g_block[g] = f;
+                f += (g_first[g + 1] - g_first[g] + 3) >> 2;
+            }
+            if (tid == 0) g_block[n_groups] = n_blocks;
+            sparse = n_blocks > M.cap;
+        }
+        __syncthreads();
+    }
+    if (sparse) {
+        if (tid == 0) {
+            md.curves[c].groups = 0;
+            cp[c].sparse = 1;
+        }
+        return;
+    }
+    auto group_of = [&](int block) {
+        int lo = 0, hi = n_groups - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (g_block[mid] <= block) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
+    double* ts = md.ts + 4 * M.boff;
+    int32_t* rows = md.rows + M.boff;
+    double* frag = reinterpret_cast<double*>(md.frag) + 128 * M.boff;
+    double* bsum = md.b + 32 * M.boff;
+    const int lane = tid & 63, wave = tid >> 6;
+    for (int b = wave; b < n_blocks; b += BLOCK / 64) {
+        const int g = group_of(b), r0 = g_row[g];
+        const int smp = g_first[g] + 4 * (b - g_block[g]) + (lane >> 4);
+        const bool has = smp < g_first[g + 1];
+        const double x = has ? pos(smp) : 0.0;
+        for (int nb = 0; nb < 2; ++nb) {
+            const int s = 4 * nb + ((lane & 15) >> 2);
+            const int node = 4 * (g_quad[g] + ((s - r0) & (kQuads64 - 1))) + (lane & 3);
+            const double d = ((double)node - x) * kNodeStep64;
+            frag[(int64_t)b * 128 + 64 * nb + lane] = has ? exp(-d * d) : 0.0;
+        }
+        if ((lane & 15) == 0) ts[4 * b + (lane >> 4)] = has ? t[idx[smp]] : 0.0;
+        if (lane == 0) rows[b] = r0;
+    }
+    __syncthreads();
+    // Sums of a quad's four nodes over all samples: one wave, sixteen lanes per node.
+    for (int k = wave; k < n_rows; k += BLOCK / 64) {
+        int lo = 0, hi = n_groups - 1;  // first group that reaches the quad
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (g_row[mid] + kQuads64 > k) hi = mid; else lo = mid + 1;
+        }
+        int last = lo;
+        while (last + 1 < n_groups && g_row[last + 1] <= k) ++last;
+        const int s = k & (kQuads64 - 1);
+        const double* from = frag + 64 * (s >> 2) + 4 * (s & 3) + (lane & 3);
+        double v = 0.0;
+        for (int b = g_block[lo] + (lane >> 2); b < g_block[last + 1]; b += 16)
+            for (int i = 0; i < 4; ++i) v += from[(int64_t)b * 128 + 16 * i];
+        for (int o = 4; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
+        if (lane < 4) bsum[4 * k + lane] = v;
+    }
+    __syncthreads();
+    double sq = 0.0, sb = 0.0;
+    if (tid < kSumThreads)
+        for (int q = tid; q < 4 * n_rows; q += kSumThreads) {
+            const double b = bsum[q];
+            sq = fma(b, b, sq);
+            sb += b;
+        }
+    sq = block_sum(sq, red);
+    sb = block_sum(sb, red);
+    const int cap = md.mode_cap, L = 3 * cap + 32;
+    double* ev = psh;
+    double* ct = psh + L;
+    double* cs = ct + L;
+    series_coefficients<BLOCK>(P.sigma_t, cap, ev, ct, cs);
+    __syncthreads();
+    if (tid == 0) {
+        int m = cap;
+        double tail = 0.0;
+        for (; m > 1; --m) {
+            tail += cs[m];
+            if (tail > kModeTail64) break;
+        }
+        m = min(m, md.max_groups * kModeGroup64);
+        ired[0] = m;
+        M.groups = (m + kModeGroup64 - 1) / kModeGroup64;
+        M.blocks = n_blocks;
+        M.nodes = 0;
+        M.c0 = cs[0];
+        M.sj0 = kNodeW64 * sq;
+        M.n0 = kNodeP64 * sb;
+        md.curves[c] = M;
+        cp[c].ipy = kInvSqrt2Pi / P.sigma_y * M.sj0 / ((double)n * (double)n);
+    }
+    __syncthreads();
+    const int keep = ired[0];
+    double* coef = md.coef + (int64_t)c * mode_stride(cap);
+    for (int m = tid + 1; m <= mode_stride(cap); m += BLOCK)
+        coef[m - 1] = m <= keep ? cs[m] : 0.0;
+}
+
+template <int BLOCK, int EMAX>
+hipError_t launch_prepare64_b(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
+                              const double* t, const double* y, const ModeDev& md) {
+    const int room = sort_room(BLOCK, max_n);
+    const int key_bytes = 8 * std::max(room, 2 * (3 * md.mode_cap + 32) + md.mode_cap + 2);
+    const int group_room = mode64_room(max_n);
+    const size_t lds = (size_t)key_bytes + 4 * (size_t)(room + 4 * group_room + 2);
+    prepare64_kernel<BLOCK, EMAX><<<n_curves, BLOCK, lds, st>>>(cp, t, y, room, key_bytes,
+                                                                group_room, md);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_prepare64(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
+                            const double* t, const double* y, const ModeDev& md) {
+    if (n_curves <= 0) return hipSuccess;
+    if (!sort_big(n_curves, max_n))
+        return launch_prepare64_b<kSortBlock, kSortE>(st, cp, n_curves, max_n, t, y, md);
+    return launch_prepare64_b<kSortBlockBig, kSortEBig>(st, cp, n_curves, max_n, t, y, md);
+}
 
 hipError_t launch_prepare(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
                           const double* t, const double* y, const double* e, double skew_lambda,
