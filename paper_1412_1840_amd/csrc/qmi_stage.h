@@ -24,7 +24,7 @@
 
 namespace qmi {
 
-constexpr size_t kStageMin = size_t(64) << 10;   // held by every context
+constexpr size_t kStageMin = size_t(256) << 10;  // held by every context (a one-curve search)
 constexpr size_t kStageMax = size_t(32) << 20;   // most page-locked memory of a context
 // Bytes a thread moves at a time: 60 MB in and 39 MB out take 5.2, 4.4, 4.1, 4.4 and 4.5 ms in
 // chunks of 0.5, 1, 2, 4 and 8 MB, with 4 to 14 threads.
