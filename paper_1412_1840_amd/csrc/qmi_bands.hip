@@ -7,7 +7,7 @@
 // The pair kernel then scores the per-curve trial lists (frequency plan kind 3).
 #include <math.h>
 
-#include "qmi_internal.h"
+#include "qmi_modes.h"
 #include "qmi_sort.h"
 
 namespace qmi {
@@ -132,11 +132,13 @@ bands_prep_kernel(const CurveParams* __restrict__ cp, const double* __restrict__
 // point from the folded phase x - rint(x), x = f t, and steps to the next points by multiplying
 // with exp(2 pi i df t) (one complex product per point instead of a sine and a cosine; the
 // rounding error grows by a few ulp per step).  Blocks walk (curve, band, grid tile).
+// Bound: FP64 instructions, six per point and sample and 40 per run for its first value.  Measured,
+// 3 windows of 30 000 points of 768 curves (about 62 samples a band): 1.36 ms, against 1.76 with
+// sincospi and unfused products.
 constexpr int kWinRun = 16;
 
 __device__ __forceinline__ void cis2pi(double x, double& c, double& s) {
-    const double p = x - rint(x);
-    sincospi(2.0 * p, &s, &c);
+    sincos_turns(x - rint(x), &s, &c);
 }
 
 __global__ void __launch_bounds__(kWindowBlock)
@@ -168,8 +170,8 @@ window_kernel(const CurveParams* __restrict__ cp, int tiles, BandsDev bd) {
         for (int g = 0; g < kWinRun; ++g) {
             re[g] += zr;
             im[g] += zi;
-            const double nr = zr * w.x - zi * w.y;
-            zi = zr * w.y + zi * w.x;
+            const double nr = fma(zr, w.x, -(zi * w.y));
+            zi = fma(zr, w.y, zi * w.x);
             zr = nr;
         }
     }
