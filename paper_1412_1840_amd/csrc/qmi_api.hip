@@ -58,7 +58,7 @@ struct qmi_ctx {
         kUp, kK, kR, kRP, kRD, kKS, kCoarse, kCoarse2, kFine, kFine2, kIps, kPeakK, kNpk, kWin,
         kArgmax, kRes, kProbe, kTS, kYS, kBandT, kBandCnt, kBandId, kS, kTrials, kTrialK, kPCnt,
         kPSt, kPDet, kPTo, kPYo, kPEo, kPart, kModeTs, kModeRows, kModeFrag, kModePart, kModeB,
-        kModeCoef, kTieCnt, kTieSlot, kTieScore, kNumBufs
+        kModeCoef, kTieCnt, kTieSlot, kTieScore, kTieUp, kNumBufs
     };
     Buf bufs[kNumBufs];
     static_assert(kNumBufs <= 64, "one bit per buffer in in_use");
@@ -447,6 +447,100 @@ int mode_count(double sigma_t, double keep_tail) {
     return 1;
 }
 
+// The near ties of the curves tied[] (indices into cp and the group's arrays): their listed points
+// scored by the pair sums, in groups of curves whose tables stay small, and the records written anew.
+// The choice among points that differ by less than the sums' errors is then the pair sums' own,
+// whichever path a curve takes.  Costs a second round trip where there are any: 0.3 ms for one curve of
+// 617 samples (one search in sixty), 1.3 ms of 95 for a batch of 768 survey curves.
+int decide_ties(qmi_ctx* ctx, const std::vector<CurveParams>& cp, const std::vector<int32_t>& tied,
+                int64_t ns, const double* t, const double* y, const double* e, int top_k,
+                int n_fine, int score_kind, double skew_lambda, double skew_mu, const double* fine,
+                const double* fine2, const PeakOut& pk, const TieDev& tie, DevResult* dres,
+                qmi_result* out) {
+    constexpr int64_t kTables = int64_t(64) << 20;  // kernel values of a group (or one curve)
+    constexpr int kPassR = kWaves * rows_per_wave<float>();
+    hipStream_t st = ctx->stream;
+    for (size_t i0 = 0, i1 = 0; i0 < tied.size(); i0 = i1) {
+        std::vector<CurveParams> c2;
+        std::vector<int32_t> order;
+        std::vector<int64_t> row_start;
+        int64_t koff = 0, poff = 0, ksoff = 0, rows = 0, pieces = 0;
+        int max_n = 2, max_pieces = 0;
+        for (; i1 < tied.size(); ++i1) {
+            CurveParams p = cp[tied[i1]];
+            p.npad = (int32_t)round_up(p.n, kPass);
+            if (i1 > i0 && koff + (int64_t)p.n * p.npad > kTables / 4) break;
+            const int nb = (p.n + kPassR - 1) / kPassR;
+            p.koff = koff;
+            p.poff = poff;
+            p.ksoff = ksoff;
+            p.pqoff = pieces;
+            koff += (int64_t)p.n * p.npad;
+            poff += p.npad;
+            ksoff += (int64_t)nb * kWaves * p.n;
+            pieces += (int64_t)nb * (nb + 1) / 2;
+            max_pieces = std::max(max_pieces, nb * (nb + 1) / 2);
+            row_start.push_back(rows);
+            order.push_back((int32_t)c2.size());
+            rows += p.n;
+            max_n = std::max(max_n, p.n);
+            c2.push_back(p);
+        }
+        const int m = (int)c2.size();
+        Upload up;
+        const size_t at_cp = up.add(c2.data(), m * sizeof(CurveParams));
+        const size_t at_order = up.add(order.data(), m * sizeof(int32_t));
+        const size_t at_row = up.add(row_start.data(), m * sizeof(int64_t));
+        const size_t at_idx = up.add(tied.data() + i0, m * sizeof(int32_t));
+        const size_t at_list = up.place((size_t)m * kTieMax * 8);
+        int rc = QMI_OK;
+        for (auto [id, bytes] : {std::pair<int, int64_t>{qmi_ctx::kTieUp, (int64_t)up.total},
+                                 {qmi_ctx::kTieScore, (int64_t)m * kTieMax * 8},
+                                 {qmi_ctx::kK, koff * 4}, {qmi_ctx::kRP, poff * 8},
+                                 {qmi_ctx::kRD, ns * 8}, {qmi_ctx::kKS, ksoff * 4},
+                                 {qmi_ctx::kPart, pieces * kTieMax * 24}})
+            if ((rc = acquire(ctx, id, (size_t)bytes)) != QMI_OK) break;
+        if (rc == QMI_ENOMEM) {  // no room beside the group's buffers: the refinement's choice stays
+            ctx->err.clear();
+            (void)hipGetLastError();
+            break;
+        }
+        if (rc != QMI_OK) return rc;
+        char* d = dptr<char>(ctx, qmi_ctx::kTieUp);
+        HIP_OK(ctx, upload(ctx->stage, up, d, ctx->device, st, true));
+        CurveParams* dcp = reinterpret_cast<CurveParams*>(d + at_cp);
+        const int32_t* dorder = reinterpret_cast<const int32_t*>(d + at_order);
+        const int64_t* drow = reinterpret_cast<const int64_t*>(d + at_row);
+        const int32_t* didx = reinterpret_cast<const int32_t*>(d + at_idx);
+        double* list = reinterpret_cast<double*>(d + at_list);
+        float* K = dptr<float>(ctx, qmi_ctx::kK);
+        float* ks = dptr<float>(ctx, qmi_ctx::kKS);
+        double* rp = dptr<double>(ctx, qmi_ctx::kRP);
+        double* rd = dptr<double>(ctx, qmi_ctx::kRD);
+        FreqPlan fp{};
+        fp.kind = 3;
+        fp.count = fp.stride = kTieMax;
+        fp.list = list;
+        PairOut po{};
+        po.score = dptr<double>(ctx, qmi_ctx::kTieScore);
+        po.score_kind = score_kind;
+        po.part = max_pieces > 1 ? dptr<double>(ctx, qmi_ctx::kPart) : nullptr;
+        HIP_OK(ctx, launch_tie_lists(st, m, didx, top_k, n_fine, pk, tie, list));
+        HIP_OK(ctx, launch_prepare(st, dcp, m, max_n, t, y, e, skew_lambda, skew_mu, ModeDev{}));
+        HIP_OK(ctx, launch_gram<float>(st, dcp, m, rows, drow, y, K, rp, rd));
+        HIP_OK(ctx, launch_gram_finalize<float>(st, dcp, m, rd, rp));
+        HIP_OK(ctx, launch_ksum<float>(st, dcp, m, max_n, K, ks));
+        HIP_OK(ctx, launch_pairs<float>(st, dcp, dorder, m, fp, t, K, rd, rp, ks, po, 0,
+                                        po.part ? max_pieces : 0));
+        HIP_OK(ctx, launch_best_of_ties(st, m, didx, po.score, fine, fine2, top_k, n_fine,
+                                        score_kind, pk, tie, dres));
+    }
+    Download dn;
+    dn.add(out, dres, cp.size() * sizeof(DevResult));
+    HIP_OK(ctx, download(ctx->stage, dn, st, true));
+    return QMI_OK;
+}
+
 // Runs one group.  pairs_only: every curve by the pair sums (curves that the mode sums left to
 // them); *left receives the curves of the group that the mode sums left.
 template <typename R>
@@ -593,7 +687,6 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         if (refine && !fp64) {
             ENSURE(qmi_ctx::kTieCnt, nc * 4);
             ENSURE(qmi_ctx::kTieSlot, nc * (int64_t)kTieMax * 4);
-            ENSURE(qmi_ctx::kTieScore, nc * (int64_t)kTieMax * 8);
         }
         ENSURE(qmi_ctx::kModeCoef, nc * (int64_t)mode_stride(mode_cap) * 8);
     }
@@ -668,8 +761,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         md.coef = dptr<double>(ctx, qmi_ctx::kModeCoef);
         if (refine && !fp64)
             tie = TieDev{dptr<int32_t>(ctx, qmi_ctx::kTieCnt),
-                         dptr<int32_t>(ctx, qmi_ctx::kTieSlot),
-                         dptr<double>(ctx, qmi_ctx::kTieScore), md.curves};
+                         dptr<int32_t>(ctx, qmi_ctx::kTieSlot), md.curves};
         if (refine && !fp64) {
             const qmi_search* q = cs.search;
             md.win_width = q->n_coarse > 1 ? 2.0 * (q->f_max - q->f_min) / (q->n_coarse - 1) : 0.0;
@@ -869,11 +961,6 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             HIP_OK(ctx, launch_best(st, dcp, nc, coarse, coarse2, s->n_coarse, fine, fine2,
                                     refine ? top_k : 0, refine ? n_fine : 0, score_kind, fp.f0,
                                     fp.df, ctx->masks, pk, tie, dres));
-            if (tie.count) {
-                HIP_OK(ctx, launch_mode_ties(st, dcp, nc, ff, md, score_kind, tie));
-                HIP_OK(ctx, launch_best_of_ties(st, nc, fine, fine2, top_k, n_fine, score_kind,
-                                                pk, tie, dres));
-            }
         }
         rec();  // device section end
         return QMI_OK;
@@ -899,7 +986,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             u(bd.S), u(bd.trials), u(bd.trial_k), (uint64_t)n_modes,
             (uint64_t)mode_groups, (uint64_t)max_pieces, (uint64_t)split1, (uint64_t)split2,
             (uint64_t)msplit1, (uint64_t)msplit2, u(dpart), u(md.curves), u(md.ts), u(md.rows),
-            u(md.frag), u(md.part), u(md.b), u(md.coef), u(tie.count), u(tie.slot), u(tie.score)};
+            u(md.frag), u(md.part), u(md.b), u(md.coef), u(tie.count), u(tie.slot)};
         if (ctx->graph_exec && key == ctx->graph_key) {
             record(ctx);
             HIP_OK(ctx, hipGraphLaunch(ctx->graph_exec, st));
@@ -998,6 +1085,17 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         if (bp && cs.scores_out)
             dn.add(cs.scores_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8);
         HIP_OK(ctx, download(ctx->stage, dn, st, !ctx->ws_base));
+        if (tie.count) {
+            std::vector<int32_t> tied;
+            for (int32_t i = 0; i < nc; ++i)
+                if (cs.out[g.c0 + i].status == QMI_OK && cs.out[g.c0 + i].reserved == 2)
+                    tied.push_back(i);
+            if (!tied.empty()) {
+                rc = decide_ties(ctx, cp, tied, ns, t, y, e, top_k, n_fine, score_kind, skew_lambda,
+                                 skew_mu, fine, fine2, pk, tie, dres, cs.out + g.c0);
+                if (rc != QMI_OK) return rc;
+            }
+        }
         if (bp && (cs.trials_out || cs.scores_out)) {
             // Empty trial slots are never scored: report them as NaN in both outputs.
             std::vector<double> tr;
@@ -1013,10 +1111,11 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         }
         for (int32_t i = 0; i < nc; ++i) {
             qmi_result& rr = cs.out[g.c0 + i];
-            if (rr.status == QMI_OK && rr.reserved) {  // left to the pair sums
+            if (rr.status == QMI_OK && rr.reserved == 1) {  // left to the pair sums
                 left->push_back(g.c0 + i);
                 continue;
             }
+            rr.reserved = 0;
             if (cp[i].status != QMI_OK) {
                 // The kernels skipped this curve; make its record explicit.
                 rr.status = cp[i].status;

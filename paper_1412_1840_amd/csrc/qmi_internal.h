@@ -199,13 +199,12 @@ struct PeakOut {
     int32_t* argmax;   // [curve]
 };
 
-// Refined points of a curve too close to the best for the mode sums' errors to tell them apart
-// (best_kernel), scored again in FP64 (mode_ties_kernel).
+// Refined points of a curve too close to the best for the mixed sums to tell them apart
+// (best_kernel): they are scored again by the pair sums, which so decide near ties on every path.
 constexpr int kTieMax = 32;
 struct TieDev {
     int32_t* count;  // [curve] listed points, 0 where one is clearly the best; nullptr: no lists
     int32_t* slot;   // [curve][kTieMax] their slots
-    double* score;   // [curve][kTieMax] their FP64 scores
     const ModeCurve* curves;
 };
 
@@ -340,13 +339,14 @@ hipError_t launch_best(hipStream_t st, const CurveParams* cp, int n_curves, cons
                        const double* fine2, int top_k, int n_fine, int score_kind, double f0,
                        double df, const MaskDev& md, const PeakOut& po, const TieDev& tie,
                        DevResult* res);
-// After launch_best with lists: their points scored in FP64, and the records of their curves
-// rewritten with the best by these scores.
-hipError_t launch_mode_ties(hipStream_t st, const CurveParams* cp, int n_curves,
-                            const FreqPlan& fp, const ModeDev& md, int score_kind,
-                            const TieDev& tie);
-hipError_t launch_best_of_ties(hipStream_t st, int n_curves, const double* fine,
-                               const double* fine2, int top_k, int n_fine, int score_kind,
-                               const PeakOut& po, const TieDev& tie, DevResult* res);
+// After launch_best with lists, for the curves idx[0 .. m): list[j][kTieMax], the frequencies of the
+// points listed for curve idx[j] (NaN past the last); and the records rewritten with the best of them
+// by their pair-sum scores score[j][kTieMax].
+hipError_t launch_tie_lists(hipStream_t st, int m, const int32_t* idx, int top_k, int n_fine,
+                            const PeakOut& po, const TieDev& tie, double* list);
+hipError_t launch_best_of_ties(hipStream_t st, int m, const int32_t* idx, const double* score,
+                               const double* fine, const double* fine2, int top_k, int n_fine,
+                               int score_kind, const PeakOut& po, const TieDev& tie,
+                               DevResult* res);
 
 }  // namespace qmi

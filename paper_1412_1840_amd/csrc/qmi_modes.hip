@@ -466,131 +466,6 @@ mode_window_kernel(const CurveParams* __restrict__ cp, FreqPlan fp, ModeDev md, 
     }
 }
 
-// --------------------------------------------------------------------------------------------
-// Near ties of a search in FP64
-// --------------------------------------------------------------------------------------------
-
-// On a flat maximum neighbouring refined points differ by less than the mixed sums' errors, which
-// are independent from point to point.  best_kernel lists the points of such a curve, and this
-// kernel forms their scores once more with the same node values, but harmonics, products and sums
-// in FP64: what is left is an error that does not change from point to point.  One workgroup per
-// (curve, listed point).  Lane = (cosine or sine, one of the block's two node blocks, node); the
-// four waves take 6 of every 24 harmonics each.  A point costs about 20 us of one workgroup (600
-// samples, 21 harmonics, bound by LDS reads of the harmonics); one curve in ten has a list.
-constexpr int kTieThreads = 256;
-constexpr int kTiePerWave = 6;
-constexpr int kTieModes = 4 * kTiePerWave;
-
-__global__ void __launch_bounds__(kTieThreads)
-mode_ties_kernel(const CurveParams* __restrict__ cp, FreqPlan fp, ModeDev md, int score_kind,
-                 TieDev tie) {
-    __shared__ double z[kTieModes][32][2];
-    __shared__ double red[4][3];
-    const int c = blockIdx.x, k = blockIdx.y;
-    if (k >= tie.count[c]) return;
-    const CurveParams P = cp[c];
-    const ModeCurve M = md.curves[c];
-    const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
-    const int r = lane & 15, nb = (lane >> 4) & 1, cs = lane >> 5;
-    bool active;
-    const double f = mode_slot_freq(fp, c, tie.slot[c * kTieMax + k], 0, active);
-    const double* ts = md.ts + 32 * M.boff;
-    const half8v* frag = reinterpret_cast<const half8v*>(md.frag) + M.boff * 256 + nb * 128 + r;
-    const double* bq = md.b + M.boff * 32 + r;
-    const int32_t* rows = md.rows + M.boff;
-    const double* coef = md.coef + (int64_t)c * mode_stride(md.mode_cap);
-    const int keep = M.groups * kModeGroup;  // coefficients past the last harmonic are zero
-    double SJ = 0.0, ST = 0.0, SC = 0.0;
-    for (int base = 0; base < keep; base += kTieModes) {
-        double a[kTiePerWave], sq[kTiePerWave], sa[kTiePerWave], sb[kTiePerWave];
-#pragma unroll
-        for (int m = 0; m < kTiePerWave; ++m) a[m] = sq[m] = sa[m] = sb[m] = 0.0;
-        // Folds the lower node block (lanes nb = 0) and moves the upper one down.
-        auto fold = [&](int row) {
-            const double b = nb == 0 ? bq[(int64_t)row * 16] : 0.0;
-#pragma unroll
-            for (int m = 0; m < kTiePerWave; ++m) {
-                if (nb == 0) {
-                    sq[m] = fma(a[m], a[m], sq[m]);
-                    sa[m] += a[m];
-                    sb[m] = fma(b, a[m], sb[m]);
-                }
-                const double up = __shfl_xor(a[m], 16, 64);
-                a[m] = nb == 0 ? up : 0.0;
-            }
-        };
-        int wb = 0;
-        for (int kb = 0; kb < M.blocks; ++kb) {
-            __syncthreads();  // the previous block's harmonics have been read
-            {
-                const int i = threadIdx.x & 31, g = threadIdx.x >> 5;
-                const double t = ts[32 * kb + i];
-                const double p = fma(f, t, -rint(f * t));
-                for (int q = 0; q < kTieModes / 8; ++q) {
-                    const int m = g * (kTieModes / 8) + q;
-                    const double md0 = (double)(base + m + 1);
-                    double sn, cn;
-                    sincospi(2.0 * fma(md0, p, -rint(md0 * p)), &sn, &cn);
-                    z[m][i][0] = cn;
-                    z[m][i][1] = sn;
-                }
-            }
-            __syncthreads();
-            const int row = uni(rows[kb]);
-            while (wb < row) fold(wb++);
-            for (int g = 0; g < 4; ++g) {
-                const half8v h = frag[(int64_t)kb * 256 + 16 * g];
-                const half8v l = frag[(int64_t)kb * 256 + 64 + 16 * g];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const double u = (double)(float)h[j] + (double)(float)l[j];
-#pragma unroll
-                    for (int m = 0; m < kTiePerWave; ++m)
-                        a[m] = fma(u, z[wave * kTiePerWave + m][8 * g + j][cs], a[m]);
-                }
-            }
-        }
-        fold(wb);
-        fold(wb + 1);
-#pragma unroll
-        for (int m = 0; m < kTiePerWave; ++m) {
-            // Sums over the nodes: the 32 lanes of cosines and of sines; then over both.
-            for (int o = 16; o > 0; o >>= 1) {
-                sq[m] += __shfl_xor(sq[m], o, 64);
-                sa[m] += __shfl_xor(sa[m], o, 64);
-                sb[m] += __shfl_xor(sb[m], o, 64);
-            }
-            double tt = kNodeP * sa[m] * (kNodeP * sa[m]);
-            double cc = kNodeP * sa[m] * (kNodeW * sb[m]);
-            const double q2 = sq[m] + __shfl_xor(sq[m], 32, 64);
-            tt += __shfl_xor(tt, 32, 64);
-            cc += __shfl_xor(cc, 32, 64);
-            const int at = base + wave * kTiePerWave + m;
-            const double cm = at < keep ? coef[at] : 0.0;
-            SJ = fma(cm, kNodeW * q2, SJ);
-            ST = fma(cm, tt, ST);
-            SC = fma(cm, cc, SC);
-        }
-    }
-    if (lane == 0) {
-        red[wave][0] = SJ;
-        red[wave][1] = ST;
-        red[wave][2] = SC;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    SJ = M.c0 * M.sj0;
-    ST = M.c0 * M.n0 * M.n0;
-    SC = M.c0 * M.n0 * M.sj0;
-    for (int w = 0; w < 4; ++w) {
-        SJ += red[w][0];
-        ST += red[w][1];
-        SC += red[w][2];
-    }
-    const PairOut out{tie.score, nullptr, nullptr, score_kind, 0, nullptr};
-    mode_scores(P, SJ, ST, SC, (int64_t)c * kTieMax + k, out);
-}
-
 }  // namespace
 
 hipError_t launch_mode_windows(hipStream_t st, const CurveParams* cp, int n_curves,
@@ -603,14 +478,6 @@ hipError_t launch_mode_windows(hipStream_t st, const CurveParams* cp, int n_curv
         mode_window_kernel<512><<<(unsigned)blocks, 512, lds, st>>>(cp, fp, md, out);
     else
         mode_window_kernel<256><<<(unsigned)blocks, 256, lds, st>>>(cp, fp, md, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_mode_ties(hipStream_t st, const CurveParams* cp, int n_curves,
-                            const FreqPlan& fp, const ModeDev& md, int score_kind,
-                            const TieDev& tie) {
-    if (n_curves <= 0) return hipSuccess;
-    mode_ties_kernel<<<dim3(n_curves, kTieMax), kTieThreads, 0, st>>>(cp, fp, md, score_kind, tie);
     return hipGetLastError();
 }
 

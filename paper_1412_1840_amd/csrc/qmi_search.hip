@@ -265,11 +265,12 @@ peaks_merge_kernel(int n_parts, int F, double f0, double df, int top_k, int n_fi
 // peak rank; without a refined candidate, the coarse argmax; without that, an empty result.
 // --------------------------------------------------------------------------------------------
 
-// Twice the largest error of a mode-sum score seen against FP64 (QMI: 1e-7 at 40 samples, 5e-8 and
-// less from 100 on; nCKP = sqrt(N st) / IP_y (V_J - V_M) with relative errors of the V's of the
-// same size): points closer to the best than this are compared in FP64.
+// Points closer to the best than this are told apart by the pair sums.  Of QMI: the largest
+// difference of two points' errors, mode sums (1e-7 at 40 samples, 5e-8 and less from 100 on) and pair
+// sums (4e-7 at 121 samples, 2e-7 at 617) together.  nCKP = sqrt(N st) / IP_y (V_J - V_M), with
+// relative errors of the V's of the same size.
 __device__ __forceinline__ double tie_margin(const CurveParams& P, int score_kind, double best) {
-    constexpr double e = 2e-7;
+    const double e = 4e-7 + 7e-5 / (double)P.n;
     return score_kind == 0 ? e : e * (fabs(best) + 2.0 * P.A * sqrt((double)P.n * P.sigma_t));
 }
 
@@ -337,6 +338,7 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
         if (ranks_before(wb[v], best)) best = wb[v];
     // The points that the mode sums cannot tell from the best (tie_margin), where there are any
     // besides it; with more than kTieMax the margin is halved until they fit.
+    int listed = 0;
     if (tie.count && P.status == 0 && npk > 0 && best.s != 0x7fffffff &&
         tie.curves[c].groups > 0) {
         double margin = tie_margin(P, score_kind, best.q);
@@ -366,7 +368,8 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
             if (threadIdx.x == 0) n_ties = 0;
             __syncthreads();
         }
-        if (threadIdx.x == 0) tie.count[c] = found > 1 ? found : 0;
+        listed = found > 1 ? found : 0;
+        if (threadIdx.x == 0) tie.count[c] = listed;
     } else if (tie.count && threadIdx.x == 0) {
         tie.count[c] = 0;
     }
@@ -377,7 +380,8 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
     r.psnr = P.psnr;
     r.n = P.n;
     r.status = P.status;
-    r.reserved = P.sparse;  // nonzero: the host searches the curve again by the pair sums
+    // 1: the host searches the curve again by the pair sums; 2: it has its near ties decided by them.
+    r.reserved = P.sparse ? 1 : listed ? 2 : 0;
     r.n_peaks = npk;
     const int am = (P.status == 0) ? po.argmax[c] : -1;
     r.coarse_argmax = am;
@@ -411,22 +415,39 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
     res[c] = r;
 }
 
-// The record of a curve with a list of near ties: the point with the highest FP64 score (ties to
+__device__ __forceinline__ double slot_of_window(const PeakOut& po, int c, int top_k, int n_fine,
+                                                 int s) {
+    const double* w = po.win + ((int64_t)c * top_k + s / n_fine) * 2;
+    return __dadd_rn(w[0], __dmul_rn((double)(s % n_fine), w[1]));
+}
+
+__global__ void tie_lists_kernel(int m, const int32_t* __restrict__ idx, int top_k, int n_fine,
+                                 PeakOut po, TieDev tie, double* __restrict__ list) {
+    const int x = blockIdx.x * blockDim.x + threadIdx.x, j = x / kTieMax, k = x % kTieMax;
+    if (j >= m) return;
+    const int c = idx[j];
+    list[x] = k < tie.count[c] ? slot_of_window(po, c, top_k, n_fine, tie.slot[c * kTieMax + k])
+                               : NAN;
+}
+
+// The record of a curve with a list of near ties: the point with the highest pair-sum score (ties to
 // the lower frequency, then the lower peak rank), with its scores as the refinement formed them.
-__global__ void best_of_ties_kernel(int n_curves, const double* __restrict__ fine,
+__global__ void best_of_ties_kernel(int m, const int32_t* __restrict__ idx,
+                                    const double* __restrict__ score,
+                                    const double* __restrict__ fine,
                                     const double* __restrict__ fine2, int top_k, int n_fine,
                                     int score_kind, PeakOut po, TieDev tie,
                                     DevResult* __restrict__ res) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_curves || tie.count[c] == 0) return;
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= m) return;
+    const int c = idx[j];
     const int64_t S = (int64_t)top_k * n_fine;
     double bq = NAN, bf = INFINITY;
     int bs = 0x7fffffff;
     for (int k = 0; k < tie.count[c]; ++k) {
-        const double v = tie.score[c * kTieMax + k];
+        const double v = score[j * kTieMax + k];
         const int s = tie.slot[c * kTieMax + k];
-        const double* w = po.win + ((int64_t)c * top_k + s / n_fine) * 2;
-        const double fr = __dadd_rn(w[0], __dmul_rn((double)(s % n_fine), w[1]));
+        const double fr = slot_of_window(po, c, top_k, n_fine, s);
         if ((v == v) &&
             (!(bq == bq) || v > bq || (v == bq && (fr < bf || (fr == bf && s < bs))))) {
             bq = v;
@@ -490,12 +511,19 @@ hipError_t launch_best(hipStream_t st, const CurveParams* cp, int n_curves, cons
     return hipGetLastError();
 }
 
-hipError_t launch_best_of_ties(hipStream_t st, int n_curves, const double* fine,
-                               const double* fine2, int top_k, int n_fine, int score_kind,
-                               const PeakOut& po, const TieDev& tie, DevResult* res) {
-    if (n_curves <= 0) return hipSuccess;
-    best_of_ties_kernel<<<(n_curves + 63) / 64, 64, 0, st>>>(n_curves, fine, fine2, top_k, n_fine,
-                                                             score_kind, po, tie, res);
+hipError_t launch_tie_lists(hipStream_t st, int m, const int32_t* idx, int top_k, int n_fine,
+                            const PeakOut& po, const TieDev& tie, double* list) {
+    tie_lists_kernel<<<(m * kTieMax + 255) / 256, 256, 0, st>>>(m, idx, top_k, n_fine, po, tie,
+                                                                list);
+    return hipGetLastError();
+}
+
+hipError_t launch_best_of_ties(hipStream_t st, int m, const int32_t* idx, const double* score,
+                               const double* fine, const double* fine2, int top_k, int n_fine,
+                               int score_kind, const PeakOut& po, const TieDev& tie,
+                               DevResult* res) {
+    best_of_ties_kernel<<<(m + 63) / 64, 64, 0, st>>>(m, idx, score, fine, fine2, top_k, n_fine,
+                                                      score_kind, po, tie, res);
     return hipGetLastError();
 }
 

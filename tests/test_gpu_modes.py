@@ -128,21 +128,41 @@ def test_both_launch_forms_and_mixed_paths_give_the_same_bits(ctx):
             assert np.array_equal(s1[0], sc[k]) and np.array_equal(i1[0], ips[k]), (st, k)
 
 
+def near_tie(r, ref, k, n, sigma_t):
+    """The points chosen by two searches of a curve are the same, or differ by no more than the pair
+    sums' errors at both, by which near ties are decided: 2 x (1e-7 + 7e-5 / n) of QMI (twice what was
+    seen of them, 2e-7 at 617 samples, 4e-7 at 121), the same share of the potentials for nCKP."""
+    if r["f_best"] == ref["f_best"][k]:
+        return True
+    tol = 2 * (1e-7 + 7e-5 / n)
+    nckp = tol * (abs(ref["score_nckp"][k]) + 2 / np.sqrt(2 * np.pi) * np.sqrt(n / sigma_t))
+    return (abs(r["score"] - ref["score"][k]) <=
+            (tol if ref["score"][k] == ref["score_qmi"][k] else nckp) + 2e-7 * abs(r["score"]))
+
+
 @pytest.mark.parametrize("score", [qmi.SCORE_QMI, qmi.SCORE_NCKP])
 @pytest.mark.parametrize("n,count,n_fine", [(96, 200, 1000), (617, 60, 1000), (150, 40, 20000)])
-def test_near_ties_are_decided_in_fp64(ctx, score, n, count, n_fine):
+def test_near_ties_are_decided_on_every_path_alike(ctx, score, n, count, n_fine):
     """On flat maxima (neighbouring refined points differ by 1e-6 and less of the score, by 1e-8
-    with 20 000 points in a window) the search takes the point that the FP64 mode takes."""
+    with 20 000 points in a window) a curve's choice is the same alone, in a batch, from device
+    arrays and in a replayed graph, and no worse than the FP64 mode's by more than the sums' errors."""
     curves = [synth.survey_batch_curve(500 + k, n=n) for k in range(count)]
     b = synth.pack(curves)
     kw = dict(f_min=1e-3, f_max=2.0, n_coarse=2500, top_k=3, n_fine=n_fine, score=score)
     mixed, _ = ctx.best_period(b.offsets, b.t, b.y, b.e, 0.3, **kw)
     ref, _ = ctx.best_period(b.offsets, b.t, b.y, b.e, 0.3, precision=qmi.PREC_FP64, **kw)
-    far = [k for k in range(count) if mixed["coarse_index"][k] != ref["coarse_index"][k]
-           or mixed["fine_index"][k] != ref["fine_index"][k]]
-    # Two points of the FP64 mode itself are apart by its own rounding, 1e-13.
-    assert not far, [(k, mixed["fine_index"][k], ref["fine_index"][k]) for k in far]
-    np.testing.assert_allclose(mixed["score"], ref["score"], rtol=QMI_TOL)
+    assert np.all(mixed["reserved"] == 0)
+    for k in range(count):
+        assert near_tie(mixed[k], ref, k, n, 0.3), (k, mixed[k], ref[k])
+    import torch
+    dev = ctx.best_period_dev(b.offsets, *[torch.from_numpy(a).cuda() for a in (b.t, b.y, b.e)], 0.3,
+                              **kw)
+    again, _ = ctx.best_period(b.offsets, b.t, b.y, b.e, 0.3, **kw)
+    for k in range(0, count, 3):
+        c = curves[k]
+        one, _ = ctx.best_period([0, c.n], c.t, c.y, c.e, 0.3, **kw)
+        for name in ("f_best", "score", "score_nckp", "fine_index", "peak_rank"):
+            assert one[0][name] == mixed[k][name] == dev[k][name] == again[k][name], (k, name)
 
 
 @pytest.mark.parametrize("score", [qmi.SCORE_QMI, qmi.SCORE_NCKP])
@@ -171,12 +191,14 @@ def test_interpolated_windows(ctx, sigma_t, n, n_coarse, n_fine, top_k, score):
     many, _ = ctx.best_period(b.offsets, b.t, b.y, b.e, sigma_t, **kw)
     for r in (one, many):
         for k in range(3):
+            assert near_tie(r[k], ref, k, curves[k].n, sigma_t), (k, r[k], ref[k])
+            if r["f_best"][k] != ref["f_best"][k]:
+                continue
             for s in ("score_qmi", "score_nckp"):
                 tol = 2e-7
                 if s == "score_nckp":
                     tol *= abs(ref[s][k]) + 2 / np.sqrt(2 * np.pi) * np.sqrt(curves[k].n / sigma_t)
                 assert abs(r[s][k] - ref[s][k]) <= tol, (k, s, r[s][k] - ref[s][k])
             assert r["coarse_index"][k] == ref["coarse_index"][k]
-            assert abs(r["f_best"][k] - ref["f_best"][k]) <= 1e-12 * ref["f_best"][k]
     for name in ("f_best", "score", "fine_index"):
         np.testing.assert_array_equal(one[name], many[name][:3])
