@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Throughput of the kernelised-periodogram period search on one MI355X.
 
-A step is one full coarse-to-fine search (prologue, magnitude Gram matrix, 20k-frequency coarse
+A step is one full coarse-to-fine search (widths and node tables, 20k-frequency coarse
 periodogram, top-10 peak selection, 10 x 1000 refinement, best-of) over a resident batch of 4096
 seeded survey-like lightcurves (N uniform in 300..1000, half periodic).  Prints one JSON line.
 
@@ -21,17 +21,24 @@ import numpy as np  # noqa: E402
 
 METRIC = "lightcurves/sec (N~600, 20k freqs) vs plain; Gpairs/s % VALU peak; p99 ms"
 
-# VALU roofline of the pair sums, from unit counts: each pair x frequency item needs 6 FP32 VALU
-# instructions (a multiply and two FMAs for the squared half-angle sine, two adds and an FMA for
-# the three accumulations) and one v_exp_f32.  The VALU issues one FP32 instruction per lane per
-# clock (packed FP32 is not used), 256 CUs x 4 SIMDs x 16 lanes at 2.4 GHz, and in the pair body the
-# exp overlaps the other VALU work (the valu_rates probe measures the body at 90% of this bound, far
-# above the 8-slot count of an exp at its own half rate), so the ceiling is 6 issue slots per item.
-PEAK_ITEMS_PER_S = 256 * 64 * 2.4e9 / 6.0
-# FP32 flops per item (FMA = 2) against MI355X's published FP32 vector peak, which counts packed
-# (two-wide) FP32 instructions.
-FLOP_PER_ITEM = 10.0
-PUBLISHED_FP32_FLOPS = 157.3e12
+# The searches sum over harmonics and magnitude nodes on the matrix units (modes_kernel): per curve,
+# frequency, block of 32 samples and group of 7 harmonics 84 matrix instructions of 16 x 16 x 32 for 16
+# frequencies.  Peak: MI355X's dense half-precision figure.
+MODE_GROUP = 7
+MODE_FLOP = 84 * 2 * 16 * 16 * 32 / 16.0
+PEAK_MATRIX_FLOPS = 2.5e15
+# Pair x frequency items per second that the pair sums could reach, whose items the calls' pair_items
+# count: 6 FP32 VALU issue slots per item, 256 CUs x 4 SIMDs x 16 lanes at 2.4 GHz.  The mode sums pass
+# it, with fewer operations per item the longer a curve is.
+PAIR_BOUND_ITEMS_PER_S = 256 * 64 * 2.4e9 / 6.0
+
+
+def mode_groups(sigma_t, tail=1e-8):
+    """Groups of harmonics of exp(-2 sin^2(x / 2) / sigma_t^2) down to the given tail."""
+    x = 2 * np.pi * np.arange(4096) / 4096
+    c = 2 * np.fft.rfft(np.exp((np.cos(x) - 1) / sigma_t ** 2)).real / 4096
+    tails = np.cumsum(c[::-1])[::-1]
+    return int(math.ceil(np.nonzero(tails > tail)[0].max() / MODE_GROUP))
 
 
 def parse():
@@ -307,11 +314,12 @@ def survey_report(qmi, synth, n_curves, batch=2048):
     ctx.close()
     return {"curves": n_curves, "batch": batch, "host_inputs": True, "status_ok": ok,
             "value": n_curves / dt * 3600.0, "unit": "lightcurves/hour",
-            "gpairs_per_s": items / dt / 1e9, "roofline_frac_wall": items / dt / PEAK_ITEMS_PER_S}
+            "gpairs_per_s": items / dt / 1e9,
+            "ratio_to_pair_bound_wall": items / dt / PAIR_BOUND_ITEMS_PER_S}
 
 
 def length_sweep(qmi, synth, lengths, tile=0):
-    """Pair-kernel rate by curve length: a resident batch of equal-length curves of the survey
+    """Rate of the sums by curve length: a resident batch of equal-length curves of the survey
     generator (enough of them for at least ~2e13 pair x frequency items, at most 4096), the
     coarse-to-fine search of the survey batch, HIP-event time of the pair launches."""
     import torch
@@ -339,41 +347,37 @@ def length_sweep(qmi, synth, lengths, tile=0):
         rate = s["pair_items"] / (s["pair_kernel_ms"] * 1e-3)
         print(json.dumps({"n": n, "curves": nc, "pair_items": s["pair_items"],
                           "pair_kernel_ms": s["pair_kernel_ms"], "items_per_s": rate,
-                          "frac_of_peak": rate / PEAK_ITEMS_PER_S, "variant": s["pair_variant"],
+                          "ratio_to_pair_bound": rate / PAIR_BOUND_ITEMS_PER_S, "variant": s["pair_variant"],
                           "wall_items_per_s": s["pair_items"] / dt,
                           "lightcurves_per_s": nc / dt}), flush=True)
         ctx.close()
         del T, Y, E
 
 
-def roofline_object(achieved, probe, pair_ms, launches, traffic, variant):
-    """The pair kernel against the 6-slot VALU issue bound, with the rates the probe measured in
-    this run beside it: the kernel's own column body (as compiled and with the exp-interleaving
-    hint), one exp with 6 and 7 independent FMAs, exp and FMA alone."""
-    measured = None
-    best = None
-    if probe:
-        mix = probe.get("mix_items_per_s", {})
-        measured = {"pair_body": probe.get("pair_items_per_s"),
-                    "pair_body_interleaved": probe.get("pair_hint_items_per_s"),
-                    "mix_1exp_6fma": mix.get("6"), "mix_1exp_7fma": mix.get("7"),
-                    "exp_alone": probe.get("exp_per_s"), "fma_alone": probe.get("fma_per_s"),
-                    "clock_mhz_reported": probe.get("clock_mhz")}
-        cands = [v for k, v in measured.items()
-                 if k.startswith(("pair", "mix_1exp_6")) and v]
-        best = max(cands) if cands else None
-    return {"bound": "alu", "achieved": achieved / 1e9, "peak": PEAK_ITEMS_PER_S / 1e9,
-            "unit": "G pair*freq items/s", "frac": achieved / PEAK_ITEMS_PER_S,
-            "peak_basis": "6 FP32 VALU issue slots per item, 256 CUs x 64 lanes x 2.4 GHz",
-            "best_measured_ceiling": best and best / 1e9,
-            "frac_of_best_measured": best and achieved / best,
-            "measured_rates_per_s": measured,
-            "fp32_flop_per_item": FLOP_PER_ITEM,
-            "frac_of_published_fp32_peak": achieved * FLOP_PER_ITEM / PUBLISHED_FP32_FLOPS,
+def roofline_object(achieved, lengths, n_coarse, sigma_t, probe, kernel_ms, launches, traffic,
+                    variant):
+    """The mode sums against the matrix units' dense half-precision peak: the operations of the
+    coarse grid alone (whole blocks of 32 samples; the refinement's frequencies and the blocks lost
+    to the ends of groups are left out), over the time of both launches."""
+    blocks = float(np.sum((np.asarray(lengths) + 31) // 32))
+    flop = MODE_FLOP * mode_groups(sigma_t) * blocks * n_coarse
+    passes = launches / 2.0  # coarse and refinement launches
+    rate = flop * passes / (kernel_ms * 1e-3) if kernel_ms > 0 else float("nan")
+    return {"bound": "matrix", "achieved": rate / 1e12, "peak": PEAK_MATRIX_FLOPS / 1e12,
+            "unit": "TFLOP/s (half precision, dense)", "frac": rate / PEAK_MATRIX_FLOPS,
+            "peak_basis": "MI355X dense half-precision figure; the vector instructions that form "
+                          "and split the harmonics take the other half of the issue slots",
+            "pair_items_per_s": achieved,
+            "ratio_to_pair_bound": achieved / PAIR_BOUND_ITEMS_PER_S,
+            "pair_bound_items_per_s": PAIR_BOUND_ITEMS_PER_S,
+            "measured_valu_rates_per_s": probe and {
+                "exp_alone": probe.get("exp_per_s"), "fma_alone": probe.get("fma_per_s"),
+                "pair_body": probe.get("pair_items_per_s"),
+                "clock_mhz_reported": probe.get("clock_mhz")},
             "traffic": traffic,
             "traffic_unit": "HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, calibrated)",
-            "kernel": "pairs_kernel<float>", "variant": variant, "launches": launches,
-            "avg_launch_ms": pair_ms / max(launches, 1)}
+            "kernel": "modes_kernel<false>", "variant": variant, "launches": launches,
+            "avg_launch_ms": kernel_ms / max(launches, 1)}
 
 
 def main():
@@ -529,7 +533,7 @@ def main():
         metric_point = {"n": 600, "n_curves": mb.n_curves,
                         "value": mb.n_curves * a.metric_point_steps / mdt,
                         "unit": "lightcurves/s", "gpairs_per_s": mitems / mdt / 1e9,
-                        "roofline_frac_wall": mitems / mdt / PEAK_ITEMS_PER_S}
+                        "ratio_to_pair_bound_wall": mitems / mdt / PAIR_BOUND_ITEMS_PER_S}
         del MT, MY, ME
 
     # The all-FP64 path (QMI_PREC_FP64) on the first curves of the batch: the cost of full
@@ -648,7 +652,8 @@ def main():
                                   wl["f_min"], wl["f_max"], st_),
                    "n_curves": nc, "samples": int(batch.offsets[-1])},
         "gpairs_per_s": items / a.steps / (dt / a.steps) / 1e9,
-        "roofline": roofline_object(achieved, probe, pair_ms, launches,
+        "roofline": roofline_object(achieved, np.diff(batch.offsets), wl["n_coarse"], st_, probe,
+                                    pair_ms, launches,
                                     measured_traffic(a.workload, nc, variant), variant),
         "graph": graph,
         "bands": bands,

@@ -24,7 +24,8 @@
  *
  * Units: t in days, f in 1/day, y and e in magnitudes.  All floating-point arguments and results
  * are IEEE double.  Inside, the phase fold frac(f t) and the final scores are FP64; in the default
- * mixed precision the kernel values and the pair sums run in FP32 with FP64 block accumulation.
+ * mixed precision the sums over samples run on half-precision pairs (22 bits) and FP32 accumulation
+ * in short runs, with FP64 beyond.
  *
  * Error behaviour: every function returns QMI_OK (0) or a negative QMI_E* code.  A call-level error
  * leaves every output buffer untouched and records a message for qmi_last_error.  A problem with
@@ -67,8 +68,8 @@ extern "C" {
 #define QMI_SCORE_CS_QMI 0
 #define QMI_SCORE_NCKP 1
 
-/* Arithmetic of the pair sums. */
-#define QMI_PREC_MIXED 0 /* FP64 fold + FP32 kernel values + FP32 short sums folded into FP64 */
+/* Arithmetic of the sums. */
+#define QMI_PREC_MIXED 0 /* FP64 fold + FP32 values + FP32 short sums folded into FP64 */
 #define QMI_PREC_FP64 1  /* every step in FP64 */
 /* Negative control for precision studies, not for use: QMI_PREC_MIXED with the phase fold
  * f t - rint(f t) taken in FP32 instead of FP64.  Over long baselines at high frequencies f t
@@ -208,12 +209,12 @@ typedef struct {
 } qmi_thresholds;
 
 /* Timing of the last qmi_periodogram / qmi_best_period call on this context, from HIP events on the
- * context stream (pair kernels only, and the whole device section). */
+ * context stream (the sums' launches only, and the whole device section). */
 typedef struct {
-    double pair_kernel_ms;   /* summed duration of the pair-sum kernel launches */
+    double pair_kernel_ms;   /* summed duration of the launches that form the sums */
     double device_ms;        /* first kernel start to last kernel end */
     double pair_items;       /* sum over curves of N(N-1)/2 x evaluated frequencies */
-    int32_t pair_launches;   /* number of pair-sum kernel launches */
+    int32_t pair_launches;   /* number of launches that form the sums */
     int32_t used_graph;      /* 1 if the device section ran as a captured hipGraph */
     int32_t pair_variant;    /* pair-kernel variant used (autotuned unless QMI_OPT_TILE is set) */
     int32_t reserved;
