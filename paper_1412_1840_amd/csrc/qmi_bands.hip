@@ -4,7 +4,7 @@
 // Per curve: samples in time order, equal-count magnitude bands, the bands ranked by the summed
 // absolute first derivative of their samples, the spectral window of each kept band's sample times
 // on a linear grid (FP64), and the band's highest local maxima of the window as trial frequencies.
-// The pair kernel then scores the per-curve trial lists (frequency plan kind 3).
+// The mode or pair sums then score the per-curve trial lists (frequency plan kind 3).
 #include <math.h>
 
 #include "qmi_modes.h"

@@ -56,7 +56,7 @@ struct CurveParams {
     double bk;     // diagonal value of the stored K table (B rounded to the kernel type)
     double sjc;    // sum_{i<j} K(i,j)            (FP64, from the stored K table)
     int64_t pqoff; // first piece of this curve in a one-piece-per-workgroup launch's partial sums
-    int32_t sparse; // set by nodes_kernel: magnitudes too scattered for the mode sums
+    int32_t sparse; // set by the preparation: magnitudes too scattered for the mode sums
     int32_t pad;
 };
 

@@ -1,6 +1,6 @@
 // HIP kernels for gfx950 (MI355X): magnitude Gram matrix, column K sums and the pair x frequency
-// sums (FP64 mode, and mixed mode where the mode sums do not pay).  The peak search and best-of kernels are in
-// qmi_search.hip.
+// sums, of the curves that the mode sums (qmi_modes.hip, qmi_modes64.hip) do not take and of near
+// ties.  The peak search and best-of kernels are in qmi_search.hip.
 //
 // Method: Protopapas et al., arXiv:1412.1840.  Gaussian kernel (Sec. 2), periodic kernel and the
 // warp identity ||u_f(z) - u_f(y)||^2 = 4 sin^2(pi f (z - y)) (Sec. 2.1), CKP and information

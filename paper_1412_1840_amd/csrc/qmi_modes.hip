@@ -106,8 +106,9 @@ __device__ __forceinline__ float4v mfma(half8v a, half8v b, float4v c) {
 // wave issues 84 MFMAs (17 cycles each) and about 460 other VALU instructions (two thirds of them
 // conversions, FP64 and sines at 5 to 9 cycles), and the two overlap only in part (a conversion
 // issued between MFMAs costs 2.7 of its 4.8 cycles): 3100 cycles of a SIMD.  Measured, 768 survey
-// curves (N 300..1000), 20 000 + 10 x 1000 frequencies: 125 ms against 1033 ms by the pair sums,
-// 8.2 times; one curve of 8192 samples at 1000 frequencies 1.7 against 7.6 ms.  Errors against
+// curves (N 300..1000): 20 000 + 10 x 1000 frequencies 125 ms against 1010 ms by the pair sums, and
+// 93 ms with the windows interpolated; one curve of 8192 samples at 1000 frequencies 0.39 ms, its
+// preparation 0.33, against 7.6.  Errors against
 // FP64 are below the pair sums' (QMI 3e-9 against 5e-8 rms at N = 617), but for V_J, IP_t and V_C
 // where most phases coincide and N > 2000 (5e-8 against 1e-8: FP32 accumulation over more blocks).
 constexpr int kModeWaves = 4;
