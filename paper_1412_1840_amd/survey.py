@@ -218,8 +218,8 @@ SOURCES = {
     "long_baseline": synth.long_baseline_curve,
 }
 
-# VALU issue bound of the pair sums: 256 CUs x 64 FP32 lanes x 2.4 GHz / 6 FP32 VALU instructions
-# per pair x frequency item (the exp overlaps them).
+# Issue bound of the pair sums: 6 FP32 VALU slots per pair x frequency item, 256 CUs x 64 lanes at
+# 2.4 GHz.  The mode sums that most curves take pass it (the fractions below are then above 1).
 PEAK_ITEMS_PER_S = 256 * 64 * 2.4e9 / 6.0
 
 
