@@ -1041,6 +1041,46 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         if (rc_sec != QMI_OK) return rc_sec;
     }
 
+    if (tune_now) {
+        // Time the four variants (2 or 4 waves per SIMD, 64- or 32-column chunks; they give the
+        // same bits, so tuning never changes a result) on the largest curves of this group (the
+        // first in LPT order) over a slice of the same frequency plan, into a scratch output, and
+        // keep the fastest for this length bucket.  Here, before near ties are decided: that takes
+        // over the pair sums' buffers, and may free them to let them grow.
+        const int pc = std::min(n_pairs, 48);
+        FreqPlan probe = fp;
+        probe.count = (int32_t)std::min<int64_t>(F1, 64 * 24);
+        // The kernel writes slot s of curve c (a curve id, not its rank in the work order) at
+        // c * count + s, so the scratch output must cover every curve id of the group.
+        int rc2 = ensure(ctx, qmi_ctx::kProbe, (size_t)nc * probe.count * 8);
+        if (rc2 != QMI_OK) return rc2;
+        PairOut pout{dptr<double>(ctx, qmi_ctx::kProbe), nullptr, nullptr, score_kind, 0};
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        HIP_OK(ctx, hipEventCreate(&e0));
+        HIP_OK(ctx, hipEventCreate(&e1));
+        float best_ms = 0.f;
+        int best_v = 0;
+        for (int v = 0; v < nvar; ++v) {
+            HIP_OK(ctx,
+                   launch_pairs<R>(st, dcp, dorder + n_modes, pc, probe, t, K, rd, rp, ks, pout, v, 0));
+            HIP_OK(ctx, hipEventRecord(e0, st));
+            for (int rep = 0; rep < 2; ++rep)
+                HIP_OK(ctx,
+                       launch_pairs<R>(st, dcp, dorder + n_modes, pc, probe, t, K, rd, rp, ks, pout, v, 0));
+            HIP_OK(ctx, hipEventRecord(e1, st));
+            HIP_OK(ctx, hipEventSynchronize(e1));
+            float ms = 0.f;
+            HIP_OK(ctx, hipEventElapsedTime(&ms, e0, e1));
+            if (v == 0 || ms < best_ms) {
+                best_ms = ms;
+                best_v = v;
+            }
+        }
+        (void)hipEventDestroy(e0);
+        (void)hipEventDestroy(e1);
+        ctx->tuned[bucket] = best_v;
+    }
+
     // Results back to the caller.
     if (cs.periodogram) {
         std::vector<CurveParams> cpo(nc);
@@ -1143,44 +1183,6 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
                                                                        g.c0 + i)))
                 ctx->stats.pair_items += (double)n * (double)(n - 1) / 2.0 * (double)F1;
         }
-    }
-    if (tune_now) {
-        // Time the four variants (2 or 4 waves per SIMD, 64- or 32-column chunks; they give the
-        // same bits, so tuning never changes a result) on the largest curves of this group (the
-        // first in LPT order) over a slice of the same frequency plan, into a scratch output, and
-        // keep the fastest for this length bucket.
-        const int pc = std::min(n_pairs, 48);
-        FreqPlan probe = fp;
-        probe.count = (int32_t)std::min<int64_t>(F1, 64 * 24);
-        // The kernel writes slot s of curve c (a curve id, not its rank in the work order) at
-        // c * count + s, so the scratch output must cover every curve id of the group.
-        int rc2 = ensure(ctx, qmi_ctx::kProbe, (size_t)nc * probe.count * 8);
-        if (rc2 != QMI_OK) return rc2;
-        PairOut pout{dptr<double>(ctx, qmi_ctx::kProbe), nullptr, nullptr, score_kind, 0};
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        HIP_OK(ctx, hipEventCreate(&e0));
-        HIP_OK(ctx, hipEventCreate(&e1));
-        float best_ms = 0.f;
-        int best_v = 0;
-        for (int v = 0; v < nvar; ++v) {
-            HIP_OK(ctx,
-                   launch_pairs<R>(st, dcp, dorder + n_modes, pc, probe, t, K, rd, rp, ks, pout, v, 0));
-            HIP_OK(ctx, hipEventRecord(e0, st));
-            for (int rep = 0; rep < 2; ++rep)
-                HIP_OK(ctx,
-                       launch_pairs<R>(st, dcp, dorder + n_modes, pc, probe, t, K, rd, rp, ks, pout, v, 0));
-            HIP_OK(ctx, hipEventRecord(e1, st));
-            HIP_OK(ctx, hipEventSynchronize(e1));
-            float ms = 0.f;
-            HIP_OK(ctx, hipEventElapsedTime(&ms, e0, e1));
-            if (v == 0 || ms < best_ms) {
-                best_ms = ms;
-                best_v = v;
-            }
-        }
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
-        ctx->tuned[bucket] = best_v;
     }
     (void)fp64;
     return QMI_OK;
