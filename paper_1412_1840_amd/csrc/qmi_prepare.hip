@@ -95,6 +95,13 @@ constexpr int tile_waves() {
 }
 constexpr int kTileBytes = 4096;
 
+// LDS bytes of the sort keys, which the series tables (2 L + cap + 1 doubles) take over: a multiple
+// of 16, since the operand tiles that follow are read 16 bytes at a time.
+int key_bytes_of(int room, int mode_cap) {
+    const int series = mode_cap ? 2 * (3 * mode_cap + 32) + mode_cap + 2 : 0;
+    return (8 * std::max(room, series) + 15) / 16 * 16;
+}
+
 // Bound: latency (one curve per call: a chain of sorts, scans and reductions by one workgroup),
 // FP64 exponentials where one workgroup has a long curve.  Measured against separate prologue and
 // node kernels with sorts in LDS and one exponential per node and sample: one curve of 617 samples
@@ -105,7 +112,7 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
                const double* __restrict__ y_all, const double* __restrict__ e_all,
                double skew_lambda, double skew_mu, int room, int key_bytes, int group_room,
                ModeDev md) {
-    extern __shared__ double psh[];
+    extern __shared__ __attribute__((aligned(16))) double psh[];
     __shared__ double red[kSumThreads / 64];
     __shared__ int ired[BLOCK / 64];
     __shared__ int bad;
@@ -435,8 +442,8 @@ hipError_t launch_prepare_b(hipStream_t st, CurveParams* cp, int n_curves, int m
                             const double* t, const double* y, const double* e,
                             double skew_lambda, double skew_mu, const ModeDev& md) {
     const int room = sort_room(BLOCK, max_n);
-    const int L = 3 * md.mode_cap + 32;
-    const int key_bytes = 8 * std::max(room, md.curves ? 2 * L + md.mode_cap + 2 : 0);
+    const int key_bytes = key_bytes_of(room, md.curves ? md.mode_cap : 0);
+    if (key_bytes % (int)sizeof(half8v) != 0) return hipErrorInvalidValue;
     const int group_room = max_n / 5 + 1;
     size_t lds = (size_t)key_bytes + 4 * (size_t)room;
     if (md.curves)
@@ -457,7 +464,7 @@ __global__ void __launch_bounds__(BLOCK)
 prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
                  const double* __restrict__ y_all, int room, int key_bytes, int group_room,
                  ModeDev md) {
-    extern __shared__ double psh[];
+    extern __shared__ __attribute__((aligned(16))) double psh[];
     __shared__ double red[kSumThreads / 64];
     __shared__ int ired[BLOCK / 64];
     const int c = blockIdx.x, tid = threadIdx.x;
@@ -621,7 +628,7 @@ template <int BLOCK, int EMAX>
 hipError_t launch_prepare64_b(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
                               const double* t, const double* y, const ModeDev& md) {
     const int room = sort_room(BLOCK, max_n);
-    const int key_bytes = 8 * std::max(room, 2 * (3 * md.mode_cap + 32) + md.mode_cap + 2);
+    const int key_bytes = key_bytes_of(room, md.mode_cap);
     const int group_room = mode64_room(max_n);
     const size_t lds = (size_t)key_bytes + 4 * (size_t)(room + 4 * group_room + 2);
     prepare64_kernel<BLOCK, EMAX><<<n_curves, BLOCK, lds, st>>>(cp, t, y, room, key_bytes,
