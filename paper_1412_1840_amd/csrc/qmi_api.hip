@@ -600,10 +600,10 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             all_p += np;
             all_ks += (int64_t)((p.n + kPassR - 1) / kPassR) * kWaves * p.n;
         }
-        const int whole = (p.n + 31) / 32 + 2;
+        const int expect = mode_expect(p.n);
         if (p.status == QMI_OK && mode_groups > 0 &&
             (fp64 ? mode64_takes(p.n, mode_groups)
-                  : whole <= mode_even(p.n, mode_groups) && whole <= p.n / 5)) {
+                  : expect <= mode_even(p.n, mode_groups) && expect <= p.n / 5)) {
             ModeCurve& m = mc[i];
             m.cap = fp64 ? mode64_room(p.n) : mode_room(p.n, mode_groups);
             m.boff = mblocks;

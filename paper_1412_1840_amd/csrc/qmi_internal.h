@@ -63,19 +63,21 @@ struct CurveParams {
 // Mode sums (qmi_modes.hip).  Samples are taken in magnitude order in blocks of 32 that reach the
 // same two blocks of 16 nodes; a block and each of its node blocks make a 16 x 32 operand of the
 // matrix unit, in two half-precision parts.
-// Harmonics are kept until the rest of the series is below this share of the kernel's value where
-// phases coincide (1): a third of half a unit in the last place of single precision.
+// Groups of harmonics are kept until the rest of the series is below this share of the kernel's value
+// where phases coincide (1); the rest goes with the last harmonic.
 constexpr double kModeTail = 1e-8;
 constexpr int kModeGroup = 7;      // harmonics per pass over the samples
 constexpr int kModeCapMax = 256;     // most harmonics (sigma_t from 0.03)
-// Blocks with which the mode sums take the pair sums' time; the host gives a curve to the mode sums
-// when its whole blocks and two more are no more than that.  Measured per curve and frequency (4096
-// frequencies, batches): the pair sums take 9.2e-5 n^2 + 0.008 n + 0.25 ns, the mode sums 0.1 ns
-// per block and group of harmonics, so they meet at n = 40, 72, 290 and 520 for sigma_t = 0.6, 0.3,
-// 0.1 and 0.05 (2, 3, 9 and 17 groups).
+// Blocks with which the mode sums take the pair sums' time.  Measured per curve and frequency (4096
+// frequencies, batches of 256 curves): the pair sums take 9.2e-5 n^2 + 0.008 n + 0.25 ns, the mode sums
+// 0.107 ns per block and group of harmonics and 0.2 ns.  The host gives a curve to the mode sums when
+// the blocks it probably has are no more than that: its whole blocks and two more, and one per 200
+// samples (the node blocks that a longer curve's narrower sigma_y adds).  They meet at n = 32, 64, 107,
+// 200, 350 and 690 for sigma_t = 2, 0.6, 0.3, 0.2, 0.1 and 0.05 (1, 2, 3, 5, 9 and 17 groups).
 inline int mode_even(int n, int groups) {
-    return (int)((9.2e-4 * n * n + 0.08 * n + 2.5) / groups);
+    return (int)((8.6e-4 * n * n + 0.075 * n + 0.5) / groups);
 }
+inline int mode_expect(int n) { return (n + 31) / 32 + 2 + n / 200; }
 // Blocks a curve has room for: the preparation gives a curve back to the pair sums when its samples
 // are so scattered over node blocks that they need more.  Twice the blocks of equal time, since
 // such a curve runs in launches of its own; n / 5 bounds the tables by the size of the pair sums'
@@ -89,13 +91,17 @@ __host__ __device__ constexpr int mode_stride(int cap) {
     return (cap + kModeGroup - 1) / kModeGroup * kModeGroup;
 }
 
-// Node spacing in units of sigma_y: the trapezoid error 2 exp(-pi^2 / (2 h^2)) is 5e-9 of a kernel
-// value and alternates in sign along the magnitudes, so that it averages out over the pairs.
-constexpr double kNodeStep = 0.5;
-constexpr double kNodeW = kNodeStep * 0.79788456080286535587989211986876;  // h sqrt(2/pi)
-constexpr double kNodeP = kNodeStep * 0.56418958354775628694807945156077;  // h / sqrt(pi)
+// Node spacing in units of sigma_y: the trapezoid error 2 exp(-pi^2 / (2 h^2)) is 1e-9 of a kernel
+// value and alternates in sign along the magnitudes, so that it averages out over the pairs.  Values of
+// U are held in units of 1 / kNodeScale: the low parts of values down to 1e-5 then are ordinary
+// half-precision numbers (without, what is below 3e-8 is lost, and 4e-9 of sum_q U with it).
+constexpr double kNodeStep = 0.48;
+constexpr double kNodeScale = 16384.0;
+constexpr double kNodeW =  // h sqrt(2/pi), for values of U in units of 1 / kNodeScale
+    kNodeStep * 0.79788456080286535587989211986876 / (kNodeScale * kNodeScale);
+constexpr double kNodeP = kNodeStep * 0.56418958354775628694807945156077 / kNodeScale;  // h / sqrt(pi)
 // A sample uses the 16-node blocks rb and rb + 1, rb chosen so that they hold at least the
-// 2 kReach + 1 nodes nearest to it (beyond, U < exp(-(8.5 h)^2) = 1.5e-8).
+// 2 kReach + 1 nodes nearest to it (beyond, U < exp(-(8.5 h)^2) = 6e-8, which the last node takes over).
 constexpr int kReach = 8;
 // The mode sums in FP64 (qmi_modes64.hip): the same series and nodes, to the rounding of a double.
 // Blocks of four samples that reach the same eight quads of nodes (32 nodes; at least the

@@ -32,11 +32,18 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
 typedef double double2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef short short2v __attribute__((ext_vector_type(2)));
 
-// v_sin_f32 and v_cos_f32 round towards zero: measured over the whole circle, sin^2 + cos^2 is
-// 6.5e-8 below 1 on average.  A harmonic formed by k products from them has its |a|^2 short by
-// (k + 1) times that, which the coefficients make up for.
-constexpr double kTrigLoss = 6.5e-8;
+// exp(2 pi i p), exactly 1 at p = 0.  v_sin_f32 and v_cos_f32 round towards zero (sin^2 + cos^2 is
+// 6.5e-8 below 1 on average): the factor 1 + (1 - sin^2 - cos^2) / 2 puts the value back on the
+// circle, to rounding.
+__device__ __forceinline__ void cis(float p, float& c, float& s) {
+    c = __builtin_amdgcn_cosf(p);
+    s = __builtin_amdgcn_sinf(p);
+    const float e = 0.5f * fmaf(-s, s, fmaf(-c, c, 1.0f));
+    c = fmaf(c, e, c);
+    s = fmaf(s, e, s);
+}
 
 // --------------------------------------------------------------------------------------------
 // Mode sums
@@ -88,31 +95,84 @@ __device__ __forceinline__ float4v mfma(half8v a, half8v b, float4v c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
+// A block's products, small parts first, summed from zero and then added: one rounding of the long
+// sums per block, where products added to them one after the other would be three and more.
+__device__ __forceinline__ void add_block(const float (&v)[8], float minus_one, half8v a0h, half8v a0l,
+                                          half8v a1h, half8v a1l, float4v& acc0, float4v& acc1) {
+    half8v h, l;
+    split8(v, minus_one, h, l);
+    const float4v zero = {0.f, 0.f, 0.f, 0.f};
+    float4v x = mfma(a0l, h, zero), y = mfma(a1l, h, zero);
+    x = mfma(a0h, l, x);
+    y = mfma(a1h, l, y);
+    x = mfma(a0h, h, x);
+    y = mfma(a1h, h, y);
+    acc0 += x;
+    acc1 += y;
+}
+
+// The sums of a wave's nodes: single-precision accumulators, out of which whole units (kNodeScale,
+// one sample at its node) are moved into 16-bit counts every few blocks, so that the accumulators
+// stay small and a long sum is as exact as a short one.
+struct Sum {
+    float4v low;
+    short2v high[2];
+};
+constexpr float kUnit = (float)kNodeScale;
+static_assert(QMI_MAX_N < 32768, "counts of units");
+
+__device__ __forceinline__ void carry(Sum& a) {
+    constexpr float kC = 12582912.0f * kUnit;  // 1.5 2^23 units: rounds to whole units
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {
+        const float x = a.low[r] + kC, y = a.low[r + 1] + kC;
+        a.low[r] -= x - kC;
+        a.low[r + 1] -= y - kC;
+        const unsigned units = __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x),
+                                                     0x05040100);  // the low halves of both
+        short2v v;
+        __builtin_memcpy(&v, &units, 4);
+        a.high[r / 2] += v;
+    }
+}
+
+__device__ __forceinline__ double value(const Sum& a, int r) {
+    return fma((double)(int)a.high[r / 2][r & 1], (double)kUnit, (double)a.low[r]);
+}
+
 // One wave = (curve, 16 frequency slots): lane l works for slot l mod 16 and, in every block of 32
 // samples (in magnitude order), for the samples 8 (l / 16) ... + 7.  Per block it forms
 // exp(2 pi i m f t) of its eight samples for the kModeGroup harmonics of a group, splits them into
 // two half-precision parts and feeds them as the B operand to the matrix unit: hi*hi + hi*lo +
-// lo*hi with the U fragments of the block's two 16-node blocks as A, accumulated in FP32 over the
-// few blocks that a node meets.  Because samples are sorted, a node block that no later sample
-// reaches is folded into the FP64 sums (sum_q a^2, sum_q a, sum_q b a, per lane in LDS) and its
-// registers are taken over by the next.
+// lo*hi with the U fragments of the block's two 16-node blocks as A.  Because samples are sorted, a
+// node block that no later sample reaches is folded into the FP64 sums (sum_q a^2, sum_q a,
+// sum_q b a, per lane in LDS) and its registers are taken over by the next.
 // The harmonic groups of a slot are summed in order; with SPLIT a wave runs one group and stores
 // its sums for mode_epilogue_kernel, which adds them in the same order.
 //
+// Precision.  A value of a harmonic is off by 4e-8 rms (22 bits of its two parts, and single
+// precision before), each sample independently, a block's sum by two roundings of it, a node's sum
+// by one rounding per block of what has come together since the last carry.  Times count from a
+// sample's, so that the values are exact where phases coincide with it.  Measured against FP64 over
+// 64 curves of each length (50 to 3000 samples) at 301 frequencies on [0.001, 10]: relative errors
+// of V_J, IP_t and V_C 0.4 to 0.9 of the pair sums' rms up to 200 samples and 0.1 to 0.5 beyond
+// (N = 617, sigma_t 0.3: 2.5e-9, 1.7e-9 and 2.1e-9 against 1.2e-8, 1.1e-8 and 2.1e-8), of QMI and
+// nCKP less (1.8e-9 against 4.2e-8; 2.4e-8 against 2.2e-7 of the highest nCKP).
+//
 // Why this shape: N^2 / 2 pairs become N x 21 harmonics x 32 nodes (sigma_t 0.3) on the matrix
-// unit.  Seven harmonics are what 256 registers of two waves per SIMD hold (112 accumulators); the
-// 16 x 16 x 32 instruction takes a lane's own eight samples as its B operand, so that the
-// harmonics go from the recurrence to the matrix unit without LDS.  Bound: per block and group a
-// wave issues 84 MFMAs (17 cycles each) and about 460 other VALU instructions (two thirds of them
+// unit.  Seven harmonics are what 256 registers of two waves per SIMD hold (112 accumulators and 56
+// counts); the 16 x 16 x 32 instruction takes a lane's own eight samples as its B operand, so that
+// the harmonics go from the recurrence to the matrix unit without LDS.  Bound: per block and group
+// a wave issues 84 MFMAs (17 cycles each) and about 650 other VALU instructions (half of them
 // conversions, FP64 and sines at 5 to 9 cycles), and the two overlap only in part (a conversion
-// issued between MFMAs costs 2.7 of its 4.8 cycles): 3100 cycles of a SIMD.  Measured, 768 survey
-// curves (N 300..1000): 20 000 + 10 x 1000 frequencies 125 ms against 1010 ms by the pair sums, and
-// 93 ms with the windows interpolated; one curve of 8192 samples at 1000 frequencies 0.39 ms, its
-// preparation 0.33, against 7.6.  Errors against
-// FP64 are below the pair sums' (QMI 3e-9 against 5e-8 rms at N = 617), but for V_J, IP_t and V_C
-// where most phases coincide and N > 2000 (5e-8 against 1e-8: FP32 accumulation over more blocks).
+// issued between MFMAs costs 2.7 of its 4.8 cycles).  Measured, 768 survey curves (N 300..1000),
+// 20 000 + 10 x 1000 frequencies with the windows interpolated: 126 ms of device time against 1010
+// ms by the pair sums.  What the precision costs: 96 ms with products added to the long sums one by
+// one, no carries and the sines as the hardware gives them, but errors of V_J up to 6e-8 at N = 617
+// and 4e-7 at N = 8192; 132 ms with carries every four blocks; 155 ms after every block.
 constexpr int kModeWaves = 4;
 constexpr int kModeThreads = 64 * kModeWaves;
+constexpr int kCarry = 8;   // blocks between carries
 constexpr int kMS = 5;  // FP64 sums per harmonic and lane
 
 template <bool SPLIT>
@@ -162,7 +222,6 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
     const int32_t* rows = md.rows + M.boff;
     const double* coef = md.coef + (int64_t)c * mode_stride(md.mode_cap);
     double (*S)[64] = S_all[wave];
-    const double loss = f != 0.0 ? kTrigLoss : 0.0;  // at f = 0 every value is exactly 1
     float minus_one = -1.0f;
     asm volatile("" : "+s"(minus_one));
 
@@ -170,8 +229,8 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
     if (SPLIT) SJ = ST = SC = 0.0;
     for (int g = g0; g < g_end; ++g) {
         const int m0 = g * kModeGroup + 1;
-        float4v acc[2][kModeGroup][2];
-        const float4v zero = {0.f, 0.f, 0.f, 0.f};
+        Sum acc[2][kModeGroup][2];
+        const Sum zero = {{0.f, 0.f, 0.f, 0.f}, {{0, 0}, {0, 0}}};
 #pragma unroll
         for (int m = 0; m < kModeGroup; ++m) {
             acc[0][m][0] = acc[0][m][1] = acc[1][m][0] = acc[1][m][1] = zero;
@@ -180,11 +239,11 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
         }
         int wb = 0;  // node block held by acc[0]
         // Folds harmonic m of the node block whose sums are (ac, as) and node sums b.
-        auto fold = [&](int m, const float4v& ac, const float4v& as, const double (&b)[4]) {
+        auto fold = [&](int m, const Sum& ac, const Sum& as, const double (&b)[4]) {
             double sq = 0.0, ca = 0.0, sa = 0.0, cb = 0.0, sb = 0.0;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const double x = (double)ac[r], z = (double)as[r];
+                const double x = value(ac, r), z = value(as, r);
                 sq = fma(x, x, sq);
                 sq = fma(z, z, sq);
                 ca += x;
@@ -202,6 +261,7 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
 #pragma unroll
             for (int r = 0; r < 4; ++r) b[r] = bq[(int64_t)row * 16 + r];
         };
+#pragma unroll 1
         for (int kb = 0; kb < M.blocks; ++kb) {
             const int row = uni(rows[kb]);
             while (wb < row) {  // at most two steps
@@ -210,9 +270,13 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
 #pragma unroll
                 for (int m = 0; m < kModeGroup; ++m) {
                     fold(m, acc[0][m][0], acc[0][m][1], b);
-                    acc[0][m][0] = copy4(acc[1][m][0]);
-                    acc[0][m][1] = copy4(acc[1][m][1]);
-                    acc[1][m][0] = acc[1][m][1] = zero;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        acc[0][m][k].low = copy4(acc[1][m][k].low);
+                        acc[0][m][k].high[0] = acc[1][m][k].high[0];
+                        acc[0][m][k].high[1] = acc[1][m][k].high[1];
+                        acc[1][m][k] = zero;
+                    }
                 }
                 ++wb;
             }
@@ -232,18 +296,13 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 tv[j] = fma(f, tv[j], -rint(f * tv[j]));  // the phase, in turns
-                const float q = (float)tv[j];
-                c1[j] = __builtin_amdgcn_cosf(q);
-                s1[j] = __builtin_amdgcn_sinf(q);
+                cis((float)tv[j], c1[j], s1[j]);
             }
             if (g > 0) {
                 const double md0 = (double)m0;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float q = (float)fma(md0, tv[j], -rint(md0 * tv[j]));
-                    C[j] = __builtin_amdgcn_cosf(q);
-                    Sn[j] = __builtin_amdgcn_sinf(q);
-                }
+                for (int j = 0; j < 8; ++j)
+                    cis((float)fma(md0, tv[j], -rint(md0 * tv[j])), C[j], Sn[j]);
             } else {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
@@ -253,21 +312,8 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
             }
 #pragma unroll
             for (int m = 0; m < kModeGroup; ++m) {
-                half8v h, l;
-                split8(C, minus_one, h, l);
-                acc[0][m][0] = mfma(a0h, h, acc[0][m][0]);
-                acc[1][m][0] = mfma(a1h, h, acc[1][m][0]);
-                acc[0][m][0] = mfma(a0h, l, acc[0][m][0]);
-                acc[1][m][0] = mfma(a1h, l, acc[1][m][0]);
-                acc[0][m][0] = mfma(a0l, h, acc[0][m][0]);
-                acc[1][m][0] = mfma(a1l, h, acc[1][m][0]);
-                split8(Sn, minus_one, h, l);
-                acc[0][m][1] = mfma(a0h, h, acc[0][m][1]);
-                acc[1][m][1] = mfma(a1h, h, acc[1][m][1]);
-                acc[0][m][1] = mfma(a0h, l, acc[0][m][1]);
-                acc[1][m][1] = mfma(a1h, l, acc[1][m][1]);
-                acc[0][m][1] = mfma(a0l, h, acc[0][m][1]);
-                acc[1][m][1] = mfma(a1l, h, acc[1][m][1]);
+                add_block(C, minus_one, a0h, a0l, a1h, a1l, acc[0][m][0].low, acc[1][m][0].low);
+                add_block(Sn, minus_one, a0h, a0l, a1h, a1l, acc[0][m][1].low, acc[1][m][1].low);
                 if (m == 0) {
 #pragma unroll
                     for (int j = 0; j < 8; ++j) {
@@ -287,6 +333,15 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
                         C[j] = x;
                         Sn[j] = y;
                     }
+                }
+            }
+            if (kb % kCarry == kCarry - 1) {
+#pragma unroll
+                for (int m = 0; m < kModeGroup; ++m) {
+                    carry(acc[0][m][0]);
+                    carry(acc[0][m][1]);
+                    carry(acc[1][m][0]);
+                    carry(acc[1][m][1]);
                 }
             }
         }
@@ -313,11 +368,12 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
 #pragma unroll
                 for (int k = 0; k < 4; ++k) v[q] += S[m * kMS + q][n16 + 16 * k];
             }
-            const double cm = coef[m0 - 1 + m] * (1.0 + loss * (double)(m + 1));
+            const double cm = coef[m0 - 1 + m];
             const double ca = kNodeP * v[1], sa = kNodeP * v[2];
-            gj = fma(cm, kNodeW * v[0], gj);
-            gt = fma(cm, ca * ca + sa * sa, gt);
-            gc = fma(cm, kNodeW * (ca * v[3] + sa * v[4]), gc);
+            // (at f = 0 every a_qm is b_q: the sums are then exact)
+            gj = fma(cm, f == 0.0 ? M.sj0 : kNodeW * v[0], gj);
+            gt = fma(cm, f == 0.0 ? M.n0 * M.n0 : ca * ca + sa * sa, gt);
+            gc = fma(cm, f == 0.0 ? M.n0 * M.sj0 : kNodeW * (ca * v[3] + sa * v[4]), gc);
         }
         for (int o = 16; o < 64; o <<= 1) {
             gj += __shfl_xor(gj, o, 64);

@@ -284,13 +284,15 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
         }
         return lo;
     };
-    // Times in magnitude order, every group padded to whole blocks.
+    // Times in magnitude order, every group padded to whole blocks; counted from a sample's, so that
+    // phases that coincide are near 0 (qmi_modes.hip).
+    const double t0 = t[idx[n / 2]];
     double* ts = md.ts + 32 * M.boff;
     int32_t* rows = md.rows + M.boff;
     for (int q = tid; q < 32 * n_blocks; q += BLOCK) {
         const int g = group_of(q >> 5);
         const int i = g_first[g] + q - 32 * g_block[g];
-        ts[q] = i < g_first[g + 1] ? t[idx[i]] : 0.0;
+        ts[q] = i < g_first[g + 1] ? t[idx[i]] - t0 : 0.0;
         if ((q & 31) == 0) rows[q >> 5] = g_row[g];
     }
     __syncthreads();  // idx is free from here
@@ -305,8 +307,7 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (wave < tile_waves<BLOCK>()) {
         _Float16* tile = reinterpret_cast<_Float16*>(idx) + wave * (kTileBytes / 2);
-        constexpr double kFall = 0.60653065971263342360379953499118;  // exp(-2 h^2), h = 1/2
-        static_assert(kNodeStep == 0.5, "kFall");
+        const double fall = exp(-2.0 * kNodeStep * kNodeStep);
         for (int b = wave; b < n_blocks; b += tile_waves<BLOCK>()) {
             const int g = group_of(b);
             const int i = lane & 31, nb = lane >> 5;
@@ -314,7 +315,7 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
             double v = 0.0, up = 0.0, down = 0.0;
             if (smp < g_first[g + 1]) {
                 const double d = ((double)(16 * (g_rb[g] + nb) + 8) - pos(smp)) * kNodeStep;
-                v = exp(-d * d);
+                v = kNodeScale * exp(-d * d);
                 up = exp(-2.0 * kNodeStep * d - kNodeStep * kNodeStep);
                 down = exp(2.0 * kNodeStep * d - kNodeStep * kNodeStep);
             }
@@ -325,21 +326,28 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
                 to[r * 8] = h;
                 to[512 + r * 8] = (_Float16)(float)(x - (double)(float)h);
             };
+            // Nodes past either end of the two blocks add their values to the last node, so that
+            // sum_q U is the same for every sample (three of them: the next is below 1e-9 of these).
             put(8, v);
-            double x = v;
+            double x = v, last = 0.0;
 #pragma unroll
-            for (int r = 9; r < 16; ++r) {
+            for (int r = 9; r < 19; ++r) {
                 x *= up;
-                up *= kFall;
-                put(r, x);
+                up *= fall;
+                if (r < 15) put(r, x);
+                else if (r == 15 || nb == 1) last += x;
             }
+            put(15, last);
             x = v;
+            last = 0.0;
 #pragma unroll
-            for (int r = 7; r >= 0; --r) {
+            for (int r = 7; r >= -3; --r) {
                 x *= down;
-                down *= kFall;
-                put(r, x);
+                down *= fall;
+                if (r > 0) put(r, x);
+                else if (r == 0 || nb == 0) last += x;
             }
+            put(0, last);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             const half8v* tv = reinterpret_cast<const half8v*>(tile);
@@ -416,9 +424,12 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
             tail += cs[m];
             if (tail > kModeTail) break;
         }
-        m = min(m, md.max_groups * kModeGroup);
+        M.groups = min((m + kModeGroup - 1) / kModeGroup, md.max_groups);
+        // All harmonics of the groups, and what is left of the series with the last of them, so that
+        // the kernel is 1 where phases coincide.
+        m = M.groups * kModeGroup;
         ired[0] = m;
-        M.groups = (m + kModeGroup - 1) / kModeGroup;
+        for (int k = m + 1; k <= cap; ++k) cs[m] += cs[k];
         M.blocks = n_blocks;
         // Windows are interpolated where that takes at most half of their points (whose score
         // arrays hold the node sums meanwhile).
@@ -430,11 +441,10 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
         cp[c].ipy = kInvSqrt2Pi / sigma_y * M.sj0 / ((double)n * (double)n);
     }
     __syncthreads();
-    // Coefficient of harmonic m at m - 1; zero past the last one kept.
+    // Coefficient of harmonic m at m - 1.
     const int keep = ired[0];
     double* coef = md.coef + (int64_t)c * mode_stride(cap);
-    for (int m = tid + 1; m <= mode_stride(cap); m += BLOCK)
-        coef[m - 1] = m <= keep ? cs[m] : 0.0;
+    for (int m = tid + 1; m <= keep; m += BLOCK) coef[m - 1] = cs[m];
 }
 
 template <int BLOCK, int EMAX>
