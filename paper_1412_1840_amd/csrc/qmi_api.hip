@@ -681,9 +681,9 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     if (n_modes) {
         ENSURE(qmi_ctx::kModeTs, mblocks * (fp64 ? 32 : 256));
         ENSURE(qmi_ctx::kModeRows, mblocks * 4);
-        ENSURE(qmi_ctx::kModeFrag, mblocks * (fp64 ? 1024 : 4096));
+        ENSURE(qmi_ctx::kModeFrag, mblocks * (fp64 ? kTiles64 * 512 : 4096));
         if (!fp64) ENSURE(qmi_ctx::kModePart, mblocks * 256);
-        ENSURE(qmi_ctx::kModeB, mblocks * 256);
+        ENSURE(qmi_ctx::kModeB, mblocks * (fp64 ? kTiles64 * 128 : 256));
         if (refine && !fp64) {
             ENSURE(qmi_ctx::kTieCnt, nc * 4);
             ENSURE(qmi_ctx::kTieSlot, nc * (int64_t)kTieMax * 4);

@@ -104,22 +104,20 @@ constexpr double kNodeP = kNodeStep * 0.56418958354775628694807945156077 / kNode
 // 2 kReach + 1 nodes nearest to it (beyond, U < exp(-(8.5 h)^2) = 6e-8, which the last node takes over).
 constexpr int kReach = 8;
 // The mode sums in FP64 (qmi_modes64.hip): the same series and nodes, to the rounding of a double.
-// Blocks of four samples that reach the same eight quads of nodes (32 nodes; at least the
-// 2 kReach64 + 1 nearest to each sample: beyond, U < exp(-(14.5 h)^2) = 2e-15).
+// Blocks of four samples that reach the same three blocks of 16 nodes: the 2 kReach64 + 1 nodes nearest
+// to each sample at least (beyond, U < exp(-(16.5 h)^2) = 5e-16).
 constexpr double kModeTail64 = 1e-16;
-constexpr int kModeGroup64 = 4;
-constexpr double kNodeStep64 = 0.4;  // trapezoid error 8e-14 of a kernel value, alternating
+constexpr int kModeGroup64 = 3;  // harmonics per pass: their 144 registers of sums leave two waves a SIMD
+constexpr double kNodeStep64 = 0.36;  // trapezoid error 6e-17 of a kernel value
 constexpr double kNodeW64 = kNodeStep64 * 0.79788456080286535587989211986876;
 constexpr double kNodeP64 = kNodeStep64 * 0.56418958354775628694807945156077;
-constexpr int kReach64 = 14;
-constexpr int kQuads64 = 8;
-// Four harmonics per pass take as long as five and half as long as six (whose sums spill): 1.09, 1.09
-// and 2.2 ms for 16 survey curves at 1024 frequencies.
+constexpr int kReach64 = 16;
+constexpr int kTiles64 = 3;
 // Whether the host gives a curve to them.  Measured per curve and frequency (4096 frequencies,
-// batches): the mode sums take 0.0098 n + 0.04 ns per group of harmonics, the pair sums 4.7e-4 n^2;
-// they meet at n = 50, 95, 170, 480 and 1150 for sigma_t = 2, 0.6, 0.3, 0.1 and 0.05 (3, 5, 9, 23
-// and 46 groups).
-inline bool mode64_takes(int n, int groups) { return n >= 20 * groups + groups * groups / 10; }
+// batches): the mode sums take 0.0105 n + 0.1 ns per group of harmonics, the pair sums 4.6e-4 n^2 and
+// up to 1 ns; they meet at n = 138, 245, 690 and 1370 for sigma_t = 0.6, 0.3, 0.1 and 0.05 (7, 11, 29
+// and 56 groups).
+inline bool mode64_takes(int n, int groups) { return n >= 25 * groups - 30; }
 // Blocks a curve has room for: its own, half as many again lost to the ends of groups (more and it
 // is given back to the pair sums).
 inline int mode64_room(int n) { return n / 4 + n / 8 + 8; }
@@ -324,8 +322,9 @@ hipError_t launch_modes(hipStream_t st, const CurveParams* cp, const int32_t* or
 hipError_t launch_mode_epilogue(hipStream_t st, const CurveParams* cp, const int32_t* order,
                                 int n_work_curves, const FreqPlan& fp, const ModeDev& md,
                                 const PairOut& out, int split_groups);
-// The same in FP64.  md: ts [block][4], rows the first node quad of a block (counted among the
-// curve's), frag [block][2][64 lanes] values of U, b [node quad (from 8 boff)][4].
+// The same in FP64.  md: ts [block][4], rows the first of a block's node blocks (counted among the
+// curve's), frag [block][kTiles64][64 lanes] values of U, node block k at k mod kTiles64,
+// b [node block (from kTiles64 boff)][16].
 hipError_t launch_prepare64(hipStream_t st, CurveParams* cp, int n_curves, int max_n,
                             const double* t, const double* y, const ModeDev& md);
 hipError_t launch_modes64(hipStream_t st, const CurveParams* cp, const int32_t* order,

@@ -12,20 +12,24 @@ typedef double double4v __attribute__((ext_vector_type(4)));
 
 // One wave = (curve, 16 frequency slots): lane l works for slot l mod 16 and, in every block of 4
 // samples, for sample l / 16, whose harmonics it feeds as the B operand of the 16 x 16 x 4 matrix
-// instruction; the block's values of U in 32 nodes are two A operands.  The nodes are eight quads;
-// quad k keeps its sums in register k mod 4 of accumulator (k mod 8) / 4, a node per lane group
-// (row 4 i + l / 16 of the result is register i), and when the samples, in magnitude order, move on
-// past it, that register is folded into the lane's sums and taken over by quad k + 8.  So a sample
-// has 32 nodes of which it needs 29, and nothing moves between registers.
+// instruction; the block's values of U in three blocks of 16 nodes are the A operands.  Node block k
+// of a curve keeps its sums in accumulator k mod 3 (register i of lane group g: node 4 i + g); when
+// the samples, in magnitude order, move on past it, they are folded into the lane's sums and the
+// accumulator is taken over by node block k + 3.
+//
+// Three node blocks, so that a sample has the 33 nodes at least that nodes 0.36 sigma_y apart need to
+// the rounding of a double: with two and 0.4 (29 nodes) a kernel value was off by up to 8e-14 where
+// magnitudes all lie at the same place between two nodes (a wide sigma_y, few values), although not
+// where they spread.
 //
 // Bound: FP64 arithmetic.  The matrix instruction takes 64 cycles of a SIMD and shares the FP64
 // units with the vector instructions (measured: 71 cycles of 2.4 GHz, 4.3 more for every fma beside
-// it), 16 of them and about 75 others per block and group of harmonics, 1500 cycles; measured 1700.
-// The pairs take 26 instructions each: N^2 / 2 of them against N times 32 nodes, 2 x 33 harmonics
-// (sigma_t 0.3) and the sines.  Measured, 16 survey curves, 1024 frequencies: 1.1 ms against 3.3
-// (1.15 with sincospi in place of sincos_turns).  Errors against extended precision are the pair
-// sums': QMI 0.5e-15 to 1.7e-15 rms against 0.5e-15 to 2e-15 at N = 300 to 1200 and sigma_t 0.3, and
-// less where both have more harmonics (sigma_t 0.1: 0.8e-15 against 5.8e-15).
+// it), 18 of them and about 70 others per block and group of harmonics, 1600 cycles.
+// The pairs take 26 instructions each: N^2 / 2 of them against N times 48 nodes, 2 x 33 harmonics
+// (sigma_t 0.3) and the sines.  Measured, 16 survey curves, 1024 frequencies: 1.5 ms for the call
+// against 4.3 (1.15 with two node blocks, four harmonics per pass).  Errors against extended precision
+// are a rounding or two: V_J 3e-16 to 9e-16 rms against the pair sums' 4e-16 to 8e-15, IP_t and V_C
+// 2e-16 to 8e-16 against 2e-16 to 7e-16 (N = 121 to 2500, sigma_t 0.05 to 2).
 constexpr int kWaves64 = 4;
 constexpr int kThreads64 = 64 * kWaves64;
 constexpr int kS64 = 5;  // sums per harmonic and lane
@@ -71,8 +75,8 @@ modes64_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ o
     const int g_end = SPLIT ? min(g0 + 1, M.groups) : M.groups;
     if (g0 >= g_end) return;  // no such group, or a curve left to the pair sums
     const double* ts = md.ts + 4 * M.boff + kg;
-    const double* frag = reinterpret_cast<const double*>(md.frag) + 128 * M.boff + lane;
-    const double* bq = md.b + 32 * M.boff + kg;
+    const double* frag = reinterpret_cast<const double*>(md.frag) + 64 * kTiles64 * M.boff + lane;
+    const double* bq = md.b + 16 * kTiles64 * M.boff + kg;
     const int32_t* rows = md.rows + M.boff;
     const double* coef = md.coef + (int64_t)c * mode_stride(md.mode_cap);
     double (*S)[64] = S_all[wave];
@@ -81,44 +85,58 @@ modes64_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ o
     if (SPLIT) SJ = ST = SC = 0.0;
     for (int g = g0; g < g_end; ++g) {
         const int m0 = g * kModeGroup64 + 1;
-        double4v acc[2][kModeGroup64][2];
+        double4v acc[kTiles64][kModeGroup64][2];
 #pragma unroll
         for (int m = 0; m < kModeGroup64; ++m) {
-            acc[0][m][0] = acc[0][m][1] = acc[1][m][0] = acc[1][m][1] = double4v{0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < kTiles64; ++k) acc[k][m][0] = acc[k][m][1] = double4v{0, 0, 0, 0};
 #pragma unroll
             for (int q = 0; q < kS64; ++q) S[m * kS64 + q][lane] = 0.0;
         }
-        int wb = 0;  // first node quad in the registers
-        // Folds the quads before `row`.  One uniform branch per register, each quad's own: a loop
-        // over the quads would have the accumulators merged, and moved, at every turn.
+        int wb = 0, at = 0;  // first node block in the accumulators, and its accumulator
+        // Folds the node blocks before `row`.  One uniform branch per accumulator, each block's own: a
+        // loop over the blocks would have the accumulators merged, and moved, at every turn.
         auto retire_to = [&](int row) __attribute__((always_inline)) {
 #pragma unroll
-            for (int s = 0; s < kQuads64; ++s) {
-                const int quad = wb + ((s - wb) & (kQuads64 - 1));
-                if (quad >= row) continue;
-                const double b = bq[4 * (int64_t)quad];
+            for (int k = 0; k < kTiles64; ++k) {
+                const int blk = wb + (k < at ? k - at + kTiles64 : k - at);
+                if (blk >= row) continue;
+                double b[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) b[r] = bq[16 * (int64_t)blk + 4 * r];
 #pragma unroll
                 for (int m = 0; m < kModeGroup64; ++m) {
-                    const double x = acc[s / 4][m][0][s % 4], z = acc[s / 4][m][1][s % 4];
-                    acc[s / 4][m][0][s % 4] = acc[s / 4][m][1][s % 4] = 0.0;
-                    lds_add(&S[m * kS64 + 0][lane], fma(x, x, z * z));
-                    lds_add(&S[m * kS64 + 1][lane], x);
-                    lds_add(&S[m * kS64 + 2][lane], z);
-                    lds_add(&S[m * kS64 + 3][lane], b * x);
-                    lds_add(&S[m * kS64 + 4][lane], b * z);
+                    double v[kS64] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const double x = acc[k][m][0][r], z = acc[k][m][1][r];
+                        v[0] += fma(x, x, z * z);
+                        v[1] += x;
+                        v[2] += z;
+                        v[3] = fma(b[r], x, v[3]);
+                        v[4] = fma(b[r], z, v[4]);
+                    }
+                    acc[k][m][0] = acc[k][m][1] = double4v{0, 0, 0, 0};
+#pragma unroll
+                    for (int q = 0; q < kS64; ++q) lds_add(&S[m * kS64 + q][lane], v[q]);
                 }
             }
+            at = (at + row - wb) % kTiles64;
             wb = row;
         };
-        double a0 = frag[0], a1 = frag[64], t = ts[0];
+        double a[kTiles64], t = ts[0];
+#pragma unroll
+        for (int k = 0; k < kTiles64; ++k) a[k] = frag[64 * k];
         for (int kb = 0; kb < M.blocks; ++kb) {
             const int row = uni(rows[kb]);
             if (wb < row) retire_to(row);
-            const double u0 = a0, u1 = a1;
+            double u[kTiles64];
+#pragma unroll
+            for (int k = 0; k < kTiles64; ++k) u[k] = a[k];
             const double p = fma(f, t, -rint(f * t));  // the phase, in turns
             if (kb + 1 < M.blocks) {
-                a0 = frag[(int64_t)(kb + 1) * 128];
-                a1 = frag[(int64_t)(kb + 1) * 128 + 64];
+#pragma unroll
+                for (int k = 0; k < kTiles64; ++k) a[k] = frag[((int64_t)(kb + 1) * kTiles64 + k) * 64];
                 t = ts[4 * (kb + 1)];
             }
             // z_m = exp(2 pi i m f t): z_m0 from its own phase, z_m0+1 = z_m0 z_1, and on from there
@@ -128,16 +146,19 @@ modes64_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ o
             C = c1;
             Sn = s1;
             if (g > 0) {
-                const double q = (double)m0 * p;
-                sincos_turns(q - rint(q), &Sn, &C);
+                const double md0 = (double)m0;
+                sincos_turns(fma(md0, p, -rint(md0 * p)), &Sn, &C);
             }
             double Cp = 0.0, Sp = 0.0;
 #pragma unroll
             for (int m = 0; m < kModeGroup64; ++m) {
-                acc[0][m][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(u0, C, acc[0][m][0], 0, 0, 0);
-                acc[1][m][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(u1, C, acc[1][m][0], 0, 0, 0);
-                acc[0][m][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(u0, Sn, acc[0][m][1], 0, 0, 0);
-                acc[1][m][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(u1, Sn, acc[1][m][1], 0, 0, 0);
+#pragma unroll
+                for (int k = 0; k < kTiles64; ++k) {
+                    acc[k][m][0] =
+                        __builtin_amdgcn_mfma_f64_16x16x4f64(u[k], C, acc[k][m][0], 0, 0, 0);
+                    acc[k][m][1] =
+                        __builtin_amdgcn_mfma_f64_16x16x4f64(u[k], Sn, acc[k][m][1], 0, 0, 0);
+                }
                 double x, y;
                 if (m == 0) {
                     x = fma(C, c1, -(Sn * s1));
@@ -153,7 +174,7 @@ modes64_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ o
                 Sn = y;
             }
         }
-        retire_to(wb + kQuads64);
+        retire_to(wb + kTiles64);
         // The four lanes of a slot hold a quarter of its nodes each: lane group kg adds them for
         // the harmonics kg, kg + 4, ... and forms their terms.
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -169,9 +190,10 @@ modes64_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ o
             }
             const double cm = coef[m0 - 1 + m];
             const double ca = kNodeP64 * v[1], sa = kNodeP64 * v[2];
-            gj = fma(cm, kNodeW64 * v[0], gj);
-            gt = fma(cm, ca * ca + sa * sa, gt);
-            gc = fma(cm, kNodeW64 * (ca * v[3] + sa * v[4]), gc);
+            // (at f = 0 every a_qm is b_q: the sums are then exact)
+            gj = fma(cm, f == 0.0 ? M.sj0 : kNodeW64 * v[0], gj);
+            gt = fma(cm, f == 0.0 ? M.n0 * M.n0 : ca * ca + sa * sa, gt);
+            gc = fma(cm, f == 0.0 ? M.n0 * M.sj0 : kNodeW64 * (ca * v[3] + sa * v[4]), gc);
         }
         for (int o = 16; o < 64; o <<= 1) {
             gj += __shfl_xor(gj, o, 64);

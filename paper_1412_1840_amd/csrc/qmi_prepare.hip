@@ -63,6 +63,18 @@ __device__ double sorted_median(const double* a, int n) {
     return (n & 1) ? a[n / 2] : 0.5 * (a[n / 2 - 1] + a[n / 2]);
 }
 
+// Distance (y - y0) inv in two parts, exact but for the rounding of inv (an outlier puts the others
+// far from y0).
+struct Exact {
+    double hi, lo;
+};
+__device__ __forceinline__ Exact node_units(double y, double y0, double inv) {
+    const double s = y - y0, v = s - y;
+    const double err = (y - (s - v)) - (y0 + v);
+    const double x = s * inv;
+    return Exact{x, fma(s, inv, -x) + err * inv};
+}
+
 // Coefficients cs[0..cap] of the periodic kernel's cosine series by the trapezoid rule over the
 // circle (exact up to the coefficients past L - m).  ev, ct: L = 3 cap + 32 entries each.
 template <int BLOCK>
@@ -224,9 +236,9 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
     const double y0 = key[0];
     const double inv = 1.0 / (kNodeStep * sigma_y);
     bool sparse = !((key[n - 1] - y0) * inv < 1e9);  // far more nodes than samples can use
-    // Position of a sample in node units, and its first node block.
-    auto pos = [&](int i) { return (key[i] - y0) * inv + (double)kReach; };
-    auto blk = [&](int i) { return ((int)rint(pos(i)) - kReach) >> 4; };
+    // Position of a sample in node units from node kReach, and its first node block.
+    auto pos = [&](int i) { return node_units(key[i], y0, inv); };
+    auto blk = [&](int i) { return (int)rint(pos(i).hi) >> 4; };
     int n_groups = 0, n_rows = 0, n_blocks = 0;
     if (!sparse) {
         const int per = (n + BLOCK - 1) / BLOCK;
@@ -314,7 +326,9 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
             const int smp = g_first[g] + 32 * (b - g_block[g]) + i;
             double v = 0.0, up = 0.0, down = 0.0;
             if (smp < g_first[g + 1]) {
-                const double d = ((double)(16 * (g_rb[g] + nb) + 8) - pos(smp)) * kNodeStep;
+                const Exact x = pos(smp);
+                const double d =
+                    ((double)(16 * (g_rb[g] + nb) + 8 - kReach) - x.hi - x.lo) * kNodeStep;
                 v = kNodeScale * exp(-d * d);
                 up = exp(-2.0 * kNodeStep * d - kNodeStep * kNodeStep);
                 down = exp(2.0 * kNodeStep * d - kNodeStep * kNodeStep);
@@ -464,11 +478,9 @@ hipError_t launch_prepare_b(hipStream_t st, CurveParams* cp, int n_curves, int m
     return hipGetLastError();
 }
 
-// The node tables of the FP64 mode sums, as above but for exact operands: quads of nodes in place of
-// blocks of 16, blocks of 4 samples, the value of every node and sample by its own exponential.
-// Node quad k of a curve has its sums in register k mod 8 of the kernel, so that its values stand in
-// rows 4 (k mod 8) ... + 3 of the operands.  Bound: latency (sort, scans, reductions);
-// measured, 16 survey curves 47 us.
+// The node tables of the FP64 mode sums, as above but for exact operands: three node blocks per sample,
+// blocks of 4 samples, the value of every node and sample by its own exponential.  Bound: latency
+// (sort, scans, reductions); measured, 16 survey curves 95 us.
 template <int BLOCK, int EMAX>
 __global__ void __launch_bounds__(BLOCK)
 prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
@@ -488,8 +500,8 @@ prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
     int32_t* idx = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(psh) + key_bytes);
     int* g_first = reinterpret_cast<int*>(idx) + room;
     int* g_block = g_first + group_room + 1;  // first block of samples of a group
-    int* g_row = g_block + group_room + 1;    // first node quad, counted among those in use
-    int* g_quad = g_row + group_room;         // and by magnitude
+    int* g_row = g_block + group_room + 1;    // first node block, counted among those in use
+    int* g_rb = g_row + group_room;           // and by magnitude
     for (int i = tid; i < n; i += BLOCK) {
         key[i] = y[i];
         idx[i] = i;
@@ -497,17 +509,17 @@ prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
     sort_block<BLOCK, EMAX, true>(key, idx, n);
     const double y0 = key[0], inv = 1.0 / (kNodeStep64 * P.sigma_y);
     bool sparse = !((key[n - 1] - y0) * inv < 1e9);
-    auto pos = [&](int i) { return (key[i] - y0) * inv + (double)kReach64; };
-    auto quad = [&](int i) { return ((int)rint(pos(i)) - kReach64) >> 2; };
+    auto pos = [&](int i) { return node_units(key[i], y0, inv); };  // from node kReach64
+    auto blk = [&](int i) { return (int)rint(pos(i).hi) >> 4; };
     int n_groups = 0, n_rows = 0, n_blocks = 0;
     if (!sparse) {
-        constexpr int kShift = 14;  // groups (at most 8192) below, quads (8 per group) above
-        static_assert(QMI_MAX_N < (1 << kShift) && QMI_MAX_N * kQuads64 < (1 << 17), "packed counts");
+        constexpr int kShift = 14;  // groups (at most 8192) below, node blocks (3 per group) above
+        static_assert(QMI_MAX_N < (1 << kShift) && QMI_MAX_N * kTiles64 < (1 << 17), "packed counts");
         const int per = (n + BLOCK - 1) / BLOCK;
         const int i0 = min(n, tid * per), i1 = min(n, i0 + per);
         int cnt = 0, all = 0;
         for (int i = i0; i < i1; ++i) {
-            const int d = i == 0 ? kQuads64 : min(kQuads64, quad(i) - quad(i - 1));
+            const int d = i == 0 ? kTiles64 : min(kTiles64, blk(i) - blk(i - 1));
             if (d > 0) cnt += 1 + (d << kShift);
         }
         int at = block_scan<BLOCK>(cnt, ired, &all);
@@ -516,14 +528,14 @@ prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
         sparse = n_groups > M.cap;
         if (!sparse) {
             for (int i = i0; i < i1; ++i) {
-                const int b = quad(i);
-                const int d = i == 0 ? kQuads64 : min(kQuads64, b - quad(i - 1));
+                const int b = blk(i);
+                const int d = i == 0 ? kTiles64 : min(kTiles64, b - blk(i - 1));
                 if (d <= 0) continue;
                 const int g = at & ((1 << kShift) - 1);
                 at += 1 + (d << kShift);
                 g_first[g] = i;
-                g_quad[g] = b;
-                g_row[g] = (at >> kShift) - kQuads64;
+                g_rb[g] = b;
+                g_row[g] = (at >> kShift) - kTiles64;
             }
             if (tid == 0) g_first[n_groups] = n;
             __syncthreads();
@@ -558,45 +570,45 @@ prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
     };
     double* ts = md.ts + 4 * M.boff;
     int32_t* rows = md.rows + M.boff;
-    double* frag = reinterpret_cast<double*>(md.frag) + 128 * M.boff;
-    double* bsum = md.b + 32 * M.boff;
+    double* frag = reinterpret_cast<double*>(md.frag) + 64 * kTiles64 * M.boff;
+    double* bsum = md.b + 16 * kTiles64 * M.boff;
     const int lane = tid & 63, wave = tid >> 6;
     for (int b = wave; b < n_blocks; b += BLOCK / 64) {
         const int g = group_of(b), r0 = g_row[g];
         const int smp = g_first[g] + 4 * (b - g_block[g]) + (lane >> 4);
         const bool has = smp < g_first[g + 1];
-        const double x = has ? pos(smp) : 0.0;
-        for (int nb = 0; nb < 2; ++nb) {
-            const int s = 4 * nb + ((lane & 15) >> 2);
-            const int node = 4 * (g_quad[g] + ((s - r0) & (kQuads64 - 1))) + (lane & 3);
-            const double d = ((double)node - x) * kNodeStep64;
-            frag[(int64_t)b * 128 + 64 * nb + lane] = has ? exp(-d * d) : 0.0;
+        const Exact x = has ? pos(smp) : Exact{0.0, 0.0};
+        for (int k = 0; k < kTiles64; ++k) {
+            const int node = 16 * (g_rb[g] + k) + (lane & 15) - kReach64;
+            const double d = ((double)node - x.hi - x.lo) * kNodeStep64;
+            frag[((int64_t)b * kTiles64 + (r0 + k) % kTiles64) * 64 + lane] =
+                has ? exp(-d * d) : 0.0;
         }
         if ((lane & 15) == 0) ts[4 * b + (lane >> 4)] = has ? t[idx[smp]] : 0.0;
         if (lane == 0) rows[b] = r0;
     }
     __syncthreads();
-    // Sums of a quad's four nodes over all samples: one wave, sixteen lanes per node.
+    // Sums of a node block's 16 nodes over all samples: one wave, four lanes per node.
     for (int k = wave; k < n_rows; k += BLOCK / 64) {
-        int lo = 0, hi = n_groups - 1;  // first group that reaches the quad
+        int lo = 0, hi = n_groups - 1;  // first group that reaches the node block
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (g_row[mid] + kQuads64 > k) hi = mid; else lo = mid + 1;
+            if (g_row[mid] + kTiles64 > k) hi = mid; else lo = mid + 1;
         }
         int last = lo;
         while (last + 1 < n_groups && g_row[last + 1] <= k) ++last;
-        const int s = k & (kQuads64 - 1);
-        const double* from = frag + 64 * (s >> 2) + 4 * (s & 3) + (lane & 3);
+        const double* from = frag + 64 * (k % kTiles64) + lane;
         double v = 0.0;
-        for (int b = g_block[lo] + (lane >> 2); b < g_block[last + 1]; b += 16)
-            for (int i = 0; i < 4; ++i) v += from[(int64_t)b * 128 + 16 * i];
-        for (int o = 4; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-        if (lane < 4) bsum[4 * k + lane] = v;
+#pragma unroll 4
+        for (int b = g_block[lo]; b < g_block[last + 1]; ++b) v += from[(int64_t)b * kTiles64 * 64];
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+        if (lane < 16) bsum[16 * k + lane] = v;
     }
     __syncthreads();
     double sq = 0.0, sb = 0.0;
     if (tid < kSumThreads)
-        for (int q = tid; q < 4 * n_rows; q += kSumThreads) {
+        for (int q = tid; q < 16 * n_rows; q += kSumThreads) {
             const double b = bsum[q];
             sq = fma(b, b, sq);
             sb += b;
