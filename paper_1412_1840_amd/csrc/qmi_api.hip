@@ -447,6 +447,28 @@ int mode_count(double sigma_t, double keep_tail) {
     return 1;
 }
 
+// Places of the pair sums' tables (K, row sums, column sums, pieces) of the curves that take them.
+template <typename R>
+struct PairTables {
+    int64_t k = 0, p = 0, ks = 0, rows = 0, pieces = 0;
+    int max_pieces = 0;
+    void add(CurveParams& c) {
+        constexpr int kPassR = kWaves * rows_per_wave<R>();
+        const int nb = (c.n + kPassR - 1) / kPassR;
+        c.npad = (int32_t)round_up(c.n, kPass);
+        c.koff = k;
+        c.poff = p;
+        c.ksoff = ks;
+        c.pqoff = pieces;
+        k += (int64_t)c.n * c.npad;
+        p += c.npad;
+        ks += (int64_t)nb * kWaves * c.n;
+        rows += c.n;
+        pieces += (int64_t)nb * (nb + 1) / 2;
+        max_pieces = std::max(max_pieces, nb * (nb + 1) / 2);
+    }
+};
+
 // The near ties of the curves tied[] (indices into cp and the group's arrays): their listed points
 // scored by the pair sums, in groups of curves whose tables stay small, and the records written anew.
 // The choice among points that differ by less than the sums' errors is then the pair sums' own,
@@ -458,31 +480,19 @@ int decide_ties(qmi_ctx* ctx, const std::vector<CurveParams>& cp, const std::vec
                 const double* fine2, const PeakOut& pk, const TieDev& tie, DevResult* dres,
                 qmi_result* out) {
     constexpr int64_t kTables = int64_t(64) << 20;  // kernel values of a group (or one curve)
-    constexpr int kPassR = kWaves * rows_per_wave<float>();
     hipStream_t st = ctx->stream;
     for (size_t i0 = 0, i1 = 0; i0 < tied.size(); i0 = i1) {
         std::vector<CurveParams> c2;
         std::vector<int32_t> order;
         std::vector<int64_t> row_start;
-        int64_t koff = 0, poff = 0, ksoff = 0, rows = 0, pieces = 0;
-        int max_n = 2, max_pieces = 0;
+        PairTables<float> tab;
+        int max_n = 2;
         for (; i1 < tied.size(); ++i1) {
             CurveParams p = cp[tied[i1]];
-            p.npad = (int32_t)round_up(p.n, kPass);
-            if (i1 > i0 && koff + (int64_t)p.n * p.npad > kTables / 4) break;
-            const int nb = (p.n + kPassR - 1) / kPassR;
-            p.koff = koff;
-            p.poff = poff;
-            p.ksoff = ksoff;
-            p.pqoff = pieces;
-            koff += (int64_t)p.n * p.npad;
-            poff += p.npad;
-            ksoff += (int64_t)nb * kWaves * p.n;
-            pieces += (int64_t)nb * (nb + 1) / 2;
-            max_pieces = std::max(max_pieces, nb * (nb + 1) / 2);
-            row_start.push_back(rows);
+            if (i1 > i0 && tab.k + p.n * round_up(p.n, kPass) > kTables / 4) break;
+            row_start.push_back(tab.rows);
             order.push_back((int32_t)c2.size());
-            rows += p.n;
+            tab.add(p);
             max_n = std::max(max_n, p.n);
             c2.push_back(p);
         }
@@ -496,9 +506,9 @@ int decide_ties(qmi_ctx* ctx, const std::vector<CurveParams>& cp, const std::vec
         int rc = QMI_OK;
         for (auto [id, bytes] : {std::pair<int, int64_t>{qmi_ctx::kTieUp, (int64_t)up.total},
                                  {qmi_ctx::kTieScore, (int64_t)m * kTieMax * 8},
-                                 {qmi_ctx::kK, koff * 4}, {qmi_ctx::kRP, poff * 8},
-                                 {qmi_ctx::kRD, ns * 8}, {qmi_ctx::kKS, ksoff * 4},
-                                 {qmi_ctx::kPart, pieces * kTieMax * 24}})
+                                 {qmi_ctx::kK, tab.k * 4}, {qmi_ctx::kRP, tab.p * 8},
+                                 {qmi_ctx::kRD, ns * 8}, {qmi_ctx::kKS, tab.ks * 4},
+                                 {qmi_ctx::kPart, tab.pieces * kTieMax * 24}})
             if ((rc = acquire(ctx, id, (size_t)bytes)) != QMI_OK) break;
         if (rc == QMI_ENOMEM) {  // no room beside the group's buffers: the refinement's choice stays
             ctx->err.clear();
@@ -524,14 +534,14 @@ int decide_ties(qmi_ctx* ctx, const std::vector<CurveParams>& cp, const std::vec
         PairOut po{};
         po.score = dptr<double>(ctx, qmi_ctx::kTieScore);
         po.score_kind = score_kind;
-        po.part = max_pieces > 1 ? dptr<double>(ctx, qmi_ctx::kPart) : nullptr;
+        po.part = tab.max_pieces > 1 ? dptr<double>(ctx, qmi_ctx::kPart) : nullptr;
         HIP_OK(ctx, launch_tie_lists(st, m, didx, top_k, n_fine, pk, tie, list));
         HIP_OK(ctx, launch_prepare(st, dcp, m, max_n, t, y, e, skew_lambda, skew_mu, ModeDev{}));
-        HIP_OK(ctx, launch_gram<float>(st, dcp, m, rows, drow, y, K, rp, rd));
+        HIP_OK(ctx, launch_gram<float>(st, dcp, m, tab.rows, drow, y, K, rp, rd));
         HIP_OK(ctx, launch_gram_finalize<float>(st, dcp, m, rd, rp));
         HIP_OK(ctx, launch_ksum<float>(st, dcp, m, max_n, K, ks));
         HIP_OK(ctx, launch_pairs<float>(st, dcp, dorder, m, fp, t, K, rd, rp, ks, po, 0,
-                                        po.part ? max_pieces : 0));
+                                        po.part ? tab.max_pieces : 0));
         HIP_OK(ctx, launch_best_of_ties(st, m, didx, po.score, fine, fine2, top_k, n_fine,
                                         score_kind, pk, tie, dres));
     }
@@ -541,11 +551,28 @@ int decide_ties(qmi_ctx* ctx, const std::vector<CurveParams>& cp, const std::vec
     return QMI_OK;
 }
 
-// Runs one group.  pairs_only: every curve by the pair sums (curves that the mode sums left to
-// them); *left receives the curves of the group that the mode sums left.
+// What the launches of a device section work on: the curves' order (those of the mode sums first) and
+// tables, and how their work is split.
+template <typename R>
+struct Pass {
+    int32_t n_modes = 0, n_pairs = 0;
+    PairTables<R> tab;
+    int variant = 0;
+    R* K = nullptr;
+    double *rp = nullptr, *rd = nullptr;
+    R* ks = nullptr;
+    bool split1 = false, split2 = false, msplit1 = false, msplit2 = false;
+    double* part = nullptr;
+    ModeDev md{};
+    TieDev tie{};
+    bool prepare = true;  // widths and node tables are formed
+    bool trials = true;   // the bands method's trial frequencies are formed
+};
+
+// Runs one group.
 template <typename R>
 int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group& g,
-              std::vector<int32_t>& pair_event_idx, bool pairs_only, std::vector<int32_t>* left) {
+              std::vector<int32_t>& pair_event_idx) {
     begin_use(ctx);
     const int32_t nc = g.c1 - g.c0;
     const int64_t ns = g.s1 - g.s0;
@@ -556,16 +583,16 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     std::vector<CurveParams> cp(nc);
     std::vector<int32_t> order(nc);
     std::vector<int64_t> row_start(nc);
-    int64_t koff = 0, poff = 0, ksoff = 0, rows = 0, pieces = 0;
+    Pass<R> pass;
     std::vector<ModeCurve> mc(nc);
     std::memset(mc.data(), 0, nc * sizeof(ModeCurve));
     int64_t mblocks = 0;
-    int64_t all_k = 0, all_p = 0, all_ks = 0;  // the pair sums' tables if they took every curve
+    PairTables<R> all;     // the pair sums' tables if they took every curve
     int32_t n_modes = 0;  // curves whose sums are taken over modes
     const bool rule_t = kp->sigma_t == QMI_SIGMA_T_SKEWNESS;
     const double min_sigma_t = !rule_t ? kp->sigma_t
                                : kp->skew_lambda > 0.0 ? kp->skew_lambda : QMI_SKEW_LAMBDA;
-    const bool modes = kp->precision != QMI_PREC_FOLD32 && !pairs_only;
+    const bool modes = kp->precision != QMI_PREC_FOLD32;
     const int per_group = fp64 ? kModeGroup64 : kModeGroup;
     if (modes && ctx->mode_sigma_t[fp64] != min_sigma_t) {
         ctx->mode_sigma_t[fp64] = min_sigma_t;
@@ -575,8 +602,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     }
     const int mode_groups = modes ? ctx->mode_groups[fp64] : 0;
     const int mode_cap = mode_groups * per_group + 8;
-    constexpr int kPassR = kWaves * rows_per_wave<R>();
-    int max_n = 2, max_pieces = 0;
+    int max_n = 2;
     std::vector<int32_t> status(nc);
     curve_statuses(g.c0, g.c1, cs.dev_inputs ? 0 : ns, status.data(),
                    [&](int32_t k) { return host_curve_status(b, k, !cs.dev_inputs); });
@@ -592,37 +618,23 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         p.sigma_t = kp->sigma_t;
         p.sigma_y_rule = kp->sigma_y;
         p.sigma_y = NAN;
-        row_start[i] = rows;
+        row_start[i] = pass.tab.rows;
         order[i] = i;
         if (p.status == QMI_OK) {
-            const int64_t np = round_up(p.n, kPass);
-            all_k += p.n * np;
-            all_p += np;
-            all_ks += (int64_t)((p.n + kPassR - 1) / kPassR) * kWaves * p.n;
+            CurveParams q = p;
+            all.add(q);
         }
-        const int expect = mode_expect(p.n);
         if (p.status == QMI_OK && mode_groups > 0 &&
-            (fp64 ? mode64_takes(p.n, mode_groups)
-                  : expect <= mode_even(p.n, mode_groups) && expect <= p.n / 5)) {
+            (fp64 ? mode64_takes(p.n, mode_groups) : mode_takes(p.n, mode_groups))) {
             ModeCurve& m = mc[i];
             m.cap = fp64 ? mode64_room(p.n) : mode_room(p.n, mode_groups);
+            m.limit = fp64 ? mode64_limit(p.n, mode_groups) : mode_limit(p.n, mode_groups);
             m.boff = mblocks;
             mblocks += m.cap;
             ++n_modes;
             max_n = std::max(max_n, p.n);
         } else if (p.status == QMI_OK) {
-            p.npad = (int32_t)round_up(p.n, kPass);
-            p.koff = koff;
-            p.poff = poff;
-            p.ksoff = ksoff;
-            koff += (int64_t)p.n * p.npad;
-            poff += p.npad;
-            ksoff += (int64_t)((p.n + kPassR - 1) / kPassR) * kWaves * p.n;
-            const int nbp = (p.n + kPassR - 1) / kPassR;
-            p.pqoff = pieces;
-            pieces += (int64_t)nbp * (nbp + 1) / 2;
-            max_pieces = std::max(max_pieces, nbp * (nbp + 1) / 2);
-            rows += p.n;
+            pass.tab.add(p);
             max_n = std::max(max_n, p.n);
         }
     }
@@ -634,6 +646,8 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         return na > nb;
     });
     const int32_t n_pairs = nc - n_modes;
+    pass.n_modes = n_modes;
+    pass.n_pairs = n_pairs;
 
     const qmi_bands* bp = cs.bands;
     const bool search = !cs.periodogram && !bp;
@@ -651,8 +665,8 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         // the pair sums, and the mode tables are smaller), or the call is refused.
         size_t at = 0;
         for (size_t bytes : {nc * sizeof(CurveParams), nc * sizeof(int32_t), nc * sizeof(int64_t),
-                             (size_t)all_k * sizeof(R), (size_t)all_p * 8, (size_t)ns * 8,
-                             (size_t)all_ks * sizeof(R)})
+                             (size_t)all.k * sizeof(R), (size_t)all.p * 8, (size_t)ns * 8,
+                             (size_t)all.ks * sizeof(R)})
             at = (at + 255) / 256 * 256 + std::max<size_t>(bytes, 1);
         if (at > ctx->ws_size) return scratch_full(ctx);
     }
@@ -672,12 +686,20 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         if (b->e) at_e = up.add(b->e + g.s0, ns * 8);
     }
     ENSURE(qmi_ctx::kUp, up.total);
-    if (n_pairs) {
-        ENSURE(qmi_ctx::kK, std::max<int64_t>(koff, 1) * sizeof(R));
-        ENSURE(qmi_ctx::kRP, std::max<int64_t>(poff, 1) * 8);
+    // The pair sums' tables of a pass.
+    auto pair_tables = [&](Pass<R>& ps) -> int {
+        int rc;
+        ENSURE(qmi_ctx::kK, std::max<int64_t>(ps.tab.k, 1) * sizeof(R));
+        ENSURE(qmi_ctx::kRP, std::max<int64_t>(ps.tab.p, 1) * 8);
         ENSURE(qmi_ctx::kRD, std::max<int64_t>(ns, 1) * 8);
-        ENSURE(qmi_ctx::kKS, std::max<int64_t>(ksoff, 1) * sizeof(R));
-    }
+        ENSURE(qmi_ctx::kKS, std::max<int64_t>(ps.tab.ks, 1) * sizeof(R));
+        ps.K = dptr<R>(ctx, qmi_ctx::kK);
+        ps.rp = dptr<double>(ctx, qmi_ctx::kRP);
+        ps.rd = dptr<double>(ctx, qmi_ctx::kRD);
+        ps.ks = dptr<R>(ctx, qmi_ctx::kKS);
+        return QMI_OK;
+    };
+    if (n_pairs && (rc = pair_tables(pass)) != QMI_OK) return rc;
     if (n_modes) {
         ENSURE(qmi_ctx::kModeTs, mblocks * (fp64 ? 32 : 256));
         ENSURE(qmi_ctx::kModeRows, mblocks * 4);
@@ -723,19 +745,24 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     constexpr int64_t kSplitBelow = 2048;
     constexpr int64_t kSplitMaxBytes = int64_t(256) << 20;
     const int64_t tiles1 = (F1 + 63) / 64, tiles2 = (F2 + 63) / 64;
-    const int64_t mode_parts = (int64_t)n_modes * mode_groups;
-    const int64_t part_bytes = std::max(pieces, mode_parts) * std::max(F1, F2) * 24;
-    bool split1 = max_pieces > 1 && n_pairs * tiles1 < kSplitBelow;
-    bool split2 = refine && max_pieces > 1 && n_pairs * tiles2 < kSplitBelow;
-    bool msplit1 = mode_groups > 1 && n_modes * tiles1 < kSplitBelow;
-    bool msplit2 = refine && mode_groups > 1 && n_modes * tiles2 < kSplitBelow;
-    if ((split1 || split2 || msplit1 || msplit2) &&
-        (part_bytes > kSplitMaxBytes || (size_t)part_bytes > ctx->budget / 8 ||
-         acquire(ctx, qmi_ctx::kPart, part_bytes) != QMI_OK)) {
-        split1 = split2 = msplit1 = msplit2 = false;
-        ctx->err.clear();
-    }
-    double* dpart = (split1 || split2 || msplit1 || msplit2) ? dptr<double>(ctx, qmi_ctx::kPart) : nullptr;
+    auto split = [&](Pass<R>& ps) {
+        const int64_t mode_parts = (int64_t)ps.n_modes * mode_groups;
+        const int64_t part_bytes = std::max(ps.tab.pieces, mode_parts) * std::max(F1, F2) * 24;
+        ps.split1 = ps.tab.max_pieces > 1 && ps.n_pairs * tiles1 < kSplitBelow;
+        ps.split2 = refine && ps.tab.max_pieces > 1 && ps.n_pairs * tiles2 < kSplitBelow;
+        ps.msplit1 = mode_groups > 1 && ps.n_modes * tiles1 < kSplitBelow;
+        ps.msplit2 = refine && mode_groups > 1 && ps.n_modes * tiles2 < kSplitBelow;
+        ps.part = nullptr;
+        if (!(ps.split1 || ps.split2 || ps.msplit1 || ps.msplit2)) return;
+        if (part_bytes > kSplitMaxBytes || (size_t)part_bytes > ctx->budget / 8 ||
+            acquire(ctx, qmi_ctx::kPart, part_bytes) != QMI_OK) {
+            ps.split1 = ps.split2 = ps.msplit1 = ps.msplit2 = false;
+            ctx->err.clear();
+            return;
+        }
+        ps.part = dptr<double>(ctx, qmi_ctx::kPart);
+    };
+    split(pass);
 
     hipStream_t st = ctx->stream;
     char* dup = dptr<char>(ctx, qmi_ctx::kUp);
@@ -749,8 +776,8 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     int32_t* dorder = reinterpret_cast<int32_t*>(dup + at_order);
     int64_t* drow = reinterpret_cast<int64_t*>(dup + at_row);
     HIP_OK(ctx, upload(ctx->stage, up, dup, ctx->device, st, !ctx->ws_base));
-    ModeDev md{};
-    TieDev tie{};
+    ModeDev& md = pass.md;
+    TieDev& tie = pass.tie;
     if (n_modes) {
         md.curves = reinterpret_cast<ModeCurve*>(dup + at_mc);
         md.ts = dptr<double>(ctx, qmi_ctx::kModeTs);
@@ -773,11 +800,6 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     const double* dfreqs = nullptr;
     if (cs.periodogram)
         dfreqs = cs.dev_inputs ? cs.freqs : reinterpret_cast<const double*>(dup + at_f);
-
-    R* K = n_pairs ? dptr<R>(ctx, qmi_ctx::kK) : nullptr;
-    double* rp = n_pairs ? dptr<double>(ctx, qmi_ctx::kRP) : nullptr;
-    double* rd = n_pairs ? dptr<double>(ctx, qmi_ctx::kRD) : nullptr;
-    R* ks = n_pairs ? dptr<R>(ctx, qmi_ctx::kKS) : nullptr;
 
     FreqPlan fp{};
     PairOut po{};
@@ -860,27 +882,31 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     // Pair-kernel variant: forced by QMI_OPT_TILE, else the autotuned choice for this length
     // bucket; until the bucket has been tuned (see the end of this function), variant 1 (4 waves
     // per SIMD, 64-column chunks), the fastest on every length mix measured.
+    const int nvar = pair_variants<R>();
+    const bool fold32 = kp->precision == QMI_PREC_FOLD32;
+    int bucket = 0;
+    auto pick_variant = [&](std::vector<int32_t> lens) -> int {
+        bucket = 0;
+        if (!lens.empty()) {
+            std::nth_element(lens.begin(), lens.begin() + lens.size() / 2, lens.end());
+            const int med = lens[lens.size() / 2];
+            while (bucket < 7 && (192 << bucket) <= med) ++bucket;
+        }
+        if (fold32) return kVariantFold32;
+        if (ctx->tile > 0) return (int)std::min<int64_t>(ctx->tile - 1, nvar - 1);
+        if (!fp64 && ctx->tuned[bucket] >= 0) return ctx->tuned[bucket];
+        return nvar > 1 ? 1 : 0;
+    };
     std::vector<int32_t> lens;
     for (int32_t i = 0; i < nc; ++i)
         if (cp[i].status == QMI_OK && (n_pairs == 0 || mc[i].cap == 0)) lens.push_back(cp[i].n);
-    int bucket = 0;
-    if (!lens.empty()) {
-        std::nth_element(lens.begin(), lens.begin() + lens.size() / 2, lens.end());
-        const int med = lens[lens.size() / 2];
-        while (bucket < 7 && (192 << bucket) <= med) ++bucket;
-    }
-    const int nvar = pair_variants<R>();
-    int variant = nvar > 1 ? 1 : 0;
-    const bool fold32 = kp->precision == QMI_PREC_FOLD32;
-    if (fold32) variant = kVariantFold32;
-    else if (ctx->tile > 0) variant = (int)std::min<int64_t>(ctx->tile - 1, nvar - 1);
-    else if (!fp64 && ctx->tuned[bucket] >= 0) variant = ctx->tuned[bucket];
+    pass.variant = pick_variant(lens);
     double group_items = 0.0;
     for (int32_t i = 0; i < nc; ++i)
         if (cp[i].status == QMI_OK && mc[i].cap == 0) group_items += 0.5 * cp[i].n * (cp[i].n - 1.0) * (double)F1;
     const bool tune_now = !fp64 && !fold32 && ctx->tile == 0 && ctx->tuned[bucket] < 0 &&
                           nvar > 1 && !ctx->ws_base && group_items > 2e9;
-    ctx->stats.pair_variant = variant;
+    ctx->stats.pair_variant = pass.variant;
 
     const bool skew_default = kp->skew_lambda == 0.0 && kp->skew_mu == 0.0;
     const double skew_lambda = skew_default ? QMI_SKEW_LAMBDA : kp->skew_lambda;
@@ -889,30 +915,32 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     // The device section: every kernel of the call, and the timing events around the pair kernels.
     // It contains no copies or allocations, so it can be captured into a hipGraph and replayed.
     constexpr auto sum_modes = std::is_same<R, double>::value ? launch_modes64 : launch_modes;
-    auto section = [&](bool events) -> int {
+    auto section = [&](const Pass<R>& ps, bool events) -> int {
         auto rec = [&]() {
             if (events) record(ctx);
         };
         rec();  // device section start
-        HIP_OK(ctx, launch_prepare(st, dcp, nc, max_n, t, y, e, skew_lambda, skew_mu,
-                                   fp64 ? ModeDev{} : md));
-        if (fp64 && n_modes) HIP_OK(ctx, launch_prepare64(st, dcp, nc, max_n, t, y, md));
-        if (n_pairs) {
-            HIP_OK(ctx, launch_gram<R>(st, dcp, nc, rows, drow, y, K, rp, rd));
-            HIP_OK(ctx, launch_gram_finalize<R>(st, dcp, nc, rd, rp));
-            HIP_OK(ctx, launch_ksum<R>(st, dcp, nc, max_n, K, ks));
+        if (ps.prepare)
+            HIP_OK(ctx, launch_prepare(st, dcp, nc, max_n, t, y, e, skew_lambda, skew_mu,
+                                       fp64 ? ModeDev{} : ps.md));
+        if (fp64 && ps.n_modes)
+            HIP_OK(ctx, launch_prepare64(st, dcp, nc, max_n, t, y, ps.md));
+        if (ps.n_pairs) {
+            HIP_OK(ctx, launch_gram<R>(st, dcp, nc, ps.tab.rows, drow, y, ps.K, ps.rp, ps.rd));
+            HIP_OK(ctx, launch_gram_finalize<R>(st, dcp, nc, ps.rd, ps.rp));
+            HIP_OK(ctx, launch_ksum<R>(st, dcp, nc, max_n, ps.K, ps.ks));
         }
-        if (bp) HIP_OK(ctx, launch_bands(st, dcp, nc, max_n, t, y, bd));
+        if (bp && ps.trials) HIP_OK(ctx, launch_bands(st, dcp, nc, max_n, t, y, bd));
         if (events) pair_event_idx.push_back(ctx->ev_used);
         rec();
         {
             PairOut pm1 = po;
-            pm1.part = msplit1 ? dpart : nullptr;
-            if (n_modes)
-                HIP_OK(ctx, sum_modes(st, dcp, dorder, n_modes, fp, md, pm1,
-                                         msplit1 ? mode_groups : 0));
+            pm1.part = ps.msplit1 ? ps.part : nullptr;
+            if (ps.n_modes)
+                HIP_OK(ctx, sum_modes(st, dcp, dorder, ps.n_modes, fp, ps.md, pm1,
+                                      ps.msplit1 ? mode_groups : 0));
             PairOut pc1 = po;
-            pc1.part = split1 ? dpart : nullptr;
+            pc1.part = ps.split1 ? ps.part : nullptr;
             // Per-curve lists whose last tile would hold only one or two slots (the bands
             // method's 450 trials): the main launch stops before that tile, and a kernel with one
             // row per lane takes its slots (FP32 path).
@@ -920,19 +948,20 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             int rem_slot0 = -1;
             if constexpr (sizeof(R) == 4) {
                 const int full = fp.count / kLanes, rem = fp.count % kLanes;
-                if (fp.kind == 3 && variant != kVariantFold32 && full > 0 && rem > 0 &&
+                if (fp.kind == 3 && ps.variant != kVariantFold32 && full > 0 && rem > 0 &&
                     rem <= kRemSlots) {
                     fpm.tile_cap = full;
                     rem_slot0 = full * kLanes;
                 }
             }
-            const int32_t* porder = dorder + n_modes;
-            HIP_OK(ctx, launch_pairs<R>(st, dcp, porder, n_pairs, fpm, t, K, rd, rp, ks, pc1,
-                                        variant, split1 ? max_pieces : 0));
+            const int32_t* porder = dorder + ps.n_modes;
+            HIP_OK(ctx, launch_pairs<R>(st, dcp, porder, ps.n_pairs, fpm, t, ps.K, ps.rd, ps.rp,
+                                        ps.ks, pc1, ps.variant,
+                                        ps.split1 ? ps.tab.max_pieces : 0));
             if constexpr (sizeof(R) == 4) {
                 if (rem_slot0 >= 0)
-                    HIP_OK(ctx, launch_pairs_rows(st, dcp, porder, n_pairs, fp, rem_slot0, t, K,
-                                                  rd, pc1));
+                    HIP_OK(ctx, launch_pairs_rows(st, dcp, porder, ps.n_pairs, fp, rem_slot0, t,
+                                                  ps.K, ps.rd, pc1));
             }
         }
         rec();
@@ -944,23 +973,24 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             HIP_OK(ctx, launch_peaks(st, dcp, nc, coarse, s->n_coarse, fp.f0, fp.df, top_k,
                                      std::max(n_fine, 2), ctx->masks, pk, fine, F2));
             if (refine) {
-                PairOut fo{fine, fine2, nullptr, score_kind, 0, split2 ? dpart : nullptr};
+                PairOut fo{fine, fine2, nullptr, score_kind, 0, ps.split2 ? ps.part : nullptr};
                 if (events) pair_event_idx.push_back(ctx->ev_used);
                 rec();
                 PairOut fm = fo;
-                fm.part = msplit2 ? dpart : nullptr;
-                if (n_modes)
-                    HIP_OK(ctx, sum_modes(st, dcp, dorder, n_modes, ff, md, fm,
-                                             msplit2 ? mode_groups : 0));
-                if (md.win_width > 0.0)
-                    HIP_OK(ctx, launch_mode_windows(st, dcp, nc, ff, md, fm));
-                HIP_OK(ctx, launch_pairs<R>(st, dcp, dorder + n_modes, n_pairs, ff, t, K, rd, rp,
-                                            ks, fo, variant, split2 ? max_pieces : 0));
+                fm.part = ps.msplit2 ? ps.part : nullptr;
+                if (ps.n_modes)
+                    HIP_OK(ctx, sum_modes(st, dcp, dorder, ps.n_modes, ff, ps.md, fm,
+                                          ps.msplit2 ? mode_groups : 0));
+                if (ps.md.win_width > 0.0)
+                    HIP_OK(ctx, launch_mode_windows(st, dcp, nc, ff, ps.md, fm));
+                HIP_OK(ctx, launch_pairs<R>(st, dcp, dorder + ps.n_modes, ps.n_pairs, ff, t, ps.K,
+                                            ps.rd, ps.rp, ps.ks, fo, ps.variant,
+                                            ps.split2 ? ps.tab.max_pieces : 0));
                 rec();
             }
             HIP_OK(ctx, launch_best(st, dcp, nc, coarse, coarse2, s->n_coarse, fine, fine2,
                                     refine ? top_k : 0, refine ? n_fine : 0, score_kind, fp.f0,
-                                    fp.df, ctx->masks, pk, tie, dres));
+                                    fp.df, ctx->masks, pk, ps.tie, dres));
         }
         rec();  // device section end
         return QMI_OK;
@@ -973,19 +1003,19 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         auto u = [](const void* p) { return (uint64_t)(uintptr_t)p; };
         auto dbits = [](double v) { uint64_t b; std::memcpy(&b, &v, 8); return b; };
         std::vector<uint64_t> key = {
-            (uint64_t)fp64, (uint64_t)cs.periodogram, (uint64_t)nc, (uint64_t)rows,
+            (uint64_t)fp64, (uint64_t)cs.periodogram, (uint64_t)nc, (uint64_t)pass.tab.rows,
             (uint64_t)max_n, (uint64_t)F1, (uint64_t)F2, (uint64_t)top_k, (uint64_t)n_fine,
-            (uint64_t)score_kind, (uint64_t)variant, dbits(fp.f0), dbits(fp.df),
+            (uint64_t)score_kind, (uint64_t)pass.variant, dbits(fp.f0), dbits(fp.df),
             dbits(skew_lambda), dbits(skew_mu), u(st), u(t), u(y),
             u(e), u(dcp),
-            u(dorder), u(drow), u(K), u(rp), u(rd), u(ks), u(dfreqs), u(coarse), u(coarse2),
+            u(dorder), u(drow), u(pass.K), u(pass.rp), u(pass.rd), u(pass.ks), u(dfreqs), u(coarse), u(coarse2),
             u(po.ips), u(fine), u(fine2), u(pk.peak_k), u(pk.npk), u(pk.win), u(pk.argmax),
             u(dres), (uint64_t)(bp != nullptr), dbits(bd.f_lo), dbits(bd.df),
             (uint64_t)bd.n_grid, (uint64_t)bd.n_bands, (uint64_t)bd.n_keep, (uint64_t)bd.n_trials,
             (uint64_t)bd.stride, u(bd.ts), u(bd.ys), u(bd.band_t), u(bd.band_cnt), u(bd.band_id),
             u(bd.S), u(bd.trials), u(bd.trial_k), (uint64_t)n_modes,
-            (uint64_t)mode_groups, (uint64_t)max_pieces, (uint64_t)split1, (uint64_t)split2,
-            (uint64_t)msplit1, (uint64_t)msplit2, u(dpart), u(md.curves), u(md.ts), u(md.rows),
+            (uint64_t)mode_groups, (uint64_t)pass.tab.max_pieces, (uint64_t)pass.split1,
+            (uint64_t)pass.split2, (uint64_t)pass.msplit1, (uint64_t)pass.msplit2, u(pass.part), u(md.curves), u(md.ts), u(md.rows),
             u(md.frag), u(md.part), u(md.b), u(md.coef), u(tie.count), u(tie.slot)};
         if (ctx->graph_exec && key == ctx->graph_key) {
             record(ctx);
@@ -1004,7 +1034,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             int rc_sec = QMI_OK;
             hipGraph_t graph = nullptr;
             if (ok) {
-                rc_sec = section(false);
+                rc_sec = section(pass, false);
                 const bool ended = hipStreamEndCapture(st, &graph) == hipSuccess;
                 hipGraphExec_t exec = nullptr;
                 ok = rc_sec == QMI_OK && ended && graph &&
@@ -1037,7 +1067,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     }
     if (!ran) {
         // Scratch mode records no timing events (their creation allocates).
-        const int rc_sec = section(!ctx->ws_base);
+        const int rc_sec = section(pass, !ctx->ws_base);
         if (rc_sec != QMI_OK) return rc_sec;
     }
 
@@ -1062,11 +1092,13 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         int best_v = 0;
         for (int v = 0; v < nvar; ++v) {
             HIP_OK(ctx,
-                   launch_pairs<R>(st, dcp, dorder + n_modes, pc, probe, t, K, rd, rp, ks, pout, v, 0));
+                   launch_pairs<R>(st, dcp, dorder + n_modes, pc, probe, t, pass.K, pass.rd,
+                                   pass.rp, pass.ks, pout, v, 0));
             HIP_OK(ctx, hipEventRecord(e0, st));
             for (int rep = 0; rep < 2; ++rep)
                 HIP_OK(ctx,
-                       launch_pairs<R>(st, dcp, dorder + n_modes, pc, probe, t, K, rd, rp, ks, pout, v, 0));
+                       launch_pairs<R>(st, dcp, dorder + n_modes, pc, probe, t, pass.K, pass.rd,
+                                   pass.rp, pass.ks, pout, v, 0));
             HIP_OK(ctx, hipEventRecord(e1, st));
             HIP_OK(ctx, hipEventSynchronize(e1));
             float ms = 0.f;
@@ -1081,18 +1113,75 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         ctx->tuned[bucket] = best_v;
     }
 
-    // Results back to the caller.
+    // The curves that the mode sums left to the pair sums (known only once their widths are): one more
+    // section over the group's curves with all others skipped, within the memory that the group was
+    // planned for (the mode sums' tables may go).
+    std::vector<int32_t> left;
+    // known: the parameters as the preparation left them, or empty (it then runs again).
+    auto pair_pass = [&](const std::vector<CurveParams>& known) -> int {
+        std::vector<CurveParams> c2 = known.empty() ? cp : known;
+        std::vector<int32_t> o2 = left, len2;
+        std::vector<char> take(nc, 0);
+        Pass<R> ps;
+        for (int32_t i : left) take[i] = 1;
+        for (int32_t i = 0; i < nc; ++i) {
+            row_start[i] = ps.tab.rows;
+            if (!take[i]) {
+                c2[i].status = QMI_EINVAL;
+                continue;
+            }
+            c2[i].sparse = 0;
+            ps.tab.add(c2[i]);
+            len2.push_back(c2[i].n);
+        }
+        std::stable_sort(o2.begin(), o2.end(),
+                         [&](int32_t a, int32_t c) { return cp[a].n > cp[c].n; });
+        o2.resize(nc, 0);
+        ps.n_pairs = (int32_t)left.size();
+        ps.variant = pick_variant(len2);
+        ps.prepare = known.empty();
+        ps.trials = false;
+        if (ctx->ws_base)
+            ctx->ws_used = (size_t)((char*)ctx->ws_ptr[qmi_ctx::kUp] - ctx->ws_base) + at_mc;
+        for (int id : {qmi_ctx::kModeTs, qmi_ctx::kModeRows, qmi_ctx::kModeFrag, qmi_ctx::kModePart,
+                       qmi_ctx::kModeB, qmi_ctx::kModeCoef})
+            ctx->in_use &= ~(1ull << id);
+        const int rc2 = pair_tables(ps);
+        if (rc2 != QMI_OK) return rc2;
+        split(ps);
+        Upload again;
+        again.add(c2.data(), nc * sizeof(CurveParams));
+        again.add(o2.data(), nc * sizeof(int32_t));
+        again.add(row_start.data(), nc * sizeof(int64_t));
+        HIP_OK(ctx, upload(ctx->stage, again, dup, ctx->device, st, !ctx->ws_base));
+        return section(ps, !ctx->ws_base);
+    };
+    // Results back to the caller.  Large ones wait for the records of the curves, which say what was
+    // left: their rows then go down once.
+    const bool rows_last = n_modes > 0 && (size_t)(nc * F1 * 8) >= kTeamBytes;
     if (cs.periodogram) {
         std::vector<CurveParams> cpo(nc);
-        Download dn;
-        dn.add(cpo.data(), dcp, nc * sizeof(CurveParams));
-        if (!cs.dev_outputs) {
-            dn.add(cs.score_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8);
-            if (cs.ips_out) dn.add(cs.ips_out + (int64_t)g.c0 * F1 * 3, po.ips, nc * F1 * 24);
-        }
-        HIP_OK(ctx, download(ctx->stage, dn, st, !ctx->ws_base));
+        auto results = [&](bool records, bool rows) -> int {
+            Download dn;
+            if (records) dn.add(cpo.data(), dcp, nc * sizeof(CurveParams));
+            if (rows && !cs.dev_outputs) {
+                dn.add(cs.score_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8);
+                if (cs.ips_out) dn.add(cs.ips_out + (int64_t)g.c0 * F1 * 3, po.ips, nc * F1 * 24);
+            }
+            HIP_OK(ctx, download(ctx->stage, dn, st, !ctx->ws_base));
+            return QMI_OK;
+        };
+        if ((rc = results(true, !rows_last)) != QMI_OK) return rc;
         for (int32_t i = 0; i < nc; ++i)
-            if (cpo[i].status == QMI_OK && cpo[i].sparse) left->push_back(g.c0 + i);
+            if (cpo[i].status == QMI_OK && cpo[i].sparse) left.push_back(i);
+        if (!left.empty()) {
+            std::vector<CurveParams> first = cpo;
+            if ((rc = pair_pass(first)) != QMI_OK || (rc = results(true, true)) != QMI_OK) return rc;
+            for (int32_t i : left) first[i] = cpo[i];
+            cpo.swap(first);
+        } else if (rows_last && (rc = results(false, true)) != QMI_OK) {
+            return rc;
+        }
         for (int32_t i = 0; i < nc; ++i) {
             if (cs.ip_y_out) cs.ip_y_out[g.c0 + i] = cpo[i].status ? NAN : cpo[i].ipy;
             if (cs.status_out) cs.status_out[g.c0 + i] = cpo[i].status;
@@ -1111,20 +1200,24 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         }
     } else {
         static_assert(sizeof(DevResult) == sizeof(qmi_result), "result layout");
-        Download dn;
-        dn.add(cs.out + g.c0, dres, nc * sizeof(DevResult));
-        if (cs.coarse_out) {
-            if (cs.dev_outputs)
-                HIP_OK(ctx, hipMemcpyAsync(cs.coarse_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8,
-                                           hipMemcpyDeviceToDevice, st));
-            else
-                dn.add(cs.coarse_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8);
-        }
-        if (bp && cs.trials_out)
-            dn.add(cs.trials_out + (int64_t)g.c0 * F1, bd.trials, nc * F1 * 8);
-        if (bp && cs.scores_out)
-            dn.add(cs.scores_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8);
-        HIP_OK(ctx, download(ctx->stage, dn, st, !ctx->ws_base));
+        auto results = [&](qmi_result* records, bool rows) -> int {
+            Download dn;
+            if (records) dn.add(records, dres, nc * sizeof(DevResult));
+            if (rows && cs.coarse_out) {
+                if (cs.dev_outputs)
+                    HIP_OK(ctx, hipMemcpyAsync(cs.coarse_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8,
+                                               hipMemcpyDeviceToDevice, st));
+                else
+                    dn.add(cs.coarse_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8);
+            }
+            if (rows && bp && cs.trials_out)
+                dn.add(cs.trials_out + (int64_t)g.c0 * F1, bd.trials, nc * F1 * 8);
+            if (rows && bp && cs.scores_out)
+                dn.add(cs.scores_out + (int64_t)g.c0 * F1, coarse, nc * F1 * 8);
+            HIP_OK(ctx, download(ctx->stage, dn, st, !ctx->ws_base));
+            return QMI_OK;
+        };
+        if ((rc = results(cs.out + g.c0, !rows_last)) != QMI_OK) return rc;
         if (tie.count) {
             std::vector<int32_t> tied;
             for (int32_t i = 0; i < nc; ++i)
@@ -1135,6 +1228,16 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
                                  skew_mu, fine, fine2, pk, tie, dres, cs.out + g.c0);
                 if (rc != QMI_OK) return rc;
             }
+        }
+        for (int32_t i = 0; i < nc; ++i)
+            if (cs.out[g.c0 + i].status == QMI_OK && cs.out[g.c0 + i].reserved == 1) left.push_back(i);
+        if (!left.empty()) {
+            std::vector<qmi_result> again(nc);
+            if ((rc = pair_pass({})) != QMI_OK || (rc = results(again.data(), true)) != QMI_OK)
+                return rc;
+            for (int32_t i : left) cs.out[g.c0 + i] = again[i];
+        } else if (rows_last && (rc = results(nullptr, true)) != QMI_OK) {
+            return rc;
         }
         if (bp && (cs.trials_out || cs.scores_out)) {
             // Empty trial slots are never scored: report them as NaN in both outputs.
@@ -1151,10 +1254,6 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         }
         for (int32_t i = 0; i < nc; ++i) {
             qmi_result& rr = cs.out[g.c0 + i];
-            if (rr.status == QMI_OK && rr.reserved == 1) {  // left to the pair sums
-                left->push_back(g.c0 + i);
-                continue;
-            }
             rr.reserved = 0;
             if (cp[i].status != QMI_OK) {
                 // The kernels skipped this curve; make its record explicit.
@@ -1179,8 +1278,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
     if (cs.periodogram) {
         for (int32_t i = 0; i < nc; ++i) {
             const int64_t n = b->offsets[g.c0 + i + 1] - b->offsets[g.c0 + i];
-            if (cp[i].status == QMI_OK && !(left && std::binary_search(left->begin(), left->end(),
-                                                                       g.c0 + i)))
+            if (cp[i].status == QMI_OK)
                 ctx->stats.pair_items += (double)n * (double)(n - 1) / 2.0 * (double)F1;
         }
     }
@@ -1268,27 +1366,10 @@ int run_call(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs) {
     } scratch_off{ctx};
     ctx->ev_used = 0;
     std::vector<int32_t> pair_ev;
-    std::vector<int32_t> left;
     for (const Group& g : groups) {
-        left.clear();
-        rc = (cs.kp->precision == QMI_PREC_FP64)
-                 ? run_group<double>(ctx, b, cs, g, pair_ev, false, &left)
-                 : run_group<float>(ctx, b, cs, g, pair_ev, false, &left);
+        rc = (cs.kp->precision == QMI_PREC_FP64) ? run_group<double>(ctx, b, cs, g, pair_ev)
+                                                 : run_group<float>(ctx, b, cs, g, pair_ev);
         if (rc) return rc;
-        // Curves that the mode sums left (known only once their widths are): runs of neighbours
-        // by the pair sums, within the memory that the group was planned for.
-        for (size_t i = 0; i < left.size();) {
-            size_t j = i + 1;
-            while (j < left.size() && left[j] == left[j - 1] + 1) ++j;
-            const Group sub{left[i], left[j - 1] + 1, b->offsets[left[i]],
-                            b->offsets[left[j - 1] + 1]};
-            ctx->ws_used = 0;
-            rc = (cs.kp->precision == QMI_PREC_FP64)
-                     ? run_group<double>(ctx, b, cs, sub, pair_ev, true, nullptr)
-                     : run_group<float>(ctx, b, cs, sub, pair_ev, true, nullptr);
-            if (rc) return rc;
-            i = j;
-        }
     }
     // Timing from the events (all complete: every group synchronised).
     float ms = 0.f;

@@ -443,7 +443,7 @@ bands_best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__
     const double* fr = bd.trials + (int64_t)c * F;
     double bq = NAN, bf = INFINITY;
     int bs = 0x7fffffff, found = 0;
-    if (P.status == 0) {
+    if (P.status == 0 && !P.sparse) {
         for (int s = threadIdx.x; s < F; s += kBandsBestBlock) {
             const double f = fr[s];
             if (!(f == f)) continue;
@@ -481,7 +481,7 @@ bands_best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__
     r.coarse_best = NAN;
     r.n = P.n;
     r.status = P.status;
-    r.reserved = P.sparse;  // nonzero: the host searches the curve again by the pair sums
+    r.reserved = P.sparse;  // nonzero: the pair sums take the curve over
     r.n_peaks = sfound[0];
     const int s = ss[0];
     if (P.status != 0 || s == 0x7fffffff) {

@@ -68,22 +68,27 @@ struct CurveParams {
 constexpr double kModeTail = 1e-8;
 constexpr int kModeGroup = 7;      // harmonics per pass over the samples
 constexpr int kModeCapMax = 256;     // most harmonics (sigma_t from 0.03)
-// Blocks with which the mode sums take the pair sums' time.  Measured per curve and frequency (4096
-// frequencies, batches of 256 curves): the pair sums take 9.2e-5 n^2 + 0.008 n + 0.25 ns, the mode sums
-// 0.107 ns per block and group of harmonics and 0.2 ns.  The host gives a curve to the mode sums when
-// the blocks it probably has are no more than that: its whole blocks and two more, and one per 200
-// samples (the node blocks that a longer curve's narrower sigma_y adds).  They meet at n = 32, 64, 107,
-// 200, 350 and 690 for sigma_t = 2, 0.6, 0.3, 0.2, 0.1 and 0.05 (1, 2, 3, 5, 9 and 17 groups).
-inline int mode_even(int n, int groups) {
-    return (int)((8.6e-4 * n * n + 0.075 * n + 0.5) / groups);
+// Which curves the mode sums take.  Measured per curve and frequency (4096 to 20 000 frequencies,
+// batches): the pair sums take 9.2e-5 n^2 + 0.008 n + 0.25 ns, the mode sums 0.2 ns and, per group of
+// harmonics, 0.1 ns per block and 0.058 per step to another node block (its sums are folded).  In
+// units of half a block: mode_limit is what the pair sums' time buys, 2 blocks + steps what is spent.
+// The host gives a curve to the mode sums when what it probably needs is less than that: its whole blocks,
+// half a block lost at the end of each of the 4 runs and fewer that Silverman's width makes, and the
+// steps.  They meet at n = 32, 64, 107, 200, 350 and 690 for sigma_t = 2, 0.6, 0.3, 0.2, 0.1 and 0.05 (1,
+// 2, 3, 5, 9 and 17 groups).  The preparation gives a curve back to the pair sums when its samples
+// are scattered over more node blocks than that and one block more (of curves with Silverman's
+// width 3% and fewer where the mode sums begin, and none beyond): it then costs its part of one more
+// section, 1% to 5% of the pair sums' time for searches of 64 curves.
+inline double mode_even(int n, int groups) { return (9.2e-4 * n * n + 0.08 * n + 0.5) / groups; }
+inline int mode_limit(int n, int groups) { return (int)(2.0 * mode_even(n, groups)) + 2; }
+inline bool mode_takes(int n, int groups) {
+    const int expect = (n + 31) / 32 + 2 + n / 200;
+    return expect <= 0.935 * mode_even(n, groups) && expect <= n / 5;
 }
-inline int mode_expect(int n) { return (n + 31) / 32 + 2 + n / 200; }
-// Blocks a curve has room for: the preparation gives a curve back to the pair sums when its samples
-// are so scattered over node blocks that they need more.  Twice the blocks of equal time, since
-// such a curve runs in launches of its own; n / 5 bounds the tables by the size of the pair sums'
-// table of kernel values.
+// Blocks a curve has room for; n / 5 bounds the tables by the size of the pair sums' table of kernel
+// values.
 inline int mode_room(int n, int groups) {
-    const int room = 2 * mode_even(n, groups);
+    const int room = mode_limit(n, groups) / 2;
     return room < n / 5 ? room : n / 5;
 }
 // Coefficients stored per curve (whole groups).
@@ -118,7 +123,9 @@ constexpr int kTiles64 = 3;
 // up to 1 ns; they meet at n = 138, 245, 690 and 1370 for sigma_t = 0.6, 0.3, 0.1 and 0.05 (7, 11, 29
 // and 56 groups).
 inline bool mode64_takes(int n, int groups) { return n >= 25 * groups - 30; }
-// Blocks a curve has room for: its own, half as many again lost to the ends of groups (more and it
+// The same limit, in blocks of four samples: 0.042 ns each per group, a third of that per step.
+inline int mode64_limit(int n, int groups) { return (int)(2.2e-2 * n * n / groups) + 16; }
+// Blocks a curve has room for: its own, half as many again lost to the ends of runs (more and it
 // is given back to the pair sums).
 inline int mode64_room(int n) { return n / 4 + n / 8 + 8; }
 struct ModeCurve {
@@ -126,6 +133,8 @@ struct ModeCurve {
     int32_t cap;    // blocks there is room for; 0: the curve is left to the pair sums
     int32_t blocks; // blocks in use
     int32_t groups; // passes over the samples; 0: left to the pair sums
+    int32_t limit;  // 2 blocks + steps from which the pair sums are faster
+    int32_t pad;
     int32_t nodes;  // frequencies per refinement window whose sums the window's points are
                     // interpolated from; 0: every point is summed
     double c0;      // coefficient of the constant term

@@ -193,8 +193,10 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
     } else if (xcd_grouped) {
         const int xcd = (int)(blk % kXcds);
         const int seq = (int)(blk / kXcds);
-        rank = (seq / tiles) * kXcds + xcd;
-        tile = seq - (seq / tiles) * tiles;
+        // (turned by one die per round of curves: what is skipped in a pattern spreads over the dies)
+        const int round = seq / tiles;
+        rank = round * kXcds + (xcd + round) % kXcds;
+        tile = seq - round * tiles;
     } else {
         rank = (int)(blk / tiles);
         tile = (int)(blk - (unsigned)rank * tiles);

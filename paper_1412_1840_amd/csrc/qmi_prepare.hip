@@ -277,7 +277,7 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
                 f += (g_first[g + 1] - g_first[g] + 31) >> 5;
             }
             if (tid == 0) g_block[n_groups] = n_blocks;
-            sparse = n_blocks > M.cap;
+            sparse = n_blocks > M.cap || 2 * n_blocks + n_groups > M.limit;
         }
         __syncthreads();
     }
@@ -549,7 +549,7 @@ prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
                 f += (g_first[g + 1] - g_first[g] + 3) >> 2;
             }
             if (tid == 0) g_block[n_groups] = n_blocks;
-            sparse = n_blocks > M.cap;
+            sparse = n_blocks > M.cap || 2 * n_blocks + n_groups > M.limit;
         }
         __syncthreads();
     }

@@ -111,7 +111,7 @@ peaks_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coar
     __shared__ int wn[NW];
     const int c = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const double* q = coarse + (int64_t)c * F;
-    const bool ok = cp[c].status == 0;
+    const bool ok = cp[c].status == 0 && !cp[c].sparse;  // (no scores: left to the pair sums)
     int k_lo = 0, k_hi = F;  // this block's points
     if (PART) {
         const int len = (F + (int)gridDim.y - 1) / (int)gridDim.y;
@@ -300,7 +300,7 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
     __shared__ int n_ties;
     const int c = blockIdx.x;
     const CurveParams P = cp[c];
-    const int npk = (top_k > 0 && n_fine > 0 && P.status == 0) ? po.npk[c] : 0;
+    const int npk = (top_k > 0 && n_fine > 0 && P.status == 0 && !P.sparse) ? po.npk[c] : 0;
     const int64_t S = (int64_t)top_k * n_fine;
     const int n_pts = npk * n_fine;
     const double* q = fine + (int64_t)c * S;
@@ -380,7 +380,7 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
     r.psnr = P.psnr;
     r.n = P.n;
     r.status = P.status;
-    // 1: the host searches the curve again by the pair sums; 2: it has its near ties decided by them.
+    // 1: the pair sums take the curve over; 2: they decide its near ties.
     r.reserved = P.sparse ? 1 : listed ? 2 : 0;
     r.n_peaks = npk;
     const int am = (P.status == 0) ? po.argmax[c] : -1;

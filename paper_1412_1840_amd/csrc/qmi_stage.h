@@ -229,7 +229,8 @@ inline hipError_t download(Stage& sg, const Download& dn, hipStream_t st, bool m
         // A round: pieces of the results until the block is full.
         now.clear();
         size_t in = 0;
-        while (seg < (int)dn.segs.size() && in < sg.bytes && now.size() < (size_t)kStageChunks) {
+        while (seg < (int)dn.segs.size() && in < sg.bytes &&
+               (!team || now.size() < (size_t)kStageChunks)) {
             const size_t len = std::min({team ? kStageChunk : sg.bytes, dn.segs[seg].bytes - at,
                                          sg.bytes - in});
             e = hipMemcpyAsync(sg.p + in, dn.segs[seg].src + at, len, hipMemcpyDeviceToHost, st);
