@@ -469,18 +469,29 @@ struct PairTables {
     }
 };
 
+// The mode sums' tables and the partial sums of a section are no longer needed by the current operation:
+// they go when memory is short.
+void release_mode_tables(qmi_ctx* ctx) {
+    for (int id : {qmi_ctx::kModeTs, qmi_ctx::kModeRows, qmi_ctx::kModeFrag, qmi_ctx::kModePart,
+                   qmi_ctx::kModeB, qmi_ctx::kModeCoef, qmi_ctx::kPart})
+        ctx->in_use &= ~(1ull << id);
+}
+
 // The near ties of the curves tied[] (indices into cp and the group's arrays): their listed points
 // scored by the pair sums, in groups of curves whose tables stay small, and the records written anew.
 // The choice among points that differ by less than the sums' errors is then the pair sums' own,
-// whichever path a curve takes.  Costs a second round trip where there are any: 0.3 ms for one curve of
-// 617 samples (one search in sixty), 1.3 ms of 95 for a batch of 768 survey curves.
+// whichever path a curve takes.  The tables take the place of the mode sums' where memory is short, and
+// the groups get smaller: one curve's tables are what the group was planned with.
+// Costs a second round trip where there are any: 0.3 ms for one curve of 617 samples (one search in
+// sixty), 1.3 ms for a batch of 768 survey curves.
 int decide_ties(qmi_ctx* ctx, const std::vector<CurveParams>& cp, const std::vector<int32_t>& tied,
                 int64_t ns, const double* t, const double* y, const double* e, int top_k,
                 int n_fine, int score_kind, double skew_lambda, double skew_mu, const double* fine,
                 const double* fine2, const PeakOut& pk, const TieDev& tie, DevResult* dres,
                 qmi_result* out) {
-    constexpr int64_t kTables = int64_t(64) << 20;  // kernel values of a group (or one curve)
+    int64_t room = int64_t(16) << 20;  // kernel values of a group, unless one curve has more
     hipStream_t st = ctx->stream;
+    release_mode_tables(ctx);
     for (size_t i0 = 0, i1 = 0; i0 < tied.size(); i0 = i1) {
         std::vector<CurveParams> c2;
         std::vector<int32_t> order;
@@ -489,7 +500,7 @@ int decide_ties(qmi_ctx* ctx, const std::vector<CurveParams>& cp, const std::vec
         int max_n = 2;
         for (; i1 < tied.size(); ++i1) {
             CurveParams p = cp[tied[i1]];
-            if (i1 > i0 && tab.k + p.n * round_up(p.n, kPass) > kTables / 4) break;
+            if (i1 > i0 && tab.k + p.n * round_up(p.n, kPass) > room) break;
             row_start.push_back(tab.rows);
             order.push_back((int32_t)c2.size());
             tab.add(p);
@@ -510,10 +521,12 @@ int decide_ties(qmi_ctx* ctx, const std::vector<CurveParams>& cp, const std::vec
                                  {qmi_ctx::kRD, ns * 8}, {qmi_ctx::kKS, tab.ks * 4},
                                  {qmi_ctx::kPart, tab.pieces * kTieMax * 24}})
             if ((rc = acquire(ctx, id, (size_t)bytes)) != QMI_OK) break;
-        if (rc == QMI_ENOMEM) {  // no room beside the group's buffers: the refinement's choice stays
+        if (rc == QMI_ENOMEM && m > 1) {
             ctx->err.clear();
             (void)hipGetLastError();
-            break;
+            room = tab.k / 2;
+            i1 = i0;
+            continue;
         }
         if (rc != QMI_OK) return rc;
         char* d = dptr<char>(ctx, qmi_ctx::kTieUp);
@@ -1143,9 +1156,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
         ps.trials = false;
         if (ctx->ws_base)
             ctx->ws_used = (size_t)((char*)ctx->ws_ptr[qmi_ctx::kUp] - ctx->ws_base) + at_mc;
-        for (int id : {qmi_ctx::kModeTs, qmi_ctx::kModeRows, qmi_ctx::kModeFrag, qmi_ctx::kModePart,
-                       qmi_ctx::kModeB, qmi_ctx::kModeCoef})
-            ctx->in_use &= ~(1ull << id);
+        release_mode_tables(ctx);
         const int rc2 = pair_tables(ps);
         if (rc2 != QMI_OK) return rc2;
         split(ps);
