@@ -139,7 +139,6 @@ struct ModeCurve {
                     // interpolated from; 0: every point is summed
     double c0;      // coefficient of the constant term
     double sj0;     // w sum_q b_q^2
-    double n0;      // p sum_q b_q
 };
 
 struct ModeDev {

@@ -227,7 +227,8 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
     float minus_one = -1.0f;
     asm volatile("" : "+s"(minus_one));
 
-    double SJ = M.c0 * M.sj0, ST = M.c0 * M.n0 * M.n0, SC = M.c0 * M.n0 * M.sj0;
+    const double n0 = (double)P.n;  // p sum_q b_q
+    double SJ = M.c0 * M.sj0, ST = M.c0 * n0 * n0, SC = M.c0 * n0 * M.sj0;
     if (SPLIT) SJ = ST = SC = 0.0;
     for (int g = g0; g < g_end; ++g) {
         const int m0 = g * kModeGroup + 1;
@@ -372,10 +373,12 @@ modes_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ ord
             }
             const double cm = coef[m0 - 1 + m];
             const double ca = kNodeP * v[1], sa = kNodeP * v[2];
-            // (at f = 0 every a_qm is b_q: the sums are then exact)
-            gj = fma(cm, f == 0.0 ? M.sj0 : kNodeW * v[0], gj);
-            gt = fma(cm, f == 0.0 ? M.n0 * M.n0 : ca * ca + sa * sa, gt);
-            gc = fma(cm, f == 0.0 ? M.n0 * M.sj0 : kNodeW * (ca * v[3] + sa * v[4]), gc);
+            // Where all phases coincide (no sine left at all, and cosines of 1) every a_qm is b_q: the
+            // sums are then exact.
+            const bool together = v[2] == 0.0 && v[4] == 0.0 && fabs(ca - n0) <= 1e-5 * n0;
+            gj = fma(cm, together ? M.sj0 : kNodeW * v[0], gj);
+            gt = fma(cm, together ? n0 * n0 : ca * ca + sa * sa, gt);
+            gc = fma(cm, together ? n0 * M.sj0 : kNodeW * (ca * v[3] + sa * v[4]), gc);
         }
         for (int o = 16; o < 64; o <<= 1) {
             gj += __shfl_xor(gj, o, 64);
@@ -425,7 +428,8 @@ mode_epilogue_kernel(const CurveParams* __restrict__ cp, const int32_t* __restri
         return;
     }
     if (M.groups == 0) return;
-    double SJ = M.c0 * M.sj0, ST = M.c0 * M.n0 * M.n0, SC = M.c0 * M.n0 * M.sj0;
+    const double n0 = (double)P.n;  // p sum_q b_q
+    double SJ = M.c0 * M.sj0, ST = M.c0 * n0 * n0, SC = M.c0 * n0 * M.sj0;
     for (int g = 0; g < M.groups; ++g) {
         const double* pp = out.part + ((rank * gmax + g) * fp.count + slot) * 3;
         SJ += pp[0];

@@ -83,7 +83,8 @@ modes64_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ o
     const double* coef = md.coef + (int64_t)c * mode_stride(md.mode_cap);
     double (*S)[64] = S_all[wave];
 
-    double SJ = M.c0 * M.sj0, ST = M.c0 * M.n0 * M.n0, SC = M.c0 * M.n0 * M.sj0;
+    const double n0 = (double)P.n;  // p sum_q b_q
+    double SJ = M.c0 * M.sj0, ST = M.c0 * n0 * n0, SC = M.c0 * n0 * M.sj0;
     if (SPLIT) SJ = ST = SC = 0.0;
     for (int g = g0; g < g_end; ++g) {
         const int m0 = g * kModeGroup64 + 1;
@@ -192,10 +193,11 @@ modes64_kernel(const CurveParams* __restrict__ cp, const int32_t* __restrict__ o
             }
             const double cm = coef[m0 - 1 + m];
             const double ca = kNodeP64 * v[1], sa = kNodeP64 * v[2];
-            // (at f = 0 every a_qm is b_q: the sums are then exact)
-            gj = fma(cm, f == 0.0 ? M.sj0 : kNodeW64 * v[0], gj);
-            gt = fma(cm, f == 0.0 ? M.n0 * M.n0 : ca * ca + sa * sa, gt);
-            gc = fma(cm, f == 0.0 ? M.n0 * M.sj0 : kNodeW64 * (ca * v[3] + sa * v[4]), gc);
+            // (every a_qm is b_q, as in the mixed mode)
+            const bool together = v[2] == 0.0 && v[4] == 0.0 && fabs(ca - n0) <= 1e-5 * n0;
+            gj = fma(cm, together ? M.sj0 : kNodeW64 * v[0], gj);
+            gt = fma(cm, together ? n0 * n0 : ca * ca + sa * sa, gt);
+            gc = fma(cm, together ? n0 * M.sj0 : kNodeW64 * (ca * v[3] + sa * v[4]), gc);
         }
         for (int o = 16; o < 64; o <<= 1) {
             gj += __shfl_xor(gj, o, 64);

@@ -382,7 +382,7 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
         }
     }
     __syncthreads();
-    double sq = 0.0, sb = 0.0;
+    double sq = 0.0;
     if (tid < kSumThreads)
         for (int q = tid; q < 16 * n_rows; q += kSumThreads) {
             const int row = q >> 4;
@@ -397,10 +397,8 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
                     b += part[(int64_t)(2 * r + row - g_row[g]) * 16 + (q & 15)];
             bsum[q] = b;
             sq = fma(b, b, sq);
-            sb += b;
         }
     sq = block_sum(sq, red);
-    sb = block_sum(sb, red);
     // Coefficients, and the number of harmonics to keep.
     const int cap = md.mode_cap, L = 3 * cap + 32;
     double* ev = psh;
@@ -450,7 +448,6 @@ prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
         M.nodes = (ired[1] > 0 && ired[1] <= kWinNodesMax && 2 * ired[1] <= md.n_fine) ? ired[1] : 0;
         M.c0 = cs[0];
         M.sj0 = kNodeW * sq;
-        M.n0 = kNodeP * sb;
         md.curves[c] = M;
         cp[c].ipy = kInvSqrt2Pi / sigma_y * M.sj0 / ((double)n * (double)n);
     }
@@ -606,15 +603,13 @@ prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
         if (lane < 16) bsum[16 * k + lane] = v;
     }
     __syncthreads();
-    double sq = 0.0, sb = 0.0;
+    double sq = 0.0;
     if (tid < kSumThreads)
         for (int q = tid; q < 16 * n_rows; q += kSumThreads) {
             const double b = bsum[q];
             sq = fma(b, b, sq);
-            sb += b;
         }
     sq = block_sum(sq, red);
-    sb = block_sum(sb, red);
     const int cap = md.mode_cap, L = 3 * cap + 32;
     double* ev = psh;
     double* ct = psh + L;
@@ -635,7 +630,6 @@ prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
         M.nodes = 0;
         M.c0 = cs[0];
         M.sj0 = kNodeW64 * sq;
-        M.n0 = kNodeP64 * sb;
         md.curves[c] = M;
         cp[c].ipy = kInvSqrt2Pi / P.sigma_y * M.sj0 / ((double)n * (double)n);
     }

@@ -72,3 +72,19 @@ def test_zero_frequency(ctx):
                                          want_ips=True)
         vj, ipt, _ = ips[0, 0]
         assert abs(vj - ipy[0] * ipt) <= 2e-9 * vj
+
+
+@pytest.mark.parametrize("precision", [qmi.PREC_MIXED, qmi.PREC_FP64])
+def test_all_phases_alike(ctx, precision):
+    """Equal times at any frequency, and times on a grid at multiples of its frequency: the kernel of
+    times is 1 everywhere, so that V_J = V_M = V_C up to the rounding of the FP64 steps that follow, 1e-15
+    of nCKP's scale sqrt(N st) IP_t / IP_y = sqrt(N / st) / sqrt(2 pi) and a dozen of them."""
+    for n in (300, 617, 3000):
+        y = synth.survey_batch_curve(43, n=n).y
+        e = np.full(n, 0.1)
+        for t, f in ((np.full(n, 51234.5678), [0.0, 1e-3, 0.37, 9.1]),
+                     (50000 + 0.25 * np.arange(n), [4.0, 8.0, 400.0])):
+            kw = dict(precision=precision)
+            q, _, _, _ = ctx.periodogram([0, n], t, y, e, np.array(f), 0.3, **kw)
+            c, _, _, _ = ctx.periodogram([0, n], t, y, e, np.array(f), 0.3, score=qmi.SCORE_NCKP, **kw)
+            assert np.abs(q).max() <= 1e-13 and np.abs(c).max() <= 1e-13 * np.sqrt(n / 0.3)
