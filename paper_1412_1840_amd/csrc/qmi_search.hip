@@ -337,14 +337,20 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
     for (int v = 1; v < BLOCK / 64; ++v)
         if (ranks_before(wb[v], best)) best = wb[v];
     // The points that the mode sums cannot tell from the best (tie_margin), where there are any
-    // besides it; with more than kTieMax the margin is halved until they fit.
+    // besides it; with more than kTieMax the margin is halved until they fit.  After kTieHalvings
+    // (1e-7 of the margin, below the sums' rounding) they count as equal: the first one stays.  A wave
+    // counts its points at once, and a pass ends when there are too many of them.
     int listed = 0;
     if (tie.count && P.status == 0 && npk > 0 && best.s != 0x7fffffff &&
         tie.curves[c].groups > 0) {
+        constexpr int kTieHalvings = 24;
+        const int lane = threadIdx.x & 63;
+        volatile int* total = &n_ties;
         double margin = tie_margin(P, score_kind, best.q);
         int found;
-        for (;;) {
-            for (int s0 = threadIdx.x; s0 < n_pts; s0 += kUnroll * BLOCK) {
+        for (int halvings = 0;; ++halvings) {
+            for (int s0 = threadIdx.x; s0 - lane < n_pts; s0 += kUnroll * BLOCK) {
+                if (*total > kTieMax) break;
                 double v[kUnroll];
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u) {
@@ -354,16 +360,23 @@ best_kernel(const CurveParams* __restrict__ cp, const double* __restrict__ coars
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u) {
                     const int s = s0 + u * BLOCK;
-                    if (!(v[u] >= best.q - margin) || in_mask(md, freq(s), v[u])) continue;
-                    const int at = atomicAdd(&n_ties, 1);
-                    if (at < kTieMax) tie.slot[c * kTieMax + at] = s;
+                    const bool in = v[u] >= best.q - margin && !in_mask(md, freq(s), v[u]);
+                    const unsigned long long m = __ballot(in);
+                    if (m == 0) continue;
+                    int at = 0;
+                    if (lane == 0) at = atomicAdd(&n_ties, __popcll(m));
+                    at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1));
+                    if (in && at < kTieMax) tie.slot[c * kTieMax + at] = s;
                 }
             }
             __syncthreads();
             found = n_ties;
-            margin = margin > 1e-15 * fabs(best.q) ? 0.5 * margin : -1.0;
-            if (margin < 0.0 && found > kTieMax) found = 1;  // equal values: the first one
             if (found <= kTieMax) break;
+            if (halvings == kTieHalvings) {
+                found = 1;
+                break;
+            }
+            margin *= 0.5;
             __syncthreads();
             if (threadIdx.x == 0) n_ties = 0;
             __syncthreads();
