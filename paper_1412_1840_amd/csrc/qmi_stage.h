@@ -18,9 +18,9 @@
 #include <cstdint>
 #include <cstring>
 #include <functional>
-#include <system_error>
-#include <thread>
 #include <vector>
+
+#include "qmi_team.h"
 
 namespace qmi {
 
@@ -33,27 +33,6 @@ constexpr int kStageChunks = (int)(kStageMax / kStageChunk);
 // Threads pay from about this many bytes on (starting and joining a team takes 0.1 ms, as long as
 // one thread takes to move 0.5 MB into fresh pages).
 constexpr size_t kTeamBytes = size_t(2) << 20;
-constexpr int kTeamMax = 8;
-
-// Runs work(k) for k in [0, n) on up to kTeamMax threads, the caller among them; work must not
-// throw.  Threads that cannot be started are done without.
-template <typename F>
-void run_team(int64_t n, const F& work) {
-    std::atomic<int64_t> next{0};
-    auto body = [&] {
-        for (int64_t k; (k = next.fetch_add(1, std::memory_order_relaxed)) < n;) work(k);
-    };
-    std::thread team[kTeamMax];
-    int started = 0;
-    const int hw = (int)std::thread::hardware_concurrency();
-    const int64_t want = std::min<int64_t>({n, (int64_t)kTeamMax, (int64_t)(hw > 0 ? hw : 1)});
-    try {
-        for (; started + 1 < want; ++started) team[started] = std::thread(body);
-    } catch (const std::system_error&) {
-    }
-    body();
-    for (int k = 0; k < started; ++k) team[k].join();
-}
 
 // A context's page-locked block, used by one call at a time.  A call that ends with an error may
 // leave copies of it in flight: the next one waits for them first.
