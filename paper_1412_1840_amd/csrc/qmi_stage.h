@@ -114,7 +114,8 @@ struct Upload {
     }
 };
 
-// Queues the copy of an upload to dst.  may_grow: page-locked memory may be allocated.
+// Queues the copy of an upload to dst; the sources may go when it returns.  may_grow: page-locked
+// memory may be allocated.
 inline hipError_t upload(Stage& sg, const Upload& up, char* dst, int device, hipStream_t st,
                          bool may_grow) {
     hipError_t e = sg.busy ? hipStreamSynchronize(st) : hipSuccess;
@@ -123,9 +124,11 @@ inline hipError_t upload(Stage& sg, const Upload& up, char* dst, int device, hip
     if (!(may_grow ? sg.grow(up.total, st) : sg.bytes >= up.total)) {
         for (const Upload::Seg& s : up.segs) {
             e = hipMemcpyAsync(dst + s.at, s.src, s.bytes, hipMemcpyHostToDevice, st);
-            if (e != hipSuccess) return e;
+            if (e != hipSuccess) break;
         }
-        return e;
+        // A copy of pageable memory may still read it after the call that queued it.
+        const hipError_t w = hipStreamSynchronize(st);
+        return e != hipSuccess ? e : w;
     }
     for (size_t lo = 0; lo < up.total; lo += sg.bytes) {
         if (lo > 0 && (e = hipStreamSynchronize(st)) != hipSuccess) return e;
@@ -194,10 +197,11 @@ inline hipError_t download(Stage& sg, const Download& dn, hipStream_t st, bool m
             e = hipMemcpyAsync(s.direct ? s.direct : tmp.data(), s.src, s.bytes,
                                hipMemcpyDeviceToHost, st);
             if (e == hipSuccess && !s.direct) e = hipStreamSynchronize(st);
-            if (e != hipSuccess) return e;
+            if (e != hipSuccess) break;
             if (!s.direct) s.put(tmp.data(), 0, s.bytes);
         }
-        e = hipStreamSynchronize(st);
+        const hipError_t w = hipStreamSynchronize(st);  // also the copies before one that failed
+        if (e == hipSuccess) e = w;
         sg.busy = e != hipSuccess;
         return e;
     }
