@@ -28,7 +28,9 @@
  * in short runs, with FP64 beyond.
  *
  * Error behaviour: every function returns QMI_OK (0) or a negative QMI_E* code.  A call-level error
- * leaves every output buffer untouched and records a message for qmi_last_error.  A problem with
+ * leaves every output buffer untouched and records a message for qmi_last_error; where the device
+ * fails in the middle of a call's work (QMI_EDEVICE), or its memory runs out there, arrays of samples
+ * and scores, and records of curves whose group was finished, may have been written.  A problem with
  * one curve (N < 2, a non-finite sample, a degenerate width rule) does not fail the call: that
  * curve's status is set and its outputs are NaN.  No C++ exception crosses this interface.
  *

@@ -1790,8 +1790,10 @@ int preprocess_call(qmi_ctx* ctx, const qmi_batch* b, const qmi_preprocess_param
         return QMI_EINVAL;
     }
     const int32_t nc = b->n_curves;
-    offsets_out[0] = 0;
-    if (nc == 0) return QMI_OK;
+    if (nc == 0) {
+        offsets_out[0] = 0;
+        return QMI_OK;
+    }
     const int64_t ns = b->offsets[nc];
     std::vector<int32_t> st_in(nc);
     curve_statuses(0, nc, ns, st_in.data(), [&](int32_t k) {
@@ -1833,23 +1835,22 @@ int preprocess_call(qmi_ctx* ctx, const qmi_batch* b, const qmi_preprocess_param
     small.add(stt.data(), pd.status, nc * 4);
     small.add(det.data(), pd.detrended, nc);
     HIP_OK(ctx, download(ctx->stage, small, st, true));
-    for (int32_t k = 0; k < nc; ++k) {
-        offsets_out[k + 1] = offsets_out[k] + (stt[k] == QMI_OK ? cnt[k] : 0);
-        if (status_out) status_out[k] = stt[k];
-        if (detrended_out) detrended_out[k] = det[k];
-    }
+    std::vector<int64_t> dense_off(nc + 1, 0);
+    for (int32_t k = 0; k < nc; ++k)
+        dense_off[k + 1] = dense_off[k] + (stt[k] == QMI_OK ? cnt[k] : 0);
     // Dense output: each accepted curve's kept samples (the first of its span); rejected curves
-    // keep none.
+    // keep none.  Offsets and statuses are written when all samples are down.
     const int64_t* off = b->offsets;
-    auto dense = [off, nc, offsets_out](double* to) {
+    const int64_t* to_off = dense_off.data();
+    auto dense = [off, nc, to_off](double* to) {
         return [=](const char* from, size_t at, size_t len) {
             const int64_t lo = (int64_t)(at / 8), hi = lo + (int64_t)(len / 8);
             int32_t k = (int32_t)(std::upper_bound(off, off + nc + 1, lo) - off) - 1;
             for (; k < nc && off[k] < hi; ++k) {
-                const int64_t m = offsets_out[k + 1] - offsets_out[k];
+                const int64_t m = to_off[k + 1] - to_off[k];
                 const int64_t x0 = std::max(lo, off[k]), x1 = std::min(hi, off[k] + m);
                 if (x0 < x1)
-                    std::memcpy(to + offsets_out[k] + (x0 - off[k]), from + (x0 - lo) * 8,
+                    std::memcpy(to + to_off[k] + (x0 - off[k]), from + (x0 - lo) * 8,
                                 (x1 - x0) * 8);
             }
         };
@@ -1859,6 +1860,9 @@ int preprocess_call(qmi_ctx* ctx, const qmi_batch* b, const qmi_preprocess_param
     dn.add(dense(y_out), pd.y_out, ns * 8);
     if (b->e) dn.add(dense(e_out), pd.e_out, ns * 8);
     HIP_OK(ctx, download(ctx->stage, dn, st, true));
+    std::copy(dense_off.begin(), dense_off.end(), offsets_out);
+    if (status_out) std::copy(stt.begin(), stt.end(), status_out);
+    if (detrended_out) std::copy(det.begin(), det.end(), detrended_out);
     return QMI_OK;
 }
 
