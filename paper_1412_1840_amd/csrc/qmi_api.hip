@@ -1228,25 +1228,27 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
             HIP_OK(ctx, download(ctx->stage, dn, st, !ctx->ws_base));
             return QMI_OK;
         };
-        if ((rc = results(cs.out + g.c0, !rows_last)) != QMI_OK) return rc;
+        // The caller's records are written last: what follows may still fail.
+        std::vector<qmi_result> res(nc);
+        if ((rc = results(res.data(), !rows_last)) != QMI_OK) return rc;
         if (tie.count) {
             std::vector<int32_t> tied;
             for (int32_t i = 0; i < nc; ++i)
-                if (cs.out[g.c0 + i].status == QMI_OK && cs.out[g.c0 + i].reserved == 2)
+                if (res[i].status == QMI_OK && res[i].reserved == 2)
                     tied.push_back(i);
             if (!tied.empty()) {
                 rc = decide_ties(ctx, cp, tied, ns, t, y, e, top_k, n_fine, score_kind, skew_lambda,
-                                 skew_mu, fine, fine2, pk, tie, dres, cs.out + g.c0);
+                                 skew_mu, fine, fine2, pk, tie, dres, res.data());
                 if (rc != QMI_OK) return rc;
             }
         }
         for (int32_t i = 0; i < nc; ++i)
-            if (cs.out[g.c0 + i].status == QMI_OK && cs.out[g.c0 + i].reserved == 1) left.push_back(i);
+            if (res[i].status == QMI_OK && res[i].reserved == 1) left.push_back(i);
         if (!left.empty()) {
             std::vector<qmi_result> again(nc);
             if ((rc = pair_pass({})) != QMI_OK || (rc = results(again.data(), true)) != QMI_OK)
                 return rc;
-            for (int32_t i : left) cs.out[g.c0 + i] = again[i];
+            for (int32_t i : left) res[i] = again[i];
         } else if (rows_last && (rc = results(nullptr, true)) != QMI_OK) {
             return rc;
         }
@@ -1264,7 +1266,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
                     if (!(trp[q] == trp[q])) cs.scores_out[(int64_t)g.c0 * F1 + q] = NAN;
         }
         for (int32_t i = 0; i < nc; ++i) {
-            qmi_result& rr = cs.out[g.c0 + i];
+            qmi_result& rr = res[i];
             rr.reserved = 0;
             if (cp[i].status != QMI_OK) {
                 // The kernels skipped this curve; make its record explicit.
@@ -1285,6 +1287,7 @@ int run_group(qmi_ctx* ctx, const qmi_batch* b, const CallSpec& cs, const Group&
                                          (double)(bp ? (int64_t)rr.n_peaks
                                                      : F1 + (int64_t)rr.n_peaks * n_fine);
         }
+        std::copy(res.begin(), res.end(), cs.out + g.c0);
     }
     if (cs.periodogram) {
         for (int32_t i = 0; i < nc; ++i) {
