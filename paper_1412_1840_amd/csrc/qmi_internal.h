@@ -70,20 +70,21 @@ constexpr int kModeGroup = 7;      // harmonics per pass over the samples
 constexpr int kModeCapMax = 256;     // most harmonics (sigma_t from 0.03)
 // Which curves the mode sums take.  Measured per curve and frequency (4096 to 20 000 frequencies,
 // batches): the pair sums take 9.2e-5 n^2 + 0.008 n + 0.25 ns, the mode sums 0.2 ns and, per group of
-// harmonics, 0.1 ns per block and 0.058 per step to another node block (its sums are folded).  In
+// harmonics, 0.107 ns per block and 0.06 per step to another node block (its sums are folded).  In
 // units of half a block: mode_limit is what the pair sums' time buys, 2 blocks + steps what is spent.
-// The host gives a curve to the mode sums when what it probably needs is less than that: its whole blocks,
-// half a block lost at the end of each of the 4 runs and fewer that Silverman's width makes, and the
-// steps.  They meet at n = 32, 64, 107, 200, 350 and 690 for sigma_t = 2, 0.6, 0.3, 0.2, 0.1 and 0.05 (1,
-// 2, 3, 5, 9 and 17 groups).  The preparation gives a curve back to the pair sums when its samples
+// The host gives a curve to the mode sums when what it probably needs is a tenth less than that: its whole
+// blocks, half a block lost at the end of each of the 4 runs and fewer that Silverman's width makes, and
+// the steps.  It does so from n = 38, 77, 114, 225, 400 and 770 for sigma_t = 2, 0.6, 0.3, 0.2, 0.1 and
+// 0.05 (1, 2, 3, 5, 9 and 17 groups); measured, the two sums take the same time at 32, 68, 118, 217, 385
+// and 730.  The preparation gives a curve back to the pair sums when its samples
 // are scattered over more node blocks than that and one block more (of curves with Silverman's
 // width 3% and fewer where the mode sums begin, and none beyond): it then costs its part of one more
 // section, 1% to 5% of the pair sums' time for searches of 64 curves.
-inline double mode_even(int n, int groups) { return (9.2e-4 * n * n + 0.08 * n + 0.5) / groups; }
+inline double mode_even(int n, int groups) { return (8.6e-4 * n * n + 0.075 * n + 0.47) / groups; }
 inline int mode_limit(int n, int groups) { return (int)(2.0 * mode_even(n, groups)) + 2; }
 inline bool mode_takes(int n, int groups) {
     const int expect = (n + 31) / 32 + 2 + n / 200;
-    return expect <= 0.935 * mode_even(n, groups) && expect <= n / 5;
+    return expect <= 0.9 * mode_even(n, groups) && expect <= n / 5;
 }
 // Blocks a curve has room for; n / 5 bounds the tables by the size of the pair sums' table of kernel
 // values.

@@ -154,25 +154,30 @@ __device__ __forceinline__ double value(const Sum& a, int r) {
 // precision before), each sample independently, a block's sum by two roundings of it, a node's sum
 // by one rounding per block of what has come together since the last carry.  Times count from a
 // sample's, so that the values are exact where phases coincide with it.  Measured against FP64 over
-// 64 curves of each length (50 to 3000 samples) at 301 frequencies on [0.001, 10]: relative errors
-// of V_J, IP_t and V_C 0.4 to 0.9 of the pair sums' rms up to 200 samples and 0.1 to 0.5 beyond
-// (N = 617, sigma_t 0.3: 2.5e-9, 1.7e-9 and 2.1e-9 against 1.2e-8, 1.1e-8 and 2.1e-8), of QMI and
-// nCKP less (1.8e-9 against 4.2e-8; 2.4e-8 against 2.2e-7 of the highest nCKP).
+// 8 to 64 curves of each length (56 to 3000 samples) at 301 frequencies on [0.001, 10]: rms errors
+// of V_J, IP_t and V_C 0.04 to 0.7 of the pair sums' (N = 617, sigma_t 0.3: 2.5e-9, 1.3e-9 and 1.8e-9
+// against 1.2e-8, 1.1e-8 and 2.1e-8), of QMI and nCKP less (1.7e-9 against 4.2e-8; 2.1e-8 against
+// 2.2e-7 of the highest nCKP).  The sums are largest at a curve's own frequency: of 16 curves of 1000
+// samples V_J is off there by 9.2e-9, 9.6e-9 and 8.3e-9 at most for sigma_t 0.3, 0.1 and 0.6.
 //
 // Why this shape: N^2 / 2 pairs become N x 21 harmonics x 32 nodes (sigma_t 0.3) on the matrix
 // unit.  Seven harmonics are what 256 registers of two waves per SIMD hold (112 accumulators and 56
 // counts); the 16 x 16 x 32 instruction takes a lane's own eight samples as its B operand, so that
-// the harmonics go from the recurrence to the matrix unit without LDS.  Bound: per block and group
-// a wave issues 84 MFMAs (17 cycles each) and about 650 other VALU instructions (half of them
-// conversions, FP64 and sines at 5 to 9 cycles), and the two overlap only in part (a conversion
-// issued between MFMAs costs 2.7 of its 4.8 cycles).  Measured, 768 survey curves (N 300..1000),
-// 20 000 + 10 x 1000 frequencies with the windows interpolated: 126 ms of device time against 1010
+// the harmonics go from the recurrence to the matrix unit without LDS.  Bound: issue slots.  Per block
+// and group a wave issues 84 MFMAs (17 cycles each) and, counted with the folds, 800 other VALU
+// instructions (half of them conversions, FP64 and sines at 5 to 9 cycles), and the two overlap only
+// in part (a conversion issued between MFMAs costs 2.7 of its 4.8 cycles): 4600 cycles of a SIMD in
+// all, a third of them MFMAs.  104 bytes a lane are spilled (2 GB written per 0.6 s launch of 4096
+// curves, a thousandth of what HBM takes).  Measured, 768 survey curves (N 300..1000),
+// 20 000 + 10 x 1000 frequencies with the windows interpolated: 134 ms of device time against 1010
 // ms by the pair sums.  What the precision costs: 96 ms with products added to the long sums one by
 // one, no carries and the sines as the hardware gives them, but errors of V_J up to 6e-8 at N = 617
-// and 4e-7 at N = 8192; 132 ms with carries every four blocks; 155 ms after every block.
+// and 4e-7 at N = 8192; 126 ms with carries every eight blocks, but 1.7e-8 at a curve's own frequency
+// with sigma_t 0.6, where the pair sums are within 1.3e-8; 131 ms every four (1.2e-8); 155 ms after
+// every block.
 constexpr int kModeWaves = 4;
 constexpr int kModeThreads = 64 * kModeWaves;
-constexpr int kCarry = 8;   // blocks between carries
+constexpr int kCarry = 3;   // blocks between carries
 constexpr int kMS = 5;  // FP64 sums per harmonic and lane
 
 template <bool SPLIT>
@@ -453,9 +458,9 @@ mode_epilogue_kernel(const CurveParams* __restrict__ cp, const int32_t* __restri
 // of 1e-3 1/d and sigma_t 0.3) and every point's sums follow from the Chebyshev series through them
 // (FP64; truncated below kWinTol), then its scores.  One workgroup per window.
 // Bound: FP64 multiply-adds (two per point, coefficient and sum) in batches, latency for one curve.
-// Measured, 768 survey curves, 10 windows of 1000 points: 0.41 ms, and 8 ms for the mode sums at the
-// nodes, against 42 ms for the mode sums at every point; one curve: 18 + 60 against 101 us.
-// (0.56 ms and 25 us without the symmetry of nodes and points.)
+// Measured, 768 survey curves, 10 windows of 1000 points: 0.41 ms, and 11 ms for the mode sums at the
+// nodes, where they would take 58 at every point (half of the coarse grid's 116); one curve of 617
+// samples 18 us.  (0.56 ms and 25 us without the symmetry of nodes and points.)
 template <int BLOCK>
 __global__ void __launch_bounds__(BLOCK)
 mode_window_kernel(const CurveParams* __restrict__ cp, FreqPlan fp, ModeDev md, PairOut out) {
