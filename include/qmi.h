@@ -24,8 +24,10 @@
  *
  * Units: t in days, f in 1/day, y and e in magnitudes.  All floating-point arguments and results
  * are IEEE double.  Inside, the phase fold frac(f t) and the final scores are FP64; in the default
- * mixed precision the sums over samples run on half-precision pairs (22 bits) and FP32 accumulation
- * in short runs, with FP64 beyond.
+ * mixed precision the sums over samples are formed in single precision: kernel values in FP32, or
+ * sines and magnitude weights as pairs of half-precision parts (22 bits each), added in FP32 over short
+ * runs and in FP64 beyond (in the sums over magnitude nodes whole samples are counted exactly).  The
+ * potentials' relative errors are then below about 1e-7, 1e-9 to 1e-8 rms for most curves.
  *
  * Error behaviour: every function returns QMI_OK (0) or a negative QMI_E* code.  A call-level error
  * leaves every output buffer untouched and records a message for qmi_last_error; where the device

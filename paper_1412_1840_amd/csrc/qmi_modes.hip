@@ -164,10 +164,10 @@ __device__ __forceinline__ double value(const Sum& a, int r) {
 // unit.  Seven harmonics are what 256 registers of two waves per SIMD hold (112 accumulators and 56
 // counts); the 16 x 16 x 32 instruction takes a lane's own eight samples as its B operand, so that
 // the harmonics go from the recurrence to the matrix unit without LDS.  Bound: issue slots.  Per block
-// and group a wave issues 84 MFMAs (17 cycles each) and, counted with the folds, 800 other VALU
+// and group a wave issues 84 MFMAs (17 cycles each) and, counted with carries and folds, 900 other VALU
 // instructions (half of them conversions, FP64 and sines at 5 to 9 cycles), and the two overlap only
-// in part (a conversion issued between MFMAs costs 2.7 of its 4.8 cycles): 4600 cycles of a SIMD in
-// all, a third of them MFMAs.  104 bytes a lane are spilled (2 GB written per 0.6 s launch of 4096
+// in part (a conversion issued between MFMAs costs 2.7 of its 4.8 cycles): 4700 cycles of a SIMD in
+// all, 30% of them MFMAs.  104 bytes a lane are spilled (2 GB written per 0.6 s launch of 4096
 // curves, a thousandth of what HBM takes).  Measured, 768 survey curves (N 300..1000),
 // 20 000 + 10 x 1000 frequencies with the windows interpolated: 134 ms of device time against 1010
 // ms by the pair sums.  What the precision costs: 96 ms with products added to the long sums one by
@@ -458,8 +458,8 @@ mode_epilogue_kernel(const CurveParams* __restrict__ cp, const int32_t* __restri
 // of 1e-3 1/d and sigma_t 0.3) and every point's sums follow from the Chebyshev series through them
 // (FP64; truncated below kWinTol), then its scores.  One workgroup per window.
 // Bound: FP64 multiply-adds (two per point, coefficient and sum) in batches, latency for one curve.
-// Measured, 768 survey curves, 10 windows of 1000 points: 0.41 ms, and 11 ms for the mode sums at the
-// nodes, where they would take 58 at every point (half of the coarse grid's 116); one curve of 617
+// Measured, 768 survey curves, 10 windows of 1000 points: 0.41 ms, and 12 ms for the mode sums at the
+// nodes, where they would take 62 at every point (half of the coarse grid's 124); one curve of 617
 // samples 18 us.  (0.56 ms and 25 us without the symmetry of nodes and points.)
 template <int BLOCK>
 __global__ void __launch_bounds__(BLOCK)

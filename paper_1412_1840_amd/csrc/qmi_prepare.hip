@@ -117,7 +117,7 @@ int key_bytes_of(int room, int mode_cap) {
 // Bound: latency (one curve per call: a chain of sorts, scans and reductions by one workgroup),
 // FP64 exponentials where one workgroup has a long curve.  Measured against separate prologue and
 // node kernels with sorts in LDS and one exponential per node and sample: one curve of 617 samples
-// 119 -> 43 us (55 by the small block), one of 8192 1274 -> 329 us, 768 survey curves 206 -> 108 us.
+// 119 -> 46 us (55 by the small block), one of 8192 1274 -> 300 us, 768 survey curves 206 -> 104 us.
 template <int BLOCK, int EMAX>
 __global__ void __launch_bounds__(BLOCK)
 prepare_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
@@ -477,7 +477,7 @@ hipError_t launch_prepare_b(hipStream_t st, CurveParams* cp, int n_curves, int m
 
 // The node tables of the FP64 mode sums, as above but for exact operands: three node blocks per sample,
 // blocks of 4 samples, the value of every node and sample by its own exponential.  Bound: latency
-// (sort, scans, reductions); measured, 16 survey curves 95 us.
+// (sort, scans, reductions); measured, 16 survey curves 62 us.
 template <int BLOCK, int EMAX>
 __global__ void __launch_bounds__(BLOCK)
 prepare64_kernel(CurveParams* __restrict__ cp, const double* __restrict__ t_all,
